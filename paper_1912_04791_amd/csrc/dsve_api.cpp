@@ -60,9 +60,12 @@ struct dsve_ctx {
     unsigned int *d_flags = nullptr;                             // [4]
 
     int tile = 256, blocks_per_cu = 0, graph_steps = 60;
-    int32_t *d_tile_chan = nullptr;
-    int64_t n_tiles = 0;
+    bool packed = false;               // short channels: the packed step kernel (tile table)
+    int32_t *d_tile_chan = nullptr;    // its tile table
+    int64_t n_tiles = 0;               // tiles of it, or of all segments
     int table_tile = 0;
+    Segment *d_segments = nullptr;     // otherwise: the segments, of at most seg_tiles tiles each
+    int64_t n_segments = 0, seg_tiles = 0;
 
     // captured graphs, valid for the buffers and launch in g_key / g_*: the main graph of
     // graph_steps steps, and graphs of the remainders n % graph_steps of recent run lengths
@@ -204,6 +207,59 @@ static dsve_status build_tile_table(dsve_ctx *c, int tile)
     return DSVE_OK;
 }
 
+// Tiles of kSegTile cells over all channels.
+static int64_t segment_tiles(const dsve_ctx *c)
+{
+    int64_t n = 0;
+    for (int64_t k = 0; k < c->n_channels; ++k) n += (c->h_off[k + 1] - c->h_off[k] + kSegTile - 1) / kSegTile;
+    return n;
+}
+
+// Largest number of tiles in a segment (one wave's work).  With blocks_per_cu > 0, what spreads the
+// tiles over that many workgroups per compute unit.  Automatic: one tile up to about four times the
+// waves the chip holds at once, then more, up to 16, where the reads at a segment's start and the
+// merge of its CFL maximum cost little and the waves still balance.
+static int64_t segment_length(const dsve_ctx *c, int tile, int blocks_per_cu)
+{
+    const int64_t waves = (int64_t)c->cus * (blocks_per_cu > 0 ? (int64_t)blocks_per_cu * (tile / 64) : 64);
+    const int64_t per = (c->n_tiles + waves - 1) / waves;
+    return std::max<int64_t>(1, std::min<int64_t>(per, blocks_per_cu > 0 ? (int64_t)1 << 22 : 16));
+}
+
+static dsve_status build_segments(dsve_ctx *c, int tile, int blocks_per_cu)
+{
+    const int64_t len = segment_length(c, tile, blocks_per_cu);
+    if (c->d_segments && c->seg_tiles == len) return DSVE_OK;
+    std::vector<Segment> seg;
+    seg.reserve((size_t)(c->n_tiles / len + c->n_channels));
+    for (int64_t k = 0; k < c->n_channels; ++k) {
+        const int64_t off = c->h_off[k], n = c->h_off[k + 1] - off;
+        const int64_t tiles = (n + kSegTile - 1) / kSegTile, parts = (tiles + len - 1) / len;
+        int64_t t0 = 0;
+        for (int64_t p = 0; p < parts; ++p) {   // whole tiles, spread evenly over the channel's segments
+            const int64_t t1 = tiles * (p + 1) / parts;
+            const int64_t a = t0 * kSegTile, b = std::min(n, t1 * kSegTile);
+            seg.push_back(Segment{off + a, (uint32_t)((b - a) << 2) | (a == 0 ? 1u : 0u) | (b == n ? 2u : 0u), (int32_t)k});
+            t0 = t1;
+        }
+    }
+    if (seg.size() >= ((size_t)1 << 31)) return fail(c, DSVE_E_ARG, "too many segments for this launch");
+    if (c->d_segments) (void)hipFree(c->d_segments);
+    c->d_segments = nullptr;
+    HIP_TRY(c, hipMalloc(&c->d_segments, sizeof(Segment) * seg.size()));
+    HIP_TRY(c, hipMemcpy(c->d_segments, seg.data(), sizeof(Segment) * seg.size(), hipMemcpyHostToDevice));
+    c->n_segments = (int64_t)seg.size();
+    c->seg_tiles = len;
+    free_graph(c);
+    return DSVE_OK;
+}
+
+// The work table of the step kernel for a launch: segments, or the packed kernel's tile table.
+static dsve_status build_table(dsve_ctx *c, int tile, int blocks_per_cu)
+{
+    return c->packed ? build_tile_table(c, tile) : build_segments(c, tile, blocks_per_cu);
+}
+
 static dsve_status setup(dsve_ctx *c, void *stream)
 {
     // the power law with an integer exponent beta - 1 in every channel runs the product form
@@ -247,7 +303,12 @@ static dsve_status setup(dsve_ctx *c, void *stream)
     // the device address of the static scratch of adot_step_noalloc, looked up once per device
     // (a failure leaves it null: that entry point then reports it, the others do not use it)
     if (noalloc_scratch(c->device, &c->scratch) != hipSuccess) c->scratch = nullptr;
-    dsve_status st = build_tile_table(c, c->tile);
+    // a wave of the segment kernel works on one channel: where that leaves more than a fifth of the
+    // lanes without an edge (most channels shorter than about 250 cells), the packed kernel, whose
+    // tiles hold several channels, runs instead
+    c->n_tiles = segment_tiles(c);
+    c->packed = c->n_tiles * 64 > c->n_edges + c->n_edges / 4;
+    dsve_status st = build_table(c, c->tile, c->blocks_per_cu);
     if (st != DSVE_OK) return st;
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     return DSVE_OK;
@@ -269,6 +330,7 @@ static void release(dsve_ctx *c)
     (void)hipFree(c->d_amax);
     (void)hipFree(c->d_flags);
     (void)hipFree(c->d_tile_chan);
+    (void)hipFree(c->d_segments);
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
     delete c;
 }
@@ -514,13 +576,17 @@ dsve_status cfl_reduce(dsve_ctx *ctx, const double *h, const double *q, const do
     return DSVE_OK;
 }
 
-// Persistent grid: blocks_per_cu workgroups per compute unit (0 = as many as fit at once),
-// never more than there are tiles.
+// Workgroups of a step: one wave per segment; the packed kernel's persistent grid is blocks_per_cu
+// workgroups per compute unit (0 = as many as fit at once), never more than there are tiles.
 static int grid_of(const dsve_ctx *ctx)
 {
+    if (!ctx->packed) {
+        const int64_t waves = ctx->tile / 64;
+        return (int)((ctx->n_segments + waves - 1) / waves);
+    }
     const int bpc = ctx->blocks_per_cu > 0 ? ctx->blocks_per_cu
-                                           : step_blocks_per_cu(ctx->precision, ctx->G, ctx->cl, ctx->tile,
-                                                                ctx->n_edges);
+                                           : packed_blocks_per_cu(ctx->precision, ctx->G, ctx->cl, ctx->tile,
+                                                                  ctx->n_edges);
     return (int)std::min<int64_t>(ctx->n_tiles, (int64_t)bpc * ctx->cus);
 }
 
@@ -532,7 +598,7 @@ static int split_of(const dsve_ctx *ctx, int grid)
 {
     if (ctx->cfl_split > 0) return ctx->cfl_split;
     const double wg_per_channel = (double)grid / (double)ctx->n_channels;
-    const double tiles_per_wg = (double)ctx->n_tiles / (double)grid;
+    const double tiles_per_wg = (double)ctx->n_tiles / (double)grid / (ctx->packed ? 1 : ctx->tile / 64);
     return (wg_per_channel >= 256.0 && tiles_per_wg <= 4.0) ? 4 : 1;
 }
 
@@ -567,6 +633,8 @@ static StepArgs step_args(dsve_ctx *ctx, const RunBufs &b, int j, double *h, dou
     a.ch = ctx->d_ch;
     a.eoff = ctx->d_eoff;
     a.tile_chan = ctx->d_tile_chan;
+    a.segments = ctx->d_segments;
+    a.n_segments = (int32_t)ctx->n_segments;
     a.amax_cur = b.amax + (j % 3) * ctx->amax_slot;
     a.amax_next = b.amax + ((j + 1) % 3) * ctx->amax_slot;
     a.amax_clear = b.amax + ((j + 2) % 3) * ctx->amax_slot;
@@ -679,7 +747,7 @@ static dsve_status run_steps(dsve_ctx *ctx, double *h, double *q, double *z, int
         ctx->last_direct = 1;
         return DSVE_OK;
     }
-    dsve_status st = build_tile_table(ctx, ctx->tile);
+    dsve_status st = build_table(ctx, ctx->tile, ctx->blocks_per_cu);
     if (st != DSVE_OK) return st;
     if (ctx->graph_steps > 0) {
         st = ensure_graphs(ctx, h, q, z, t, n_steps);   // before any work of the run is enqueued
@@ -730,7 +798,7 @@ dsve_status dsve_prepare_run(dsve_ctx *ctx, double *h, double *q, double *z, int
     if (!h || !q || !z || !t_dev) return fail(ctx, DSVE_E_ARG, "null pointer");
     if (n_steps < 0) return fail(ctx, DSVE_E_ARG, "n_steps must be >= 0");
     if (n_steps == 0 || (ctx->resident_ok && ctx->resident_mode == 0)) return DSVE_OK;
-    dsve_status st = build_tile_table(ctx, ctx->tile);
+    dsve_status st = build_table(ctx, ctx->tile, ctx->blocks_per_cu);
     if (st != DSVE_OK || ctx->graph_steps == 0) return st;
     return ensure_graphs(ctx, h, q, z, t_dev, n_steps);
 }
@@ -793,9 +861,10 @@ dsve_status adot_step_noalloc(dsve_ctx *ctx, double *h, double *q, double *z, in
         ctx->last_direct = 1;
         return DSVE_OK;
     }
-    // the tile table of the current tile size exists from init or dsve_set_launch
-    if (!ctx->d_tile_chan || ctx->table_tile != ctx->tile)
-        return fail(ctx, DSVE_E_HIP, "adot_step_noalloc: no tile table for the current launch");
+    // the work table of the current launch exists from init or dsve_set_launch
+    if (ctx->packed ? (!ctx->d_tile_chan || ctx->table_tile != ctx->tile)
+                    : (!ctx->d_segments || ctx->seg_tiles != segment_length(ctx, ctx->tile, ctx->blocks_per_cu)))
+        return fail(ctx, DSVE_E_HIP, "adot_step_noalloc: no work table for the current launch");
     HIP_TRY(ctx, launch_fill_u64(b.amax, 3 * ctx->amax_slot, 0ull, ctx->stream));
     dsve_status st = enqueue_cfl(ctx, h, q, z, b.amax);
     if (st != DSVE_OK) return st;
@@ -864,8 +933,8 @@ dsve_status dsve_set_launch(dsve_ctx *ctx, int tile, int blocks_per_cu, int grap
     if (blocks_per_cu < 0 || blocks_per_cu > 1024) return fail(ctx, DSVE_E_ARG, "blocks_per_cu must be in [0, 1024]");
     if (graph_steps != 0 && (graph_steps % 6 || graph_steps < 6 || graph_steps > 600))
         return fail(ctx, DSVE_E_ARG, "graph_steps must be 0 or a multiple of 6 in [6, 600]");
-    if (tile != ctx->tile) {
-        dsve_status st = build_tile_table(ctx, tile);
+    if (tile != ctx->tile || blocks_per_cu != ctx->blocks_per_cu) {
+        dsve_status st = build_table(ctx, tile, blocks_per_cu);
         if (st != DSVE_OK) return st;
     }
     if (tile != ctx->tile || blocks_per_cu != ctx->blocks_per_cu || graph_steps != ctx->graph_steps)

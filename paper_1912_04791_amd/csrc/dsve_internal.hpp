@@ -146,12 +146,24 @@ template <> struct Gauss<5> {
 constexpr int kAmaxSplitMax = 4;   // CFL sub-slots per channel allocated in each slot
 inline int64_t amax_stride(int64_t n_channels) { return (n_channels + 511) / 512 * 512; }
 
+constexpr int kSegTile = 63;     // cells per tile of the step kernel (64 edges, one shared)
+
+// A run of cells of one channel, the work of one wave of the step kernel.
+struct alignas(16) Segment {
+    int64_t cell0;      // its first cell in the concatenated state
+    uint32_t n_flags;   // 4 n + (1: the channel's first cell is in it) + (2: its last cell is), n cells
+    int32_t chan;
+};
+static_assert(sizeof(Segment) == 16, "Segment layout changed");
+
 struct StepArgs {
     const double *h, *q, *z;     // W^n
     double *hn, *qn, *zn;        // W^{n+1}
     const ChanInfo *ch;
     const int64_t *eoff;         // [C+1]
-    const int32_t *tile_chan;    // [n_tiles]
+    const int32_t *tile_chan;    // [n_tiles] (packed kernel)
+    const Segment *segments;     // [n_segments]
+    int32_t n_segments;
     const unsigned long long *amax_cur;  // [S][Cs] CFL max of W^n
     unsigned long long *amax_next;       // [S][Cs] CFL max of W^{n+1} (pre-cleared)
     unsigned long long *amax_clear;      // [S][Cs] slot to clear for step n+1
@@ -210,9 +222,9 @@ struct FluctArgs {
 // hipError_t of the launch; `precision` is one of PREC_*.
 hipError_t launch_step(const StepArgs &a, int precision, int G, int cl, int tile, int grid,
                        hipStream_t stream);
-// Workgroups of the step kernel that fit on one compute unit at once (occupancy query).
-int step_blocks_per_cu(int precision, int G, int cl, int tile, int64_t n_edges);
-// The step kernel indexes cells and edges in 32 bits below 2^29 edges (byte offsets into the
+// Workgroups of the packed step kernel that fit on one compute unit at once (occupancy query).
+int packed_blocks_per_cu(int precision, int G, int cl, int tile, int64_t n_edges);
+// The packed step kernel indexes cells and edges in 32 bits below 2^29 edges (byte offsets into the
 // state arrays then fit in 32 bits), in 64 bits from there on.
 inline bool step_needs_wide_index(int64_t n_edges) { return n_edges >= (int64_t(1) << 29); }
 hipError_t launch_cfl(const CflArgs &a, int precision, int cl, hipStream_t stream);

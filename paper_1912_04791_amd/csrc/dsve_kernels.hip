@@ -1,10 +1,10 @@
 // dsve_kernels.hip -- HIP kernels of the A-DOT hot path for gfx950 (wave64).
 //
-// k_step      one fused kernel per time step over the flat edge space of all channels:
-//             ghost cells (boundary conditions), DOT fluctuation of every edge, exchange of
-//             D^- through LDS, cell update into the other ping-pong buffer, CFL speed of the
-//             new state reduced per channel (DPP lane moves -> LDS -> one global atomic max
-//             per workgroup into its CFL sub-slot).
+// k_step      one fused kernel per time step: ghost cells (boundary conditions), DOT fluctuation of
+//             every edge, exchange of D^+ with the lane above by a DPP lane move, cell update into
+//             the other ping-pong buffer, CFL speed of the new state reduced per channel (DPP lane
+//             moves -> LDS -> one global atomic max per workgroup into its CFL sub-slot).
+// k_step_packed  the same for many short channels: tiles over the flat edge space of all channels.
 // k_cfl       CFL maximum of a state (start of a run, and the cfl_reduce entry point).
 // k_fluct     pairwise fluctuations (dot_edge_fluct entry point).
 // k_update    cell update from given fluctuations (cell_update entry point).
@@ -15,11 +15,8 @@
 // the numerical eigen-decomposition of the original DOT solver (Sec. 3.1), the baseline of the
 // closed form.
 //
-// Tiling of the step kernel: a workgroup of T threads takes T consecutive edges of the flat
-// edge space and updates the T-1 cells whose two faces both lie in the tile; tile k starts at
-// edge k (T-1), so consecutive tiles share one edge, which both compute.  Every cell is
-// updated by exactly one thread and every value computed depends only on its own edge or
-// cell, so results do not depend on T or on the number of workgroups.
+// Every cell is updated by exactly one thread and every value computed depends only on its own edge
+// or cell, so results do not depend on the kernel, the workgroup size or the number of workgroups.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -163,6 +160,14 @@ __device__ __forceinline__ double ldx(const double *__restrict__ p, I i)
     if constexpr (WIDE) return p[i];
     else return *reinterpret_cast<const double *>(reinterpret_cast<const char *>(p) + ((uint32_t)i << 3));
 }
+__device__ __forceinline__ double ldx(const double *__restrict__ p, int i)
+{
+    return *reinterpret_cast<const double *>(reinterpret_cast<const char *>(p) + ((uint32_t)i << 3));
+}
+__device__ __forceinline__ void stx(double *__restrict__ p, int i, double v)
+{
+    *reinterpret_cast<double *>(reinterpret_cast<char *>(p) + ((uint32_t)i << 3)) = v;
+}
 template <bool WIDE, typename I>
 __device__ __forceinline__ void stx(double *__restrict__ p, I i, double v)
 {
@@ -171,11 +176,15 @@ __device__ __forceinline__ void stx(double *__restrict__ p, I i, double v)
 }
 
 // ---------------------------------------------------------------------------
+// Step kernel for many short channels: a workgroup of T threads takes T consecutive edges of the flat
+// edge space and updates the T-1 cells whose two faces both lie in the tile; tile k starts at edge
+// k (T-1), so consecutive tiles share one edge, which both compute, and a tile holds several whole
+// channels.  D^- goes to the left neighbour through LDS.
 template <int G, int PREC, int CL, bool WIDE>
-__global__ __launch_bounds__(kMaxTile, step_min_waves(PREC, CL)) void k_step(StepArgs A, const ChanInfo *__restrict__ CH,
-                                                                           const int64_t *__restrict__ EO,
-                                                                           const int32_t *__restrict__ TC,
-                                                                           const unsigned long long *__restrict__ AM)
+__global__ __launch_bounds__(kMaxTile, step_min_waves(PREC, CL)) void k_step_packed(StepArgs A, const ChanInfo *__restrict__ CH,
+                                                                                  const int64_t *__restrict__ EO,
+                                                                                  const int32_t *__restrict__ TC,
+                                                                                  const unsigned long long *__restrict__ AM)
 {
     extern __shared__ double s_dm_all[];      // [2][3][T]: D^- of even and odd tiles
     __shared__ unsigned long long s_acc;
@@ -329,6 +338,148 @@ __global__ __launch_bounds__(kMaxTile, step_min_waves(PREC, CL)) void k_step(Ste
     if (lane == 0 && m != 0ull) atomicMax(&s_acc, m);
     __syncthreads();
     if (t == 0 && s_acc != 0ull) flush_max(&amax_mine[home], s_acc);
+}
+
+// ---------------------------------------------------------------------------
+// Value of the lane below (lane 0 reads 0): one DPP move per 32-bit half.
+__device__ __forceinline__ double lane_below(double v)
+{
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)b, 0x138, 0xf, 0xf, true);
+    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x138, 0xf, 0xf, true);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// Step kernel over segments: each wave takes one segment, a run of cells of one channel, in tiles of
+// 64 edges (63 cells: the first edge of a tile is the last of the tile before, computed by both).
+// Lane l computes edge e = t0 + l of the segment, the left face of cell e, and updates cell e - 1,
+// whose right face it is, with D^+ of the edge below from the lane below.
+//
+// Waves share nothing until their CFL maxima are merged, so no wave waits for another at a tile, and
+// everything of the channel is the same for the whole wave (scalar registers and branches; the lanes
+// at a channel's ends fix up their ghost cell in a branch that other tiles skip).  Bound by VALU issue
+// in FP64 and by the waits of each wave on its loads and dependent instructions.  Against tiles of 256
+// edges with D^- through LDS, a barrier per tile and per-lane channel lookups, the same arithmetic
+// took, FP64: 65 536 channels of 512-4096 cells 3.12 -> 2.47 ms a step, one channel of 2^20 cells
+// 24.5 -> 22.3 us; mixed: one of 4 000 001 cells 65 -> 56 us.
+template <int G, int PREC, int CL>
+__global__ __launch_bounds__(kMaxTile, step_min_waves(PREC, CL)) void k_step(StepArgs A, const ChanInfo *__restrict__ CH,
+                                                                           const Segment *__restrict__ SEG,
+                                                                           const unsigned long long *__restrict__ AM)
+{
+    __shared__ unsigned long long s_max[kMaxTile / 64];
+    __shared__ int s_chan[kMaxTile / 64];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int waves = (int)(blockDim.x >> 6);
+    const int sidx = (int)blockIdx.x * waves + wave;
+    unsigned long long acc = 0ull;
+    int c = -1;
+    if (sidx < A.n_segments) {
+        const Segment sg = SEG[sidx];
+        const int n = (int)(sg.n_flags >> 2);
+        const bool first = (sg.n_flags & 1u) != 0u, last = (sg.n_flags & 2u) != 0u;
+        c = sg.chan;
+        const ChanInfo &ci = CH[c];
+        const Closure K = closure_of(ci);
+        const double fric = ci.fric;
+        const double dt = ci.cfl_dx * rcp_h(amax_of(AM, c, A.amax_stride, A.amax_split));
+        const double r = dt * ci.inv_dx;
+        // cell i of the segment is at index i + 1 from these bases (cell -1, the left neighbour of
+        // a segment inside a channel, at 0; a segment at its channel's start does not read it)
+        const int64_t base = sg.cell0 - 1;
+        const double *const h = A.h + base, *const q = A.q + base, *const z = A.z + base;
+        double *const hn = A.hn + base, *const qn = A.qn + base, *const zn = A.zn + base;
+        const int il_min = first ? 1 : 0, ir_max = last ? n : n + 1;
+        unsigned bad = 0u;
+        for (int t0 = 0; t0 < n; t0 += kSegTile) {
+            // lanes past the segment's last edge compute it again; they update nothing
+            const int e = t0 + lane < n ? t0 + lane : n;
+            const int il = e > il_min ? e : il_min, ir = e + 1 < ir_max ? e + 1 : ir_max;
+            double hL = ldx(h, il), qL = ldx(q, il), zL = ldx(z, il);
+            double hR = ldx(h, ir), qR = ldx(q, ir), zR = ldx(z, ir);
+            const double h0 = hL, q0 = qL, z0 = zL;
+            if (first && t0 == 0) {
+                // ghost cell left of the channel's first cell (which every lane of edge 0 holds as R)
+                double gh = hR, gq = qR, gz = zR;
+                if (ci.bcl == BC_PERIODIC) {
+                    const int64_t far = ci.cell0 + ci.ncell - 1;
+                    gh = A.h[far];
+                    gq = A.q[far];
+                    gz = A.z[far];
+                }
+                gh = ghost_h(ci.bcl, ci.bl, gh);
+                gq = ghost_q(ci.bcl, ci.bl, gq);
+                if (ci.bcl == BC_DIRICHLET) gz = ghost_z(ci.bcl, ci.bl, gz, A.t_cur[c]);
+                if (e == 0) {
+                    hL = gh;
+                    qL = gq;
+                    zL = gz;
+                }
+            }
+            if (last && t0 + 64 > n) {
+                // ghost cell right of the channel's last cell
+                double gh = h0, gq = q0, gz = z0;
+                if (ci.bcr == BC_PERIODIC) {
+                    gh = A.h[ci.cell0];
+                    gq = A.q[ci.cell0];
+                    gz = A.z[ci.cell0];
+                }
+                gh = ghost_h(ci.bcr, ci.br, gh);
+                gq = ghost_q(ci.bcr, ci.br, gq);
+                if (ci.bcr == BC_DIRICHLET) gz = ghost_z(ci.bcr, ci.br, gz, A.t_cur[c]);
+                if (e == n) {
+                    hR = gh;
+                    qR = gq;
+                    zR = gz;
+                }
+            }
+            double Dm[3], Dp[3];
+            edge_fluct<G, PREC, CL>(hL, qL, zL, hR, qR, zR, A.g, K, Dm, Dp, bad);
+            const double p0 = lane_below(Dp[0]), p1 = lane_below(Dp[1]), p2 = lane_below(Dp[2]);
+            if (lane > 0 && t0 + lane <= n) {
+                // W_i^{n+1} = W_i^n - dt/dx (D^-_{i+1/2} + D^+_{i-1/2}) + dt S(W_i^n)
+                // (Sec. 3, Eq. scheme; S from the friction slope when K_s is given)
+                const double hv = h0 - r * (Dm[0] + p0);
+                double qv = q0 - r * (Dm[1] + p1);
+                const double zv = z0 - r * (Dm[2] + p2);
+                if (fric > 0.0) qv = fma(dt, friction_source(h0, q0, A.g, fric), qv);
+                stx(hn, e, hv);
+                stx(qn, e, qv);
+                stx(zn, e, zv);
+                const double sp = fabs(cell_speed<PREC, CL>(hv, qv, A.g, K, bad));
+                const unsigned long long bits = (unsigned long long)__double_as_longlong(sp);
+                acc = bits > acc ? bits : acc;
+            }
+        }
+        if (first && lane == 0) {
+            A.t_next[c] = A.t_cur[c] + dt;
+            A.amax_clear[c] = 0ull;
+#pragma unroll
+            for (int s = 1; s < kAmaxSplitMax; ++s)
+                if (s < A.amax_split) A.amax_clear[c + s * A.amax_stride] = 0ull;
+        }
+        raise_flag(A.flags, bad);
+    }
+    // the wave's maximum; waves of one workgroup in the same channel merge theirs in LDS first
+    const unsigned long long m = wave_max_u64(acc);
+    unsigned long long *const amax_mine =
+        A.amax_next + (int64_t)(blockIdx.x & (unsigned)(A.amax_split - 1)) * A.amax_stride;
+    if (waves == 1) {
+        if (lane == 0 && m != 0ull) flush_max(&amax_mine[c], m);
+        return;
+    }
+    if (lane == 0) {
+        s_max[wave] = m;
+        s_chan[wave] = c;
+    }
+    __syncthreads();
+    const int t = (int)threadIdx.x;
+    if (t < waves && s_chan[t] >= 0 && (t == 0 || s_chan[t - 1] != s_chan[t])) {
+        unsigned long long v = s_max[t];
+        for (int w = t + 1; w < waves && s_chan[w] == s_chan[t]; ++w) v = s_max[w] > v ? s_max[w] : v;
+        if (v != 0ull) flush_max(&amax_mine[s_chan[t]], v);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -660,11 +811,11 @@ static hipError_t launch_fluct_prec(const FluctArgs &a, int G, int cl, hipStream
 }
 
 template <int PREC, bool WIDE>
-static hipError_t launch_step_prec(const StepArgs &a, int G, int cl, int tile, int grid, hipStream_t s)
+static hipError_t launch_packed_prec(const StepArgs &a, int G, int cl, int tile, int grid, hipStream_t s)
 {
     const size_t lds = sizeof(double) * 6 * (size_t)tile;
-#define DSVE_LAUNCH_STEP(GG, CC) hipLaunchKernelGGL((k_step<GG, PREC, CC, WIDE>), dim3(grid), dim3(tile), lds, s, a, \
-                                                   a.ch, a.eoff, a.tile_chan, a.amax_cur)
+#define DSVE_LAUNCH_STEP(GG, CC) hipLaunchKernelGGL((k_step_packed<GG, PREC, CC, WIDE>), dim3(grid), dim3(tile), lds, s, \
+                                                   a, a.ch, a.eoff, a.tile_chan, a.amax_cur)
     DSVE_DISPATCH_G_CL(G, cl, DSVE_LAUNCH_STEP)
 #undef DSVE_LAUNCH_STEP
     return hipGetLastError();
@@ -675,7 +826,7 @@ static hipError_t occupancy_query(int G, int cl, int tile, int &n)
 {
     const size_t lds = sizeof(double) * 6 * (size_t)tile;
     hipError_t e = hipErrorInvalidValue;
-#define DSVE_OCC(GG, CC) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_step<GG, PREC, CC, WIDE>, tile, lds)
+#define DSVE_OCC(GG, CC) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_step_packed<GG, PREC, CC, WIDE>, tile, lds)
     DSVE_DISPATCH_G_CL(G, cl, DSVE_OCC)
 #undef DSVE_OCC
     return e;
@@ -689,7 +840,7 @@ static hipError_t occupancy_of(int precision, int G, int cl, int tile, int &n)
                                    : occupancy_query<PREC_FP64, WIDE>(G, cl, tile, n);
 }
 
-int step_blocks_per_cu(int precision, int G, int cl, int tile, int64_t n_edges)
+int packed_blocks_per_cu(int precision, int G, int cl, int tile, int64_t n_edges)
 {
     int n = 0;
     const hipError_t e = step_needs_wide_index(n_edges) ? occupancy_of<true>(precision, G, cl, tile, n)
@@ -698,25 +849,42 @@ int step_blocks_per_cu(int precision, int G, int cl, int tile, int64_t n_edges)
 }
 
 template <bool WIDE>
-static hipError_t launch_step_w(const StepArgs &a, int precision, int G, int cl, int tile, int grid,
-                                hipStream_t stream)
+static hipError_t launch_packed_w(const StepArgs &a, int precision, int G, int cl, int tile, int grid,
+                                  hipStream_t stream)
 {
-    if (precision == PREC_FP64) return launch_step_prec<PREC_FP64, WIDE>(a, G, cl, tile, grid, stream);
-    if (precision == PREC_MIXED) return launch_step_prec<PREC_MIXED, WIDE>(a, G, cl, tile, grid, stream);
-    if (precision == PREC_DOT) return launch_step_prec<PREC_DOT, WIDE>(a, G, cl, tile, grid, stream);
+    if (precision == PREC_FP64) return launch_packed_prec<PREC_FP64, WIDE>(a, G, cl, tile, grid, stream);
+    if (precision == PREC_MIXED) return launch_packed_prec<PREC_MIXED, WIDE>(a, G, cl, tile, grid, stream);
+    if (precision == PREC_DOT) return launch_packed_prec<PREC_DOT, WIDE>(a, G, cl, tile, grid, stream);
     return hipErrorNotSupported;
+}
+
+template <int PREC>
+static hipError_t launch_step_prec(const StepArgs &a, int G, int cl, int tile, int grid, hipStream_t s)
+{
+#define DSVE_LAUNCH_STEP(GG, CC) hipLaunchKernelGGL((k_step<GG, PREC, CC>), dim3(grid), dim3(tile), 0, s, \
+                                                   a, a.ch, a.segments, a.amax_cur)
+    DSVE_DISPATCH_G_CL(G, cl, DSVE_LAUNCH_STEP)
+#undef DSVE_LAUNCH_STEP
+    return hipGetLastError();
 }
 
 hipError_t launch_step(const StepArgs &a, int precision, int G, int cl, int tile, int grid,
                        hipStream_t stream)
 {
     if (tile < 64 || tile > kMaxTile || (tile & 63) || grid < 1) return hipErrorInvalidValue;
+    if (a.segments) {
+        if ((int64_t)grid * (tile / 64) < a.n_segments) return hipErrorInvalidValue;
+        if (precision == PREC_FP64) return launch_step_prec<PREC_FP64>(a, G, cl, tile, grid, stream);
+        if (precision == PREC_MIXED) return launch_step_prec<PREC_MIXED>(a, G, cl, tile, grid, stream);
+        if (precision == PREC_DOT) return launch_step_prec<PREC_DOT>(a, G, cl, tile, grid, stream);
+        return hipErrorNotSupported;
+    }
     // workgroup b takes tiles [b lo + min(b, rem), ...), lo + 1 of them for b < rem, else lo
     StepArgs b = a;
     b.tiles_lo = (int32_t)(a.n_tiles / grid);
     b.tiles_rem = (int32_t)(a.n_tiles % grid);
-    return step_needs_wide_index(a.n_edges) ? launch_step_w<true>(b, precision, G, cl, tile, grid, stream)
-                                            : launch_step_w<false>(b, precision, G, cl, tile, grid, stream);
+    return step_needs_wide_index(a.n_edges) ? launch_packed_w<true>(b, precision, G, cl, tile, grid, stream)
+                                            : launch_packed_w<false>(b, precision, G, cl, tile, grid, stream);
 }
 
 template <int PREC>

@@ -1,0 +1,81 @@
+"""The step kernel's segments (one wave per run of cells of one channel, 63 cells per tile) on the
+MI355X: channel lengths at the edges of tiles and segments, every boundary condition, and the choice
+between it and the packed kernel of short channels; against the channel-resident kernel (bitwise),
+across launches (bitwise) and against the oracle.
+
+Tolerances: the FP64 and mixed bars of the parity tests, relative L1 1e-12 and 1e-5.
+"""
+import numpy as np
+import pytest
+
+from paper_1912_04791_amd import inputs
+
+from common import oracle_run, per_channel_rel_l1
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dsve():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1912_04791_amd import dsve as d
+    return d
+
+
+def channels(lengths, seed, steps):
+    """Channels of the given lengths, every kind of end among them: transmissive, periodic,
+    inflow-q, fixed depth, inflow-(q, h), moving Dirichlet."""
+    rng = np.random.default_rng(seed)
+    parts = [inputs.riemann_state(rng, n) if n > 1 else tuple(np.array([v]) for v in (1.2, 0.3, 0.1))
+             for n in lengths]
+    C = len(lengths)
+    kinds = [(inputs.BC_TRANSMISSIVE, inputs.BC_TRANSMISSIVE), (inputs.BC_PERIODIC, inputs.BC_PERIODIC),
+             (inputs.BC_INFLOW_Q, inputs.BC_FIXED_DEPTH), (inputs.BC_INFLOW_QH, inputs.BC_TRANSMISSIVE),
+             (inputs.BC_DIRICHLET, inputs.BC_DIRICHLET)]
+    bcl, bcr = zip(*[kinds[c % len(kinds)] for c in range(C)])
+    ends = np.array([[1.1, 0.25, 0.0, -1e-3]] * C)
+    return inputs._assemble("segments", parts, np.full(C, 0.04), rng.uniform(0.001, 0.05, C),
+                            rng.uniform(0.3, 0.45, C), bcl, bcr, steps, seed, q_in=np.full(C, 0.3),
+                            h_in=np.full(C, 1.3), h_out=np.full(C, 1.1), dir_left=ends, dir_right=ends)
+
+
+def run(dsve, wl, precision, launch=None, resident=1):
+    ctx = dsve.Context.from_workload(wl, precision=precision)
+    ctx.set_resident(resident)
+    if launch:
+        ctx.set_launch(*launch)
+    h, q, z, t = dsve.upload(wl)
+    ctx.adot_step(h, q, z, wl.steps, t)
+    ctx.sync()
+    out = tuple(x.cpu().numpy() for x in (h, q, z, t))
+    ctx.close()
+    return out
+
+
+@pytest.mark.parametrize("precision,tol", [("fp64", 1e-12), ("mixed", 1e-5)])
+@pytest.mark.parametrize("lengths", [
+    [n for k in (4, 5, 6, 8) for n in (63 * k - 1, 63 * k, 63 * k + 1)] * 5,     # edges of tiles
+    [1, 2, 62, 63, 64, 65, 125, 126, 127, 128] + [500, 504, 505, 511] * 15,      # short ones among them
+    [5, 9, 1, 62, 63, 64, 30, 128] * 12,                                         # mostly short: packed
+])
+def test_segment_edges(dsve, lengths, precision, tol):
+    wl = channels(lengths, seed=len(lengths), steps=14)
+    ref = run(dsve, wl, precision, resident=0)     # every channel has at most 511 cells
+    for launch in [(256, 0, 60), (64, 0, 0), (192, 1, 6), (64, 128, 6), (128, 1, 0)]:
+        for a, b in zip(run(dsve, wl, precision, launch), ref):
+            assert np.array_equal(a, b), launch
+    want = oracle_run(wl)
+    assert per_channel_rel_l1(ref, want, wl.offsets).max() <= tol
+    np.testing.assert_allclose(ref[3], want[3], rtol=1e-12 if precision == "fp64" else 1e-6)
+
+
+@pytest.mark.parametrize("n_cells", [63 * 17 - 1, 63 * 17, 63 * 17 + 1, 200_003])
+def test_one_channel_in_many_segments(dsve, n_cells):
+    wl = inputs.make_c2(n_cells=n_cells, steps=13, length=1000.0 * n_cells / (1 << 20))
+    outs = [run(dsve, wl, "fp64", launch) for launch in [(256, 0, 60), (64, 1, 0), (256, 7, 6), (192, 40, 0)]]
+    for o in outs[1:]:
+        for a, b in zip(o, outs[0]):
+            assert np.array_equal(a, b)
+    assert per_channel_rel_l1(outs[0], oracle_run(wl), wl.offsets).max() <= 1e-12
