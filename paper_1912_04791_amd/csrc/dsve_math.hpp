@@ -36,10 +36,13 @@
 // and, in FP64,
 //   D^- = sum_k w_k A^-(Psi_k) dW,  D^+ = S_A - D^-,
 // where A^- = (A - |A|)/2 (Eqs. asbA, ExAbsA) is the sum of c mu_m r_m l_m over the negative
-// eigenvalues.  The root labelled 3 below is always the middle one, so at most one root differs
-// in sign from it, and A^- takes one eigenpair o: A^- dW = c min(mu_o, 0) (l_o . dW) r_o when
-// mu_3 >= 0 (o the smallest root), A^- dW = A dW - c max(mu_o, 0) (l_o . dW) r_o when mu_3 < 0
-// (o the largest).  So |A| is never formed, and R^-1 dW is needed for one row only.
+// eigenvalues.  At most one root differs in sign from the middle one, so A^- or A^+ takes one
+// eigenpair o: |A| is never formed, and R^-1 dW is needed for one row only.  fluct64 takes that root,
+// alone, from its closed form in FP32 refined on the characteristic polynomial;
+// fluct64_general, for the edges where that does not hold to FP64, from the full eigenstructure
+// below: the root labelled 3 there is always the middle one, and A^- dW = c min(mu_o, 0) (l_o . dW)
+// r_o when mu_3 >= 0 (o the smallest root), A^- dW = A dW - c max(mu_o, 0) (l_o . dW) r_o when
+// mu_3 < 0 (o the largest).
 // The mixed form sums in FP32
 //   S_B = sum_k w_k |A(Psi_k)| dW  with |A| dW = sum_m c |mu_m| (l_m . dW) r_m,
 //   D^- = (S_A - S_B)/2,  D^+ = (S_A + S_B)/2,
@@ -75,6 +78,7 @@ constexpr double kSqrt3Half = 0.86602540378443864676372317075293618;
 constexpr double kAcosTol = 1e-12;            // tolerance on |arccos argument| - 1 before flagging
 constexpr double kInvGapScale = 2.59807621135331594029116951225880855;   // 3 sqrt3 / 2
 constexpr float kMixedFp64Band = 1e-2f;       // mixed form: 1 - |x| below this -> FP64 node
+constexpr float kSeedBand = 1e-2f;            // FP64 form: 1 - |x| below this -> fluct64_general
 
 // Unrolling of the quadrature-node loop (independent nodes interleave for ILP when unrolled;
 // a rolled loop needs fewer registers).
@@ -372,7 +376,7 @@ __device__ __forceinline__ void eig64(double h, double q, double g, const Closur
 // under weak transport) the cosine is cos_third_acos(x'); for x' < 0 it follows from the angle
 // at -x' (third_angle).
 template <int CL>
-__device__ __forceinline__ double speed64(double h, double q, double g, const Closure &K, unsigned &bad)
+__device__ __forceinline__ double speed64_general(double h, double q, double g, const Closure &K, unsigned &bad)
 {
     const ArgX<CL> a = arg_x<CL>(h, q, g, K);
     const double Fr = a.Fr, k1 = a.k1, r1 = a.r1, x = a.x;
@@ -430,13 +434,6 @@ __device__ __forceinline__ void node_accumulate64(const Eig64 &E, double w, doub
     SB[2] = fma(wcP, B2, SB[2]);
 }
 
-// Paths of an FP64 quadrature node through D^-: with every lane's mu_3 >= 0 and ms >= 0 (flow
-// towards +x below |Fr| of about 3 under weak transport), o = 2 and A^- dW takes the share
-// min(mu_2, 0) of that eigenpair; with every lane's mu_3 < 0 and ms < 0 (the mirror case), o = 2
-// and A^- dW = A dW less the share max(mu_2, 0); any other wave picks o per lane (o = 2 exactly
-// when the signs of mu_3 and ms agree).
-enum { NODE_PER_LANE = 0, NODE_UP = 1, NODE_DOWN = 2 };
-
 // Sums over the nodes of an edge: S1, S2 = w A dW (rows 1, 2) over the nodes with mu_3 >= 0 and
 // mu_3 < 0, Wt = sum of w over the latter (row 0 of A dW is dq at every node), SD = twice the
 // projection terms of D^-.  Then D^- = (dq Wt, S2) + SD/2 and D^+ = (dq, S1 + S2) - D^-; the
@@ -446,14 +443,12 @@ struct NodeSums {
     double Wt;
 };
 
-template <int PATH>
 __device__ __forceinline__ void node_minus64(const Eig64 &E, double w, double dh, double dq, double dz,
                                              NodeSums &N)
 {
-    // One body for the three paths, so that a lane's arithmetic does not depend on the path its
-    // wave takes: the uniform paths fix `up` and `two`, and their selects fold away.
-    const bool up = PATH == NODE_UP ? true : PATH == NODE_DOWN ? false : E.mu3 >= 0.0;
-    const bool two = PATH != NODE_PER_LANE ? true : up == (E.ms >= 0.0);
+    // o = 2 exactly when the signs of mu_3 and ms agree
+    const bool up = E.mu3 >= 0.0;
+    const bool two = up == (E.ms >= 0.0);
     const double Fr = E.Fr, c = E.c;
     const double dqn = dq * E.inv_c;
     const double base = fma(-Fr, Fr, 1.0);   // (c^2 - u^2) / c^2
@@ -502,34 +497,272 @@ __device__ __forceinline__ void node_sums_to_fluct(const NodeSums &N, double dq,
     }
 }
 
-// DOT fluctuations of one edge, FP64 throughout.  Each node takes the path its wave allows
-// (one branch per node for the whole wave).
+// The edge from the eigenstructure at every node (eig64), for the edges that fluct64 does not
+// refine from an FP32 estimate.
+template <int G, int CL>
+__device__ __forceinline__ void fluct64_general(double hL, double qL, double zL, double hR, double qR,
+                                                double zR, double g, const Closure &K, double Dm[3],
+                                                double Dp[3], unsigned &bad)
+{
+    const double dh = hR - hL, dq = qR - qL, dz = zR - zL;
+    NodeSums N = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}, 0.0};
+    unsigned long long xmax = 0ull;
+#pragma unroll 1
+    for (int k = 0; k < G; ++k) {
+        const double s = Gauss<G>::s[k];
+        Eig64 E;
+        eig64<CL>(fma(s, dh, hL), fma(s, dq, qL), g, K, E, xmax);
+        node_minus64(E, Gauss<G>::w[k], dh, dq, dz, N);
+    }
+    bad |= arg_flags(xmax, true);
+    node_sums_to_fluct(N, dq, Dm, Dp);
+}
+
+// (2/3) cos((pi - arccos(x)) / 3), x = 1 - w^2, in FP32 for x in [-0.99, 1]: minus the smallest root
+// of the trisection cubic, scaled.  As a function of w it is analytic over the whole range (x = 1
+// is a branch point in x), so one polynomial of degree 6, interpolated at the Chebyshev nodes of
+// [0, 1.411] in 60-digit arithmetic, meets it to 1.3e-7.
+__device__ __forceinline__ float outer_cos(float w)
+{
+    float p = -0.00017594896780792624f;
+    p = fmaf(p, w, 0.0012402319116517901f);
+    p = fmaf(p, w, -0.004403755068778992f);
+    p = fmaf(p, w, 0.012135269120335579f);
+    p = fmaf(p, w, -0.03693592548370361f);
+    p = fmaf(p, w, 0.2721569538116455f);
+    return fmaf(p, w, 0.33333346247673035f);
+}
+
+// FP32 cubic parameters at |Fr| (the halved k2 and c1 = Fr^2 - 1 - b, the linear coefficient of the
+// characteristic polynomial of mu); b is rounded from FP64 except for the Grass law, where it is
+// kqg Fr^2.
+template <int CL>
+__device__ __forceinline__ void cubic_paramsf(const Closure &K, float F, float b, float &k1, float &k2h,
+                                              float &c1)
+{
+    const float F2 = F * F;
+    if constexpr (CL == CL_GRASS) {
+        k1 = fmaf(F2, (float)K.K1, 3.0f);
+        k2h = F * fmaf(-F2, (float)K.K2h, 9.0f);
+        c1 = fmaf(F2, (float)(1.0 - K.kqg), -1.0f);
+    } else {
+        constexpr bool stress = CL == CL_MPM || CL == CL_VANRIJN;
+        k1 = fmaf(3.0f, b, F2 + 3.0f);
+        k2h = F * fmaf(stress ? -6.75f : -4.5f, b, 9.0f - F2);
+        c1 = F2 - (1.0f + b);
+    }
+}
+
+// FP64 state of a node for the refinement: u, g h, b and g h b of the closure.
+struct Node64 {
+    double u, gh, b, ghb;
+};
+template <int CL>
+__device__ __forceinline__ Node64 node_state64(double h, double q, double g, const Closure &K)
+{
+    Node64 n;
+    const double r = (double)__builtin_amdgcn_rcpf((float)h);   // 1/h: FP32 estimate, one Halley step
+    const double e = fma(-h, r, 1.0);
+    const double ih = fma(r, fma(e, e, e), r);
+    n.u = q * ih;
+    n.gh = g * h;
+    if constexpr (CL == CL_GRASS) {
+        const double u2 = n.u * n.u;
+        n.b = (K.lp0 * u2) * ih;
+        n.ghb = K.kqg * u2;
+    } else {
+        n.b = law_b<CL, double>(K, h, q, ih);
+        n.ghb = n.gh * n.b;
+    }
+    return n;
+}
+
+// g h as an FP32 bit pattern lies in [1e-20, 1e20]: the range where the FP32 estimates neither
+// overflow nor meet subnormals (negative, zero, NaN and infinite depths fail it too).
+__device__ __forceinline__ bool in_seed_range(float gh)
+{
+    return __float_as_uint(gh) - 0x1E3CE508u <= 0x60AD78ECu - 0x1E3CE508u;
+}
+
+// Sums over the nodes of an edge for fluct64: P = the share of the eigenvalue o in w A dW (rows 0-2),
+// S1, S2 = rows 1 and 2 of w A dW without the term w g h (dh + dz) of row 1.
+struct OuterSums {
+    double P0, P1, P2, S1, S2;
+};
+
+// One node into the sums of an edge; dir = +-1 is the direction of the flow.  False where the node is
+// too close to coalescing roots (or not finite) for the refinement.
+template <int CL>
+__device__ __forceinline__ bool node_outer(const Node64 &n, const Closure &K, float dir, double w, double dh,
+                                           double dq, double eta, OuterSums &N)
+{
+    constexpr double kappa = (CL == CL_MPM || CL == CL_VANRIJN) ? 7.0 / 6.0 : 1.0;
+    // root o in FP32, in units of c at |Fr| (there the smallest), and 1 / p'
+    const float ghf = (float)n.gh;
+    const float ic = __builtin_amdgcn_rsqf(ghf);
+    const float F = fabsf((float)n.u) * ic;
+    float k1, k2h, c1f;
+    cubic_paramsf<CL>(K, F, (float)n.b, k1, k2h, c1f);
+    const float r1 = __builtin_amdgcn_rsqf(k1);
+    const float x = k2h * (r1 * r1 * r1);
+    const float mu = fmaf(-(k1 * r1), outer_cos(__builtin_amdgcn_sqrtf(1.0f - x)), (2.0f / 3.0f) * F);
+    const float d = fmaf(mu, fmaf(3.0f, mu, -4.0f * F), c1f);
+    const double rd = (double)__builtin_amdgcn_rcpf(d * ghf);
+    double lam = (double)((dir * (ghf * ic)) * mu);
+    // two Newton steps on p
+    const double sb = n.gh + n.ghb;
+    const double c1 = fma(n.u, n.u, -sb);
+    const double c0 = kappa == 1.0 ? n.ghb * n.u : (kappa * n.ghb) * n.u;
+#pragma unroll
+    for (int it = 0; it < 2; ++it)
+        lam = fma(-fma(lam, fma(lam, fma(-2.0, n.u, lam), c1), c0), rd, lam);
+    const double l2 = fma(-2.0, n.u, lam);
+    const double e = fma(-fma(lam, fma(2.0, l2, lam), c1), rd, 1.0);
+    const double ip = fma(rd, fma(e, e, e), rd);   // 1 / p'(lambda_o)
+    // (l_o . dW) p' = g h (dh + dz) + lambda_o dq + (lambda_j lambda_k - u^2) dh
+    const double no = fma(n.gh, eta, fma(lam, dq, fma(lam, l2, -sb) * dh));
+    const double wn = w * (no * ip);
+    const double pb = wn * lam;
+    const double ku = kappa == 1.0 ? n.u : kappa * n.u;
+    N.P0 += pb;
+    N.P1 = fma(pb, lam, N.P1);
+    N.P2 = fma(wn * n.b, lam - ku, N.P2);
+    const double t = fma(-n.u, dh, dq);
+    N.S1 = fma(w * n.u, t + dq, N.S1);
+    N.S2 = fma(w * n.b, kappa == 1.0 ? t : fma(-ku, dh, dq), N.S2);
+    return fabsf(x) < 1.0f - kSeedBand;
+}
+
+// DOT fluctuations of one edge, FP64 throughout.
+//
+// At a node A has exactly one eigenvalue whose sign differs from that of the flow: the
+// characteristic polynomial
+//   p(lambda) = lambda^3 - 2u lambda^2 + c1 lambda + c0,  c1 = u^2 - g h (1 + b),  c0 = kappa g h b u
+// has p(0) of the sign of u and, for b >= 0, two roots on the other side of 0.  That eigenvalue, o,
+// alone gives the node's A^- dW (flow towards +x, where it is the smallest root) or A^+ dW (towards
+// -x, the largest), and the other of the two is A dW less it.  Nothing else of the eigenstructure is
+// needed:
+//   l_o . dW = [(g h - u^2 + lambda_j lambda_k) dh + lambda_o dq + g h dz] / p'(lambda_o),
+//   lambda_j lambda_k = c1 + lambda_o (lambda_o - 2u)   (Vieta),
+//   r_o = [1, lambda_o, b (lambda_o - kappa u) / lambda_o]   (third row of A r = lambda r),
+// so a node takes the root o from the closed form (Eq. lambda) in FP32 and two FP64 Newton steps on p
+// (FP32 derivative: each takes an error e to about e (1e-6 + e / gap)), its p' with the FP32
+// reciprocal refined, and no square root, arccos or second root in FP64.  The sum over the nodes of
+// w g h (dh + dz) is g (hL + hR)/2 (dh + dz).
+//
+// Flow in one direction along the path (q of one sign at both ends) is the common case; a wave with a
+// lane whose q changes sign sums the nodes of either direction apart (its other lanes get the same
+// bits).  Left to fluct64_general: edges with a node within kSeedBand of coalescing roots (the Newton
+// steps then start too far off, and the error bits need the FP64 argument), and states outside the
+// range of the FP32 estimate or not finite.
+//
+// Bound by VALU issue: an FP64 instruction holds the SIMD 4 cycles, an FP64 reciprocal or root 16, an
+// FP32 one 2.3 and an FP32 root 8.5 when several waves are there to issue (measured).  Against the
+// full FP64 eigenstructure at each node (three FP64 roots and about 110 FP64 instructions; here about
+// 45, 35 FP32 and four FP32 roots), same kernel around it: 513 -> 425 instructions per edge and step,
+// 65 536 channels of 512-4096 cells 2.47 -> 1.94 ms a step, one channel of 2^20 cells 22.3 -> 19.8 us;
+// 500 cells in one workgroup 2.8 -> 2.5 us a step.  The error against 80-bit values falls by about
+// half (median 1.6e-16 -> 7.5e-17 of the edge's fluctuations; the bed row, which no longer cancels, by
+// 4 to 400).
 template <int G, int CL>
 __device__ __forceinline__ void fluct64(double hL, double qL, double zL, double hR, double qR,
                                         double zR, double g, const Closure &K, double Dm[3],
                                         double Dp[3], unsigned &bad)
 {
-    const double dh = hR - hL, dq = qR - qL, dz = zR - zL;
-    NodeSums N = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}, 0.0};
-    unsigned long long xmax = 0ull;
-    DSVE_UNROLL(DSVE_NODE_UNROLL)
-    for (int k = 0; k < G; ++k) {
-        const double s = Gauss<G>::s[k];
-        Eig64 E;
-        eig64<CL>(fma(s, dh, hL), fma(s, dq, qL), g, K, E, xmax);
-        const double w = Gauss<G>::w[k];
-        const unsigned long long act = __builtin_amdgcn_read_exec();
-        const unsigned long long m3 = __builtin_amdgcn_ballot_w64(E.mu3 >= 0.0);
-        const unsigned long long ms = __builtin_amdgcn_ballot_w64(E.ms >= 0.0);
-        if ((m3 & ms) == act)
-            node_minus64<NODE_UP>(E, w, dh, dq, dz, N);
-        else if ((m3 | ms) == 0ull)
-            node_minus64<NODE_DOWN>(E, w, dh, dq, dz, N);
-        else
-            node_minus64<NODE_PER_LANE>(E, w, dh, dq, dz, N);
+    const double dh = hR - hL, dq = qR - qL, dz = zR - zL, eta = dh + dz;
+    const bool up = qL >= 0.0 && qR >= 0.0;
+    const bool one = up || (qL <= 0.0 && qR <= 0.0);
+    bool ok = in_seed_range((float)(g * hL)) && in_seed_range((float)(g * hR));
+    const double gh_eta = (g * fma(0.5, dh, hL)) * eta;
+    if (__builtin_amdgcn_ballot_w64(!one) == 0ull) {
+        const float dir = up ? 1.0f : -1.0f;
+        OuterSums N = {0.0, 0.0, 0.0, 0.0, 0.0};
+        DSVE_UNROLL(DSVE_NODE_UNROLL)
+        for (int k = 0; k < G; ++k) {
+            const double s = Gauss<G>::s[k];
+            const Node64 n = node_state64<CL>(fma(s, dh, hL), fma(s, dq, qL), g, K);
+            ok = node_outer<CL>(n, K, dir, Gauss<G>::w[k], dh, dq, eta, N) && ok;
+        }
+        const double Q0 = dq - N.P0, Q1 = (N.S1 + gh_eta) - N.P1, Q2 = N.S2 - N.P2;
+        Dm[0] = up ? N.P0 : Q0;
+        Dm[1] = up ? N.P1 : Q1;
+        Dm[2] = up ? N.P2 : Q2;
+        Dp[0] = up ? Q0 : N.P0;
+        Dp[1] = up ? Q1 : N.P1;
+        Dp[2] = up ? Q2 : N.P2;
+    } else {
+        OuterSums U = {0.0, 0.0, 0.0, 0.0, 0.0}, D = U;   // nodes with flow towards +x, towards -x
+        double wd = 0.0, gd = 0.0;       // sums of w and of w g h over the latter
+#pragma unroll 1
+        for (int k = 0; k < G; ++k) {
+            const double s = Gauss<G>::s[k], w = Gauss<G>::w[k];
+            const double q = fma(s, dq, qL);
+            const Node64 n = node_state64<CL>(fma(s, dh, hL), q, g, K);
+            const bool u = one ? up : q >= 0.0;
+            OuterSums N;
+            N.P0 = u ? U.P0 : D.P0;
+            N.P1 = u ? U.P1 : D.P1;
+            N.P2 = u ? U.P2 : D.P2;
+            N.S1 = u ? U.S1 : D.S1;
+            N.S2 = u ? U.S2 : D.S2;
+            ok = node_outer<CL>(n, K, u ? 1.0f : -1.0f, w, dh, dq, eta, N) && ok;
+            U.P0 = u ? N.P0 : U.P0;
+            U.P1 = u ? N.P1 : U.P1;
+            U.P2 = u ? N.P2 : U.P2;
+            U.S1 = u ? N.S1 : U.S1;
+            U.S2 = u ? N.S2 : U.S2;
+            D.P0 = u ? D.P0 : N.P0;
+            D.P1 = u ? D.P1 : N.P1;
+            D.P2 = u ? D.P2 : N.P2;
+            D.S1 = u ? D.S1 : N.S1;
+            D.S2 = u ? D.S2 : N.S2;
+            wd = u ? wd : wd + w;
+            gd = u ? gd : fma(w, n.gh, gd);
+        }
+        // one direction: P and A dW less P, as above; both: D^- = P of +x and A dW less P of -x
+        const double ed = one ? (up ? 0.0 : gh_eta) : gd * eta, eu = one ? (up ? gh_eta : 0.0) : gh_eta - ed;
+        const double Qd0 = one ? dq - D.P0 : fma(wd, dq, -D.P0);
+        const double Qd1 = (D.S1 + ed) - D.P1, Qd2 = D.S2 - D.P2;
+        const double Qu1 = (U.S1 + eu) - U.P1, Qu2 = U.S2 - U.P2;
+        const bool dn = one && !up;
+        Dm[0] = one ? (up ? U.P0 : Qd0) : U.P0 + Qd0;
+        Dp[0] = dn ? D.P0 : dq - Dm[0];
+        Dm[1] = one ? (up ? U.P1 : Qd1) : U.P1 + Qd1;
+        Dm[2] = one ? (up ? U.P2 : Qd2) : U.P2 + Qd2;
+        Dp[1] = one ? (up ? Qu1 : D.P1) : D.P1 + Qu1;
+        Dp[2] = one ? (up ? Qu2 : D.P2) : D.P2 + Qu2;
     }
-    bad |= arg_flags(xmax, true);
-    node_sums_to_fluct(N, dq, Dm, Dp);
+    if (!ok) fluct64_general<G, CL>(hL, qL, zL, hR, qR, zR, g, K, Dm, Dp, bad);
+}
+
+// The same speed refined from an FP32 estimate as a node's root is (fluct64): the largest root of p
+// at |u|, which no other root comes near (its gap to the next is at least about c), where the arccos
+// argument at |Fr| is not negative (|Fr| below about 3 under weak transport) and the state lies in
+// the range of the FP32 estimate; speed64_general otherwise.
+template <int CL>
+__device__ __forceinline__ double speed64(double h, double q, double g, const Closure &K, unsigned &bad)
+{
+    constexpr double kappa = (CL == CL_MPM || CL == CL_VANRIJN) ? 7.0 / 6.0 : 1.0;
+    const Node64 n = node_state64<CL>(h, q, g, K);
+    const float ghf = (float)n.gh;
+    const float ic = __builtin_amdgcn_rsqf(ghf);
+    const float F = fabsf((float)n.u) * ic;
+    float k1, k2h, c1f;
+    cubic_paramsf<CL>(K, F, (float)n.b, k1, k2h, c1f);
+    const float r1 = __builtin_amdgcn_rsqf(k1);
+    const float x = k2h * (r1 * r1 * r1);
+    if (!(x >= 0.0f && in_seed_range(ghf))) return speed64_general<CL>(h, q, g, K, bad);
+    const float mu = (2.0f / 3.0f) * fmaf(k1 * r1, cos_third_acos(x), F);
+    const float d = fmaf(mu, fmaf(3.0f, mu, -4.0f * F), c1f);
+    const double rd = (double)__builtin_amdgcn_rcpf(d * ghf);
+    const double au = fabs(n.u);
+    const double c1 = fma(au, au, -(n.gh + n.ghb));
+    const double c0 = kappa == 1.0 ? n.ghb * au : (kappa * n.ghb) * au;
+    double lam = (double)((ghf * ic) * mu);
+#pragma unroll
+    for (int it = 0; it < 2; ++it)
+        lam = fma(-fma(lam, fma(lam, fma(-2.0, au, lam), c1), c0), rd, lam);
+    return lam;
 }
 
 // ---------------------------------------------------------------------------
@@ -680,7 +913,7 @@ __device__ __forceinline__ double speed_mixed(double h, double q, double g, cons
     const float xa = Fr < 0.0f ? -x : x;
     if (xa >= 0.0f && xa < 1.0f - kMixedFp64Band)
         return (double)((gh * inv_c) * ((2.0f / 3.0f) * fmaf(k1 * r1, cos_third_acos(xa), fabsf(Fr))));
-    return speed64<CL>(h, q, g, K, bad);
+    return speed64_general<CL>(h, q, g, K, bad);
 }
 
 // Friction source of the momentum equation (Sec. 2): -g h s_f with
