@@ -217,7 +217,7 @@ dsve_status cfl_reduce(dsve_ctx *ctx, const double *h, const double *q, const do
  * cells from the boundary conditions, dt = cfl*dx/amax(W^n), DOT fluctuations
  * at every edge, cell update with the friction source, and the CFL speed of W^{n+1} --
  * one fused kernel per step, or one launch for the whole run when the run is
- * channel-resident (dsve_set_resident).  With graph_steps > 0 (dsve_set_launch) the steps
+ * channel-resident or runs in parts (dsve_set_resident).  With graph_steps > 0 (dsve_set_launch) the steps
  * are replayed from captured HIP graphs: n_steps / graph_steps replays of a graph of
  * graph_steps steps, then one replay of a graph of the remaining n_steps % graph_steps
  * steps; the graphs are captured at the first run that needs them and kept while the
@@ -228,8 +228,8 @@ dsve_status adot_step(dsve_ctx *ctx, double *h, double *q, double *z, int n_step
 
 /* As adot_step for a batched context: h, q, z hold all channels back to back
  * (offsets as given to dsve_batch_init); t_dev[n_channels] receives each
- * channel's clock.  All channels run in one persistent kernel per step, or in one
- * launch for the whole run when it is channel-resident. */
+ * channel's clock.  All channels run in one kernel per step, or in one launch for the
+ * whole run when it is channel-resident or runs in parts. */
 dsve_status adot_step_batched(dsve_ctx *ctx, double *h, double *q, double *z, int n_steps,
                               double *t_dev);
 
@@ -249,13 +249,13 @@ dsve_status adot_step_noalloc(dsve_ctx *ctx, double *h, double *q, double *z, in
 /* Capture ahead the HIP graphs a run of n_steps on these arrays will replay (see adot_step),
  * so that the run itself only replays them: graph capture and instantiation then fall
  * outside a timed or latency-critical region.  Enqueues no work; the arrays are not read.
- * Nothing to do for channel-resident runs or with graph_steps = 0. */
+ * Nothing to do for runs in one launch (channel-resident or in parts) or with graph_steps = 0. */
 dsve_status dsve_prepare_run(dsve_ctx *ctx, double *h, double *q, double *z, int n_steps,
                              double *t_dev);
 
 /* How the last run (adot_step, adot_step_batched) was launched: *graph_launches HIP graph
  * replays covering *graph_steps steps, and *direct_launches kernels launched one by one (step
- * kernels, or 1 for a channel-resident run).  Any pointer may be NULL. */
+ * kernels, or 1 for a run in one launch).  Any pointer may be NULL. */
 dsve_status dsve_get_last_run(const dsve_ctx *ctx, int *graph_launches, int *graph_steps,
                               int *direct_launches);
 
@@ -279,6 +279,9 @@ dsve_status dsve_clear_error(dsve_ctx *ctx);
  *                  even contiguous run of the tiles
  *   graph_steps    steps per captured HIP graph: a multiple of 6 in [6, 600],
  *                  or 0 to launch every step directly
+ * Unless many channels are very short, each wave of a workgroup takes a run of cells of one channel
+ * on its own, and blocks_per_cu sets how many waves share them (0 = automatic).  Setting a launch
+ * turns off runs in parts (dsve_set_resident) for channels of more than 511 cells.
  * The results do not depend on these (each edge and cell is computed the same
  * way whatever tile it falls in). */
 dsve_status dsve_set_launch(dsve_ctx *ctx, int tile, int blocks_per_cu, int graph_steps);
@@ -305,7 +308,12 @@ dsve_status dsve_get_cfl_split(const dsve_ctx *ctx, int *split);
  * per-step kernels.  The launch configuration and CFL sub-slots do not apply to resident
  * runs.  dsve_get_resident reports whether the next run will be resident.  Resident runs
  * leave lanes idle in channels much shorter than their workgroup; dsve_autotune compares
- * them with the per-step kernels. */
+ * them with the per-step kernels.
+ * With few channels (at most 256 short ones, or about 7000 cells in all) the run is spread over more
+ * of the chip: each channel is held by one or several workgroups that exchange their CFL maxima and
+ * end cells, also channels of more than 511 cells unless a launch was set; same results, one launch.
+ * Those workgroups wait for one another; should they not come to run together within 20 s on a device
+ * held by others, the run fails with DSVE_E_HIP at dsve_sync. */
 dsve_status dsve_set_resident(dsve_ctx *ctx, int mode);
 dsve_status dsve_get_resident(const dsve_ctx *ctx, int *active);
 

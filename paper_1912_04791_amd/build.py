@@ -11,6 +11,7 @@ import os
 import shutil
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -30,6 +31,7 @@ HOST_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-Wall"]
 
 SOURCES = {
     "dsve_kernels.hip": DEVICE_FLAGS,
+    "dsve_resident.hip": DEVICE_FLAGS,
     "dsve_api.cpp": HOST_FLAGS,
 }
 
@@ -46,8 +48,9 @@ def build(verbose: bool = False, extra_device_flags=None, out: str | None = None
     cc = hipcc()
     lib = out or LIB
     os.makedirs(BUILD, exist_ok=True)
-    objs = []
-    for src, flags in SOURCES.items():
+
+    def compile_one(item):
+        src, flags = item
         obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
         fl = list(flags)
         if src.endswith(".hip") and extra_device_flags:
@@ -56,7 +59,10 @@ def build(verbose: bool = False, extra_device_flags=None, out: str | None = None
         if verbose:
             print(" ".join(cmd), flush=True)
         subprocess.check_call(cmd)
-        objs.append(obj)
+        return obj
+
+    with ThreadPoolExecutor(len(SOURCES)) as pool:   # one compiler process per source
+        objs = list(pool.map(compile_one, SOURCES.items()))
     tmp = f"{lib}.{os.getpid()}.tmp"
     cmd = [cc, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs]
     if verbose:

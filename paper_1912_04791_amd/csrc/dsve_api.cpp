@@ -50,13 +50,18 @@ struct dsve_ctx {
 
     double *pp_h = nullptr, *pp_q = nullptr, *pp_z = nullptr;   // ping-pong copy
     double *pp_t = nullptr;                                      // ping-pong clocks [C]
-    unsigned long long *d_amax = nullptr;                        // [3][S][Cs]
+    unsigned long long *d_amax = nullptr;                        // [3][S][Cs], then the mailboxes of the parts
     int64_t amax_cs = 0;                                         // Cs (sub-slot stride)
     int64_t amax_slot = 0;                                       // kAmaxSplitMax * Cs (one slot)
     int cfl_split = 0;                                           // CFL sub-slots; 0 = automatic
     bool resident_ok = false;    // every channel has at most kResidentCells cells
     int resident_threads = 256;  // workgroup size of resident runs: 256, or 512 past 255 cells
     int resident_mode = 0;       // 0: channel-resident runs when resident_ok; 1: never
+    // few channels: the run in one launch of k_parts (see build_parts)
+    Part *d_parts = nullptr;
+    int64_t n_parts = 0;         // 0: the context does not run that way
+    int parts_grid = 0;
+    bool launch_set = false;     // a launch configuration was asked for: per-step kernels where not resident
     unsigned int *d_flags = nullptr;                             // [4]
 
     int tile = 256, blocks_per_cu = 0, graph_steps = 60;
@@ -260,6 +265,87 @@ static dsve_status build_table(dsve_ctx *c, int tile, int blocks_per_cu)
     return c->packed ? build_tile_table(c, tile) : build_segments(c, tile, blocks_per_cu);
 }
 
+// Parts of a context with few channels (k_parts): one per channel that a workgroup holds, up to one per
+// compute unit (with more channels the workgroups fill the chip, and k_resident, with fewer waves per
+// channel, does more of them at once); with longer channels among them, cut into parts that wait for
+// one another, at most kMaxParts in all, eight on an XCD.  An XCD has a compute unit for each of 32, so
+// launches from four hardware queues, of which each may be partly on the chip, always all get there.
+// Past kMaxParts (about 7000 cells) the per-step kernels take over, on a stream restricted to some of
+// the compute units too.  Channels of 127 to 255 cells stay with one workgroup of k_resident, as fast
+// as three parts (250 cells: 1.79 against 1.89 us a step), except with the numerical eigensolver.
+static dsve_status build_parts(dsve_ctx *c)
+{
+    int64_t longest = 0;
+    for (int64_t k = 0; k < c->n_channels; ++k) longest = std::max<int64_t>(longest, c->h_off[k + 1] - c->h_off[k]);
+    const int64_t room = part_cells(c->G), own = room - 2 * kPartHalo;
+    const bool cut = longest > room;
+    int64_t parts = 0;
+    for (int64_t k = 0; k < c->n_channels; ++k) {
+        const int64_t N = c->h_off[k + 1] - c->h_off[k];
+        parts += N <= room ? 1 : (N + own - 1) / own;
+    }
+    if (parts > (cut ? kMaxParts : (int64_t)c->cus)) return DSVE_OK;
+    if (cut && longest <= kResidentSmall && c->precision != PREC_DOT) return DSVE_OK;
+    if (cut) {
+        uint32_t mask[32] = {0};
+        int on = 0;
+        if (hipExtStreamGetCUMask(c->stream, 32, mask) != hipSuccess) return DSVE_OK;
+        for (uint32_t m : mask) on += __builtin_popcount(m);
+        if (on < c->cus) return DSVE_OK;
+    }
+    // Block b runs on XCD b mod 8.  The parts of a channel go to one XCD, where they exchange words
+    // faster, if it then holds no more than an eighth of kMaxParts, else round all of them.
+    std::vector<Part> lists[8];
+    int64_t id = 0;
+    for (int64_t k = 0; k < c->n_channels; ++k) {
+        const int64_t N = c->h_off[k + 1] - c->h_off[k];
+        const int64_t parts = N <= room ? 1 : (N + own - 1) / own;
+        const bool ring = c->h_ch[k].bcl == BC_PERIODIC;
+        auto shortest = [&] {
+            int x = 0;
+            for (int j = 1; j < 8; ++j)
+                if (lists[j].size() < lists[x].size()) x = j;
+            return x;
+        };
+        int x = shortest();
+        const bool together = (int64_t)lists[x].size() + parts <= kMaxParts / 8;
+        for (int64_t p = 0; p < parts; ++p) {
+            const int64_t a = N * p / parts, b = N * (p + 1) / parts;
+            const bool lcut = parts > 1 && (p > 0 || ring), rcut = parts > 1 && (p + 1 < parts || ring);
+            Part P{};
+            P.cell0 = c->h_off[k];
+            P.ncell = N;
+            P.own0 = lcut ? kPartHalo : 0;
+            P.own1 = P.own0 + (int32_t)(b - a);
+            P.a = a - P.own0;
+            P.n = P.own1 + (rcut ? kPartHalo : 0);
+            P.chan = (int32_t)k;
+            P.index = (int32_t)p;
+            P.n_parts = (int32_t)parts;
+            P.id = (int32_t)(id + p);
+            P.cut = (lcut ? 1 : 0) | (rcut ? 2 : 0);
+            lists[together ? x : shortest()].push_back(P);
+        }
+        id += parts;
+    }
+    size_t rows = 0;
+    for (const auto &l : lists) rows = std::max(rows, l.size());
+    std::vector<Part> table(8 * rows);   // blocks without work end at once
+    for (size_t r = 0; r < rows; ++r)
+        for (size_t j = 0; j < 8; ++j)
+            if (r < lists[j].size()) table[8 * r + j] = lists[j][r];
+    HIP_TRY(c, hipMalloc(&c->d_parts, sizeof(Part) * table.size()));
+    HIP_TRY(c, hipMemcpy(c->d_parts, table.data(), sizeof(Part) * table.size(), hipMemcpyHostToDevice));
+    c->n_parts = id;
+    c->parts_grid = (int)table.size();
+    return DSVE_OK;
+}
+
+static bool runs_in_parts(const dsve_ctx *c)
+{
+    return c->n_parts > 0 && c->resident_mode == 0 && (c->resident_ok || !c->launch_set);
+}
+
 static dsve_status setup(dsve_ctx *c, void *stream)
 {
     // the power law with an integer exponent beta - 1 in every channel runs the product form
@@ -296,7 +382,9 @@ static dsve_status setup(dsve_ctx *c, void *stream)
         return fail(c, DSVE_E_HIP, "kernels built with another CFL sub-slot count than the host code");
     c->amax_cs = amax_stride(C);
     c->amax_slot = (int64_t)kAmaxSplitMax * c->amax_cs;
-    HIP_TRY(c, hipMalloc(&c->d_amax, sizeof(unsigned long long) * 3 * c->amax_slot));
+    dsve_status st = build_parts(c);
+    if (st != DSVE_OK) return st;
+    HIP_TRY(c, hipMalloc(&c->d_amax, sizeof(unsigned long long) * (3 * c->amax_slot + part_box_words(c->n_parts))));
     HIP_TRY(c, hipMalloc(&c->d_flags, sizeof(unsigned int) * 4));
     HIP_TRY(c, launch_fill_u64(c->d_amax, 3 * c->amax_slot, 0ull, c->stream));
     HIP_TRY(c, launch_fill_u32(c->d_flags, 4, 0u, c->stream));
@@ -308,7 +396,7 @@ static dsve_status setup(dsve_ctx *c, void *stream)
     // tiles hold several channels, runs instead
     c->n_tiles = segment_tiles(c);
     c->packed = c->n_tiles * 64 > c->n_edges + c->n_edges / 4;
-    dsve_status st = build_table(c, c->tile, c->blocks_per_cu);
+    st = build_table(c, c->tile, c->blocks_per_cu);
     if (st != DSVE_OK) return st;
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     return DSVE_OK;
@@ -331,6 +419,7 @@ static void release(dsve_ctx *c)
     (void)hipFree(c->d_flags);
     (void)hipFree(c->d_tile_chan);
     (void)hipFree(c->d_segments);
+    (void)hipFree(c->d_parts);
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
     delete c;
 }
@@ -722,12 +811,33 @@ static dsve_status ensure_graphs(dsve_ctx *ctx, double *h, double *q, double *z,
     return DSVE_OK;
 }
 
+// The whole run in one launch of k_parts; the final CFL maxima land in sub-slot 0 of slot 0 for the
+// check in dsve_sync.
+static dsve_status run_parts(dsve_ctx *ctx, double *h, double *q, double *z, int n_steps, double *t)
+{
+    HIP_TRY(ctx, launch_fill_u64(ctx->d_amax, 3 * ctx->amax_slot + part_box_words(ctx->n_parts), 0ull, ctx->stream));
+    PartArgs a{};
+    a.h = h; a.q = q; a.z = z; a.t = t;
+    a.ch = ctx->d_ch; a.parts = ctx->d_parts; a.box = ctx->d_amax + 3 * ctx->amax_slot; a.amax = ctx->d_amax;
+    a.flags = ctx->d_flags;
+    a.n_parts = (int32_t)ctx->n_parts;
+    a.n_steps = n_steps;
+    a.g = ctx->g;
+    HIP_TRY(ctx, launch_parts(a, ctx->precision, ctx->G, ctx->cl, ctx->parts_grid, ctx->stream));
+    ctx->last_amax_slot = 0;
+    ctx->last_graph_launches = 0;
+    ctx->last_graph_steps = 0;
+    ctx->last_direct = 1;
+    return DSVE_OK;
+}
+
 static dsve_status run_steps(dsve_ctx *ctx, double *h, double *q, double *z, int n_steps, double *t)
 {
     if (ctx->sticky != DSVE_OK) return ctx->sticky;
     if (!h || !q || !z || !t) return fail(ctx, DSVE_E_ARG, "null pointer");
     if (n_steps < 0) return fail(ctx, DSVE_E_ARG, "n_steps must be >= 0");
     if (n_steps == 0) return DSVE_OK;
+    if (runs_in_parts(ctx)) return run_parts(ctx, h, q, z, n_steps, t);
     if (ctx->resident_ok && ctx->resident_mode == 0) {
         // short channels: the whole run in one launch, one workgroup per channel at a time;
         // the final CFL maximum lands in sub-slot 0 of slot 0 for the check in dsve_sync
@@ -797,7 +907,7 @@ dsve_status dsve_prepare_run(dsve_ctx *ctx, double *h, double *q, double *z, int
     if (ctx->sticky != DSVE_OK) return ctx->sticky;
     if (!h || !q || !z || !t_dev) return fail(ctx, DSVE_E_ARG, "null pointer");
     if (n_steps < 0) return fail(ctx, DSVE_E_ARG, "n_steps must be >= 0");
-    if (n_steps == 0 || (ctx->resident_ok && ctx->resident_mode == 0)) return DSVE_OK;
+    if (n_steps == 0 || runs_in_parts(ctx) || (ctx->resident_ok && ctx->resident_mode == 0)) return DSVE_OK;
     dsve_status st = build_table(ctx, ctx->tile, ctx->blocks_per_cu);
     if (st != DSVE_OK || ctx->graph_steps == 0) return st;
     return ensure_graphs(ctx, h, q, z, t_dev, n_steps);
@@ -841,6 +951,7 @@ dsve_status adot_step_noalloc(dsve_ctx *ctx, double *h, double *q, double *z, in
                         " channels); use adot_step or adot_step_batched");
     if (!ctx->scratch) return fail(ctx, DSVE_E_HIP, "adot_step_noalloc: no static scratch on this device");
     if (n_steps == 0) return DSVE_OK;
+    if (runs_in_parts(ctx)) return run_parts(ctx, h, q, z, n_steps, t_dev);
     const RunBufs b = scratch_bufs(ctx);
     if (ctx->resident_ok && ctx->resident_mode == 0) {
         HIP_TRY(ctx, launch_fill_u64(b.amax, 3 * ctx->amax_slot, 0ull, ctx->stream));
@@ -905,6 +1016,8 @@ dsve_status dsve_sync(dsve_ctx *ctx)
     if (flags[0] & kFlagCoalesce)
         return fail(ctx, DSVE_E_NONHYPERBOLIC,
                     "coalescing eigenvalues at a quadrature node (arccos argument +-1: R^-1 undefined)");
+    if (flags[0] & kFlagTimeout)
+        return fail(ctx, DSVE_E_HIP, "the workgroups of a channel-resident run were not on the device together");
     if (ctx->last_amax_slot >= 0) {
         const int64_t C = ctx->n_channels;
         std::vector<unsigned long long> am(ctx->amax_slot);
@@ -942,6 +1055,7 @@ dsve_status dsve_set_launch(dsve_ctx *ctx, int tile, int blocks_per_cu, int grap
     ctx->tile = tile;
     ctx->blocks_per_cu = blocks_per_cu;
     ctx->graph_steps = graph_steps;
+    ctx->launch_set = true;
     return DSVE_OK;
 }
 
@@ -1010,7 +1124,7 @@ static std::string tune_key(const dsve_ctx *ctx)
 }
 
 static bool cache_lookup(const char *path, const std::string &key, int &tile, int &bpc, int &split,
-                         int &resident)
+                         int &resident, int &parts)
 {
     if (!path) return false;
     std::ifstream f(path);
@@ -1018,7 +1132,7 @@ static bool cache_lookup(const char *path, const std::string &key, int &tile, in
     std::string line;
     while (std::getline(f, line)) {
         // one entry per line: {"key": "<key>", "tile": T, "blocks_per_cu": B, "cfl_split": S,
-        // "resident_mode": M, ...} (older entries without S or M read as 0)
+        // "resident_mode": M, "parts": P, ...} (older entries without S, M or P read as 0)
         const std::string pat = "\"key\": \"" + key + "\"";
         if (line.find(pat) == std::string::npos) continue;
         const size_t pt = line.find("\"tile\": ");
@@ -1030,13 +1144,15 @@ static bool cache_lookup(const char *path, const std::string &key, int &tile, in
         split = ps == std::string::npos ? 0 : std::atoi(line.c_str() + ps + 13);
         const size_t pr = line.find("\"resident_mode\": ");
         resident = pr == std::string::npos ? 0 : std::atoi(line.c_str() + pr + 17);
+        const size_t pp = line.find("\"parts\": ");
+        parts = pp == std::string::npos ? 0 : std::atoi(line.c_str() + pp + 9);
         return true;
     }
     return false;
 }
 
 static void cache_store(const char *path, const std::string &key, int tile, int bpc, int split,
-                        int resident, double ms)
+                        int resident, int parts, double ms)
 {
     if (!path) return;
     std::vector<std::string> keep;
@@ -1050,7 +1166,7 @@ static void cache_store(const char *path, const std::string &key, int tile, int 
     std::ofstream o(path, std::ios::trunc);
     for (auto &l : keep) o << l << "\n";
     o << "{\"key\": \"" << key << "\", \"tile\": " << tile << ", \"blocks_per_cu\": " << bpc
-      << ", \"cfl_split\": " << split << ", \"resident_mode\": " << resident
+      << ", \"cfl_split\": " << split << ", \"resident_mode\": " << resident << ", \"parts\": " << parts
       << ", \"ms_per_step\": " << ms << "}\n";
 }
 
@@ -1065,9 +1181,12 @@ extern "C" dsve_status dsve_autotune(dsve_ctx *ctx, const double *h, const doubl
     // left them on
     const bool try_resident = ctx->resident_ok && ctx->resident_mode == 0;
     const std::string key = tune_key(ctx) + (try_resident ? "|res" : "");
-    int tile = 0, bpc = 0, split = 0, resident = ctx->resident_mode;
-    if (cache_lookup(cache_path, key, tile, bpc, split, resident)) {
+    // longer channels that can run in parts (k_parts) are timed that way too
+    const bool try_parts = ctx->n_parts > 0 && !ctx->resident_ok && ctx->resident_mode == 0;
+    int tile = 0, bpc = 0, split = 0, resident = ctx->resident_mode, parts = 0;
+    if (cache_lookup(cache_path, key, tile, bpc, split, resident, parts)) {
         dsve_status st = dsve_set_launch(ctx, tile, bpc, ctx->graph_steps);
+        ctx->launch_set = parts == 0;
         if (st == DSVE_OK) st = dsve_set_cfl_split(ctx, split);
         return st != DSVE_OK ? st : dsve_set_resident(ctx, resident);
     }
@@ -1115,12 +1234,14 @@ extern "C" dsve_status dsve_autotune(dsve_ctx *ctx, const double *h, const doubl
     const int save_graph = ctx->graph_steps;
     const int save_split = ctx->cfl_split;
     const int save_mode = ctx->resident_mode;
+    const bool save_set = ctx->launch_set;
     const int tg = save_graph > 0 ? std::min(save_graph, 12) : 0;
     const int warm = tg > 0 ? tg : 2;
     const int timed = tg > 0 ? std::max(tg, (trial_steps + tg - 1) / tg * tg) : trial_steps;
     dsve_status status = DSVE_OK;
-    auto trial = [&](int ti, int bi, int sp, float &ms) -> dsve_status {
+    auto trial = [&](int ti, int bi, int sp, float &ms, bool in_parts = false) -> dsve_status {
         dsve_status s = dsve_set_launch(ctx, ti, bi, tg);
+        ctx->launch_set = !in_parts;
         if (s == DSVE_OK) s = dsve_set_cfl_split(ctx, sp);
         if (s != DSVE_OK) return s;
         (void)hipMemcpyAsync(sh, h, bytes, hipMemcpyDeviceToDevice, ctx->stream);
@@ -1141,11 +1262,11 @@ extern "C" dsve_status dsve_autotune(dsve_ctx *ctx, const double *h, const doubl
     struct Cand { float ms; int tile, bpc, split; };
     std::vector<Cand> cands;
     float resident_ms = 1e30f;
-    if (try_resident) {   // one launch for all the trial steps
+    if (try_resident || try_parts) {   // one launch for all the trial steps
         float ms = 0.f;
-        status = trial(ctx->tile, ctx->blocks_per_cu, ctx->cfl_split, ms);
+        status = trial(ctx->tile, ctx->blocks_per_cu, ctx->cfl_split, ms, try_parts);
         if (status == DSVE_OK) resident_ms = ms;
-        ctx->resident_mode = 1;   // the per-step candidates below
+        if (try_resident) ctx->resident_mode = 1;   // the per-step candidates below
     }
     for (int ti : tiles) {
         if (status != DSVE_OK) break;
@@ -1182,6 +1303,7 @@ extern "C" dsve_status dsve_autotune(dsve_ctx *ctx, const double *h, const doubl
         ctx->graph_steps = save_graph;
         ctx->cfl_split = save_split;
         ctx->resident_mode = save_mode;
+        ctx->launch_set = save_set;
         free_graph(ctx);
         return status;
     }
@@ -1191,9 +1313,11 @@ extern "C" dsve_status dsve_autotune(dsve_ctx *ctx, const double *h, const doubl
     const int mode = (try_resident && resident_ms <= best.ms) ? 0 : (try_resident ? 1 : ctx->resident_mode);
     if (try_resident) ctx->resident_mode = mode;
     dsve_status st = dsve_set_launch(ctx, best.tile, best.bpc, save_graph);
+    const bool in_parts = try_parts && resident_ms <= best.ms;
+    ctx->launch_set = !in_parts;
     if (st == DSVE_OK) st = dsve_set_cfl_split(ctx, best.split);
     if (st != DSVE_OK) return st;
-    cache_store(cache_path, key, best.tile, best.bpc, best.split, ctx->resident_mode,
+    cache_store(cache_path, key, best.tile, best.bpc, best.split, ctx->resident_mode, in_parts ? 1 : 0,
                 std::min(best.ms, resident_ms) / timed);
     return DSVE_OK;
 }

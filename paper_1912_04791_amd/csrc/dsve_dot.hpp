@@ -266,6 +266,52 @@ __device__ __forceinline__ double speed_dot(double h, double q, double g, const 
     return fmax(fmax(fabs(A[0][0]), fabs(A[1][1])), fabs(A[2][2]));
 }
 
+// One node of the numerical route: A dW and |A| dW (|A| = R |Lambda| R^-1, Eq. asbA) at a state.
+struct TermsDot {
+    double a[3], aa[3];
+};
+template <int CL>
+__device__ __forceinline__ TermsDot node_dot(double h, double q, double g, const Closure &K, const double dW[3],
+                                             unsigned &bad)
+{
+    double A[3][3], lam[3], R[3][3], Ri[3][3];
+    flux_matrix<CL>(h, q, g, K, A);
+    bad |= eig3_numeric(A, lam, R) ? 0u : kFlagComplex;
+    inverse3_lu(R, Ri);
+    TermsDot T;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        double ad = 0.0, aad = 0.0;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            double absA = 0.0;
+#pragma unroll
+            for (int m = 0; m < 3; ++m) absA = fma(R[i][m] * fabs(lam[m]), Ri[m][j], absA);
+            ad = fma(A[i][j], dW[j], ad);
+            aad = fma(absA, dW[j], aad);
+        }
+        T.a[i] = ad;
+        T.aa[i] = aad;
+    }
+    return T;
+}
+__device__ __forceinline__ void add_terms(double SA[3], double SB[3], const TermsDot &T, double w)
+{
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        SA[i] = fma(w, T.a[i], SA[i]);
+        SB[i] = fma(w, T.aa[i], SB[i]);
+    }
+}
+__device__ __forceinline__ void sums_to_fluct_dot(const double SA[3], const double SB[3], double Dm[3], double Dp[3])
+{
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+        Dm[r] = 0.5 * (SA[r] - SB[r]);
+        Dp[r] = 0.5 * (SA[r] + SB[r]);
+    }
+}
+
 // DOT fluctuations of one edge with the numerical eigen-decomposition at every node.
 template <int G, int CL>
 __device__ __forceinline__ void fluct_dot(double hL, double qL, double zL, double hR, double qR,
@@ -275,32 +321,10 @@ __device__ __forceinline__ void fluct_dot(double hL, double qL, double zL, doubl
     const double dW[3] = {hR - hL, qR - qL, zR - zL};
     double SA[3] = {0.0, 0.0, 0.0}, SB[3] = {0.0, 0.0, 0.0};
     for (int k = 0; k < G; ++k) {
-        const double s = Gauss<G>::s[k], w = Gauss<G>::w[k];
-        double A[3][3], lam[3], R[3][3], Ri[3][3];
-        flux_matrix<CL>(fma(s, dW[0], hL), fma(s, dW[1], qL), g, K, A);
-        bad |= eig3_numeric(A, lam, R) ? 0u : kFlagComplex;
-        inverse3_lu(R, Ri);
-        // |A| = R |Lambda| R^-1 (Eq. asbA), then the node's contributions to sum_k w_k (A, |A|) dW
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            double ad = 0.0, aad = 0.0;
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                double absA = 0.0;
-#pragma unroll
-                for (int m = 0; m < 3; ++m) absA = fma(R[i][m] * fabs(lam[m]), Ri[m][j], absA);
-                ad = fma(A[i][j], dW[j], ad);
-                aad = fma(absA, dW[j], aad);
-            }
-            SA[i] = fma(w, ad, SA[i]);
-            SB[i] = fma(w, aad, SB[i]);
-        }
+        const double s = Gauss<G>::s[k];
+        add_terms(SA, SB, node_dot<CL>(fma(s, dW[0], hL), fma(s, dW[1], qL), g, K, dW, bad), Gauss<G>::w[k]);
     }
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-        Dm[r] = 0.5 * (SA[r] - SB[r]);
-        Dp[r] = 0.5 * (SA[r] + SB[r]);
-    }
+    sums_to_fluct_dot(SA, SB, Dm, Dp);
 }
 
 }  // namespace dsve

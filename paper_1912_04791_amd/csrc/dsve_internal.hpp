@@ -43,6 +43,7 @@ enum { CL_GRASS = LAW_GRASS, CL_GRASS_THR = LAW_GRASS_THR, CL_POWER = LAW_POWER,
 constexpr unsigned kFlagComplex = 1u;    // complex eigenvalues: arccos argument past 1 + tol, or k1 <= 0
 constexpr unsigned kFlagCoalesce = 2u;   // a quadrature node whose arccos argument is +-1 to working
                                          // precision: two eigenvalues equal, R^-1 does not exist
+constexpr unsigned kFlagTimeout = 8u;    // a part of a channel waited in vain for another (k_parts)
 constexpr unsigned kFlagNonfinite = 4u;  // a non-finite arccos argument (an overflowed or NaN state)
 
 constexpr int kMaxGauss = 5;
@@ -198,6 +199,46 @@ struct ResidentArgs {
     double g;
 };
 
+// Runs of few channels (k_parts): a channel is held by one workgroup, or by several, its parts, that
+// exchange CFL maxima every step and kPartHalo cells on either side every kPartHalo steps through
+// global memory.
+constexpr int kPartHalo = 8;
+constexpr int64_t kMaxParts = 64;   // parts of a context with channels of several parts, at most
+struct Part {
+    int64_t cell0;      // first cell of the channel in the concatenated state
+    int64_t ncell;      // cells of the channel
+    int64_t a;          // channel cell of local cell 0 (negative or past the end: round a periodic channel)
+    int32_t n;          // local cells, halos included (0: no work)
+    int32_t own0, own1; // local range of the part's own cells
+    int32_t chan;
+    int32_t index;      // part of the channel, of n_parts
+    int32_t n_parts;
+    int32_t id;         // number of the part over all channels (parts of a channel are consecutive)
+    int32_t cut;        // 1: another part's cells lie left of it, 2: right of it
+};
+// Mailboxes of a context with P parts, in 64-bit words {tag, 32 bits of data}: [2][P][kMaxWords] CFL
+// maxima, [2][P][2][kHaloWords] cells next to the left and the right cut.
+constexpr int kPartMaxWords = 2 * 8;                  // two words per wave that takes CFL speeds
+constexpr int kPartHaloWords = kPartHalo * 3 * 2;
+inline int64_t part_box_words(int64_t parts) { return 2 * parts * (kPartMaxWords + 2 * kPartHaloWords); }
+
+struct PartArgs {
+    double *h, *q, *z;           // state, updated in place
+    double *t;                   // [C] clocks
+    const ChanInfo *ch;
+    const Part *parts;           // [grid]
+    unsigned long long *box;     // mailboxes, zero at the start of the run
+    unsigned long long *amax;    // [C] CFL maximum of the final state (bit patterns), zero at the start
+    unsigned int *flags;
+    int32_t n_parts;             // P
+    int32_t n_steps;
+    double g;
+};
+constexpr int kPartThreads = 512;   // per workgroup
+// Waves per role (G nodes, and the rest of the step) and cells held by a workgroup.
+constexpr int part_waves(int G) { return kPartThreads / 64 / (G + 1); }
+constexpr int part_cells(int G) { return 63 * part_waves(G); }
+
 struct CflArgs {
     const double *h, *q, *z;
     const ChanInfo *ch;
@@ -243,6 +284,8 @@ hipError_t launch_fill_u32(unsigned int *p, int64_t n, unsigned int v, hipStream
 // workgroups of `threads` (256 or 512) threads, more than the longest channel has cells.
 hipError_t launch_resident(const ResidentArgs &a, int precision, int G, int cl, int threads, int grid,
                            hipStream_t stream);
+// All n_steps of a run of the parts in one launch.
+hipError_t launch_parts(const PartArgs &a, int precision, int G, int cl, int grid, hipStream_t stream);
 // kAmaxSplitMax as compiled into the kernels (the host code checks it against its own).
 int amax_split_of_kernels();
 hipError_t launch_copy_u64(unsigned long long *dst, const unsigned long long *src, int64_t n,

@@ -22,133 +22,11 @@
 
 #include <mutex>
 
-#include "dsve_dot.hpp"
-#include "dsve_internal.hpp"
-#include "dsve_math.hpp"
+#include "dsve_device.hpp"
 
 namespace dsve {
 
-// Maximum over the 64 lanes of a wave of 32-bit values, read back to every lane.  DPP lane
-// moves (swaps within quads, half-row and row mirrors: each lane then holds its row of 16; then
-// the broadcasts of lane 15 of each row into the next row and of lane 31 into the upper half)
-// leave the maximum in lane 63.  A lane whose DPP source lies outside the wave reads 0, the
-// identity of the maximum, so every lane is written and no copy of the old value is needed.
-template <int CTRL>
-__device__ __forceinline__ unsigned dpp_umax32(unsigned v)
-{
-    const unsigned o = (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
-    return o > v ? o : v;
-}
-__device__ __forceinline__ unsigned wave_max_u32(unsigned v)
-{
-    v = dpp_umax32<0xB1>(v);    // quad_perm [1, 0, 3, 2]
-    v = dpp_umax32<0x4E>(v);    // quad_perm [2, 3, 0, 1]
-    v = dpp_umax32<0x141>(v);   // row_half_mirror
-    v = dpp_umax32<0x140>(v);   // row_mirror
-    v = dpp_umax32<0x142>(v);   // row_bcast:15
-    v = dpp_umax32<0x143>(v);   // row_bcast:31
-    return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
-}
-// Maximum over the wave of 64-bit patterns: the largest high word, then the largest low word among
-// the lanes that hold it (one 32-bit maximum per step instead of a 64-bit compare and two selects).
-__device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long v)
-{
-    const unsigned hi = (unsigned)(v >> 32), lo = (unsigned)v;
-    const unsigned mh = wave_max_u32(hi);
-    const unsigned ml = wave_max_u32(hi == mh ? lo : 0u);
-    return ((unsigned long long)mh << 32) | ml;
-}
-
-// Per-channel maximum of `v` (bit patterns of non-negative doubles, so unsigned order is
-// value order and a NaN wins) over the active lanes of a wave.  Lanes are grouped by channel;
-// a group whose channel is `home` goes to the workgroup accumulator in LDS, any other group
-// straight to the global slot of its channel.
-__device__ __forceinline__ void reduce_channel_max(unsigned long long v, int chan, bool active,
-                                                   int home, unsigned long long *s_acc,
-                                                   unsigned long long *gmax)
-{
-    const int lane = threadIdx.x & 63;
-    unsigned long long pending = __ballot(active);
-    while (pending) {
-        const int leader = __ffsll((long long)pending) - 1;
-        const int cl = __shfl(chan, leader, 64);
-        const bool mine = active && (chan == cl);
-        const unsigned long long m = wave_max_u64(mine ? v : 0ull);
-        if (lane == leader) {
-            if (cl == home) atomicMax(s_acc, m);
-            else atomicMax(&gmax[cl], m);
-        }
-        pending &= ~__ballot(mine);
-    }
-}
-
-// Atomic maximum of a workgroup's partial result into a per-channel slot, skipped when the slot
-// already holds at least the value.  Slot values only grow while a kernel runs, so a load that
-// returns an older (smaller) value only costs an atomic that was not needed; the load bypasses
-// the compute unit's cache.  Most workgroups do not hold their channel's maximum, so most
-// flushes skip the atomic, which would otherwise serialise on the one address at the end of
-// the kernel.
-__device__ __forceinline__ void flush_max(unsigned long long *slot, unsigned long long v)
-{
-    const unsigned long long cur = __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (v > cur) atomicMax(slot, v);
-}
-
-// CFL maximum of channel c: the largest of its S sub-slots, as a double.  The floating-point
-// maximum drops a NaN sub-slot when another holds a number; a NaN state still shows, since its
-// cells stay NaN and the host's check of the last slot orders bit patterns as unsigned
-// integers, where NaN is the largest.
-__device__ __forceinline__ double amax_of(const unsigned long long *__restrict__ AM, int c,
-                                         int64_t stride, int split)
-{
-    double m = __longlong_as_double((long long)AM[c]);
-#pragma unroll
-    for (int s = 1; s < kAmaxSplitMax; ++s)
-        if (s < split) m = fmax(m, __longlong_as_double((long long)AM[c + s * stride]));
-    return m;
-}
-
-__device__ __forceinline__ void raise_flag(unsigned int *flags, unsigned bad)
-{
-    if (bad) atomicOr(&flags[0], bad);
-}
-
-// Edge fluctuation and cell speed for the chosen precision and closure form.
-template <int G, int PREC, int CL>
-__device__ __forceinline__ void edge_fluct(double hL, double qL, double zL, double hR, double qR,
-                                           double zR, double g, const Closure &K, double Dm[3],
-                                           double Dp[3], unsigned &bad)
-{
-    if constexpr (PREC == PREC_FP64) fluct64<G, CL>(hL, qL, zL, hR, qR, zR, g, K, Dm, Dp, bad);
-    else if constexpr (PREC == PREC_MIXED) fluct_mixed<G, CL>(hL, qL, zL, hR, qR, zR, g, K, Dm, Dp, bad);
-    else fluct_dot<G, CL>(hL, qL, zL, hR, qR, zR, g, K, Dm, Dp, bad);
-}
-
-template <int PREC, int CL>
-__device__ __forceinline__ double cell_speed(double h, double q, double g, const Closure &K,
-                                             unsigned &bad)
-{
-    if constexpr (PREC == PREC_FP64) return speed64<CL>(h, q, g, K, bad);
-    else if constexpr (PREC == PREC_MIXED) return speed_mixed<CL>(h, q, g, K, bad);
-    else return speed_dot<CL>(h, q, g, K, bad);
-}
-
-// Ghost states (boundary conditions): the state beyond edge 0 (left) or edge N (right) of a
-// channel from the adjacent cell's and the end's boundary data b = {h, q, z, dz/dt}.
-__device__ __forceinline__ double ghost_h(int bc, const double *b, double h)
-{
-    return (bc == BC_FIXED_DEPTH || bc == BC_INFLOW_QH || bc == BC_DIRICHLET) ? b[0] : h;
-}
-__device__ __forceinline__ double ghost_q(int bc, const double *b, double q)
-{
-    return (bc == BC_INFLOW_Q || bc == BC_INFLOW_QH || bc == BC_DIRICHLET) ? b[1] : q;
-}
-__device__ __forceinline__ double ghost_z(int bc, const double *b, double z, double t)
-{
-    return bc == BC_DIRICHLET ? fma(t, b[3], b[2]) : z;
-}
-
-// Index arithmetic of the step kernel: 32-bit when the context has fewer than 2^29 edges (then
+// Index arithmetic of the packed step kernel: 32-bit when the context has fewer than 2^29 edges (then
 // every byte offset into a state array fits in 32 bits and a load is an SGPR base plus a 32-bit
 // VGPR offset), 64-bit otherwise.
 template <bool WIDE> struct StepIdx { using type = int32_t; };
@@ -341,15 +219,6 @@ __global__ __launch_bounds__(kMaxTile, step_min_waves(PREC, CL)) void k_step_pac
 }
 
 // ---------------------------------------------------------------------------
-// Value of the lane below (lane 0 reads 0): one DPP move per 32-bit half.
-__device__ __forceinline__ double lane_below(double v)
-{
-    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)b, 0x138, 0xf, 0xf, true);
-    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x138, 0xf, 0xf, true);
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-
 // Step kernel over segments: each wave takes one segment, a run of cells of one channel, in tiles of
 // 64 edges (63 cells: the first edge of a tile is the last of the tile before, computed by both).
 // Lane l computes edge e = t0 + l of the segment, the left face of cell e, and updates cell e - 1,
@@ -480,110 +349,6 @@ __global__ __launch_bounds__(kMaxTile, step_min_waves(PREC, CL)) void k_step(Ste
         for (int w = t + 1; w < waves && s_chan[w] == s_chan[t]; ++w) v = s_max[w] > v ? s_max[w] : v;
         if (v != 0ull) flush_max(&amax_mine[s_chan[t]], v);
     }
-}
-
-// ---------------------------------------------------------------------------
-// Maximum over the workgroup (uniform result): wave maxima through LDS.  `s_w` holds one entry
-// per wave; consecutive calls are separated by at least one other barrier of the caller.
-__device__ __forceinline__ unsigned long long block_max_u64(unsigned long long v, unsigned long long *s_w)
-{
-    const unsigned long long m = wave_max_u64(v);
-    if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = m;
-    __syncthreads();
-    unsigned long long r = 0ull;
-    const int nw = (blockDim.x + 63) >> 6;
-    for (int w = 0; w < nw; ++w) r = (s_w[w] > r) ? s_w[w] : r;
-    return r;
-}
-
-// Channel-resident run: one workgroup of NT threads takes one channel of N < NT cells (thread i
-// holds cell i and computes edge i, between cells i-1 and i) through all n steps of the run,
-// with the state in registers, the neighbour states and D^- exchanged through LDS, and the
-// channel's CFL maximum reduced within the workgroup; then the next channel.  Every value is
-// computed as in k_step (same fluctuation, update and speed, same order of operations), so the
-// results are bitwise those of the per-step kernels.
-template <int G, int PREC, int CL, int NT>
-__global__ __launch_bounds__(NT, step_min_waves(PREC, CL) < 3 ? step_min_waves(PREC, CL) : 3)
-void k_resident(ResidentArgs A)
-{
-    __shared__ double s_st[3][NT];        // h, q, z of the cells
-    __shared__ double s_dm[3][NT + 1];    // D^- of the edges
-    __shared__ unsigned long long s_w[NT / 64];
-    const int t = threadIdx.x;
-    unsigned bad = 0u;
-    for (int c = blockIdx.x; c < A.n_channels; c += gridDim.x) {
-        const ChanInfo ci = A.ch[c];
-        const Closure K = closure_of(ci);
-        const int64_t cell0 = A.off[c];
-        const int N = (int)(A.off[c + 1] - cell0);
-        const bool has_cell = t < N, has_edge = t <= N;
-        double h = 0.0, q = 0.0, z = 0.0;
-        if (has_cell) {
-            h = A.h[cell0 + t];
-            q = A.q[cell0 + t];
-            z = A.z[cell0 + t];
-        }
-        double tc = A.t[c];
-        unsigned long long sp = 0ull;
-        if (has_cell) sp = (unsigned long long)__double_as_longlong(fabs(cell_speed<PREC, CL>(h, q, A.g, K, bad)));
-        unsigned long long amax_bits = block_max_u64(sp, s_w);
-        for (int n = 0; n < A.n_steps; ++n) {
-            const double dt = ci.cfl_dx * rcp_h(__longlong_as_double((long long)amax_bits));
-            const double r = dt * ci.inv_dx;
-            if (has_cell) {
-                s_st[0][t] = h;
-                s_st[1][t] = q;
-                s_st[2][t] = z;
-            }
-            __syncthreads();
-            double Dm[3] = {0.0, 0.0, 0.0}, Dp[3] = {0.0, 0.0, 0.0};
-            if (has_edge) {
-                const int il = (t == 0) ? (ci.bcl == BC_PERIODIC ? N - 1 : 0) : t - 1;
-                const int ir = (t == N) ? (ci.bcr == BC_PERIODIC ? 0 : N - 1) : t;
-                double hL = s_st[0][il], qL = s_st[1][il], zL = s_st[2][il];
-                double hR = s_st[0][ir], qR = s_st[1][ir], zR = s_st[2][ir];
-                if (t == 0) {
-                    hL = ghost_h(ci.bcl, ci.bl, hL);
-                    qL = ghost_q(ci.bcl, ci.bl, qL);
-                    if (ci.bcl == BC_DIRICHLET) zL = ghost_z(ci.bcl, ci.bl, zL, tc);
-                } else if (t == N) {
-                    hR = ghost_h(ci.bcr, ci.br, hR);
-                    qR = ghost_q(ci.bcr, ci.br, qR);
-                    if (ci.bcr == BC_DIRICHLET) zR = ghost_z(ci.bcr, ci.br, zR, tc);
-                }
-                edge_fluct<G, PREC, CL>(hL, qL, zL, hR, qR, zR, A.g, K, Dm, Dp, bad);
-                s_dm[0][t] = Dm[0];
-                s_dm[1][t] = Dm[1];
-                s_dm[2][t] = Dm[2];
-            }
-            __syncthreads();
-            sp = 0ull;
-            if (has_cell) {
-                // W_i^{n+1} = W_i^n - dt/dx (D^-_{i+1/2} + D^+_{i-1/2}) + dt S(W_i^n) (Sec. 3, Eq. scheme)
-                const double hn = h - r * (s_dm[0][t + 1] + Dp[0]);
-                double qn = q - r * (s_dm[1][t + 1] + Dp[1]);
-                const double zn = z - r * (s_dm[2][t + 1] + Dp[2]);
-                if (ci.fric > 0.0) qn = fma(dt, friction_source(h, q, A.g, ci.fric), qn);
-                h = hn;
-                q = qn;
-                z = zn;
-                sp = (unsigned long long)__double_as_longlong(fabs(cell_speed<PREC, CL>(h, q, A.g, K, bad)));
-            }
-            amax_bits = block_max_u64(sp, s_w);
-            tc += dt;
-        }
-        if (has_cell) {
-            A.h[cell0 + t] = h;
-            A.q[cell0 + t] = q;
-            A.z[cell0 + t] = z;
-        }
-        if (t == 0) {
-            A.t[c] = tc;
-            A.amax[c] = amax_bits;
-        }
-        __syncthreads();   // the next channel reuses the LDS
-    }
-    raise_flag(A.flags, bad);
 }
 
 // ---------------------------------------------------------------------------
@@ -752,54 +517,6 @@ static inline unsigned int cfl_grid(int64_t n_cells)
     return full < 512u ? full : 512u;
 }
 
-// Dispatch over the compile-time variants: G in [1, 5] quadrature points, closure (law).
-#define DSVE_DISPATCH_G_CL(G, CL, MACRO)                                                  \
-    switch ((G) * 8 + (CL)) {                                                             \
-    case 8: MACRO(1, CL_GRASS); break;                                                \
-    case 9: MACRO(1, CL_GRASS_THR); break;                                            \
-    case 10: MACRO(1, CL_POWER); break;                                               \
-    case 11: MACRO(1, CL_MPM); break;                                                 \
-    case 12: MACRO(1, CL_VANRIJN); break;                                             \
-    case 13: MACRO(1, CL_POWER_INT); break;                                           \
-    case 16: MACRO(2, CL_GRASS); break;                                               \
-    case 17: MACRO(2, CL_GRASS_THR); break;                                           \
-    case 18: MACRO(2, CL_POWER); break;                                               \
-    case 19: MACRO(2, CL_MPM); break;                                                 \
-    case 20: MACRO(2, CL_VANRIJN); break;                                             \
-    case 21: MACRO(2, CL_POWER_INT); break;                                           \
-    case 24: MACRO(3, CL_GRASS); break;                                               \
-    case 25: MACRO(3, CL_GRASS_THR); break;                                           \
-    case 26: MACRO(3, CL_POWER); break;                                               \
-    case 27: MACRO(3, CL_MPM); break;                                                 \
-    case 28: MACRO(3, CL_VANRIJN); break;                                             \
-    case 29: MACRO(3, CL_POWER_INT); break;                                           \
-    case 32: MACRO(4, CL_GRASS); break;                                               \
-    case 33: MACRO(4, CL_GRASS_THR); break;                                           \
-    case 34: MACRO(4, CL_POWER); break;                                               \
-    case 35: MACRO(4, CL_MPM); break;                                                 \
-    case 36: MACRO(4, CL_VANRIJN); break;                                             \
-    case 37: MACRO(4, CL_POWER_INT); break;                                           \
-    case 40: MACRO(5, CL_GRASS); break;                                               \
-    case 41: MACRO(5, CL_GRASS_THR); break;                                           \
-    case 42: MACRO(5, CL_POWER); break;                                               \
-    case 43: MACRO(5, CL_MPM); break;                                                 \
-    case 44: MACRO(5, CL_VANRIJN); break;                                             \
-    case 45: MACRO(5, CL_POWER_INT); break;                                           \
-    default: return hipErrorInvalidValue;                                                 \
-    }
-
-// Dispatch over the closure alone.
-#define DSVE_DISPATCH_CL(CL, MACRO)                                                       \
-    switch (CL) {                                                                         \
-    case CL_GRASS: MACRO(CL_GRASS); break;                                                \
-    case CL_GRASS_THR: MACRO(CL_GRASS_THR); break;                                        \
-    case CL_POWER: MACRO(CL_POWER); break;                                                \
-    case CL_MPM: MACRO(CL_MPM); break;                                                    \
-    case CL_VANRIJN: MACRO(CL_VANRIJN); break;                                            \
-    case CL_POWER_INT: MACRO(CL_POWER_INT); break;                                        \
-    default: return hipErrorInvalidValue;                                                 \
-    }
-
 template <int PREC>
 static hipError_t launch_fluct_prec(const FluctArgs &a, int G, int cl, hipStream_t stream)
 {
@@ -944,34 +661,6 @@ hipError_t launch_fill_u32(unsigned int *p, int64_t n, unsigned int v, hipStream
     if (n < 1) return hipSuccess;
     hipLaunchKernelGGL(k_fill_u32, dim3(blocks_for(n, 256)), dim3(256), 0, s, p, n, v);
     return hipGetLastError();
-}
-
-template <int PREC, int NT>
-static hipError_t launch_resident_prec(const ResidentArgs &a, int G, int cl, int grid, hipStream_t s)
-{
-#define DSVE_LAUNCH_RES(GG, CC) hipLaunchKernelGGL((k_resident<GG, PREC, CC, NT>), dim3(grid), dim3(NT), 0, s, a)
-    DSVE_DISPATCH_G_CL(G, cl, DSVE_LAUNCH_RES)
-#undef DSVE_LAUNCH_RES
-    return hipGetLastError();
-}
-
-template <int NT>
-static hipError_t launch_resident_nt(const ResidentArgs &a, int precision, int G, int cl, int grid,
-                                     hipStream_t stream)
-{
-    if (precision == PREC_FP64) return launch_resident_prec<PREC_FP64, NT>(a, G, cl, grid, stream);
-    if (precision == PREC_MIXED) return launch_resident_prec<PREC_MIXED, NT>(a, G, cl, grid, stream);
-    if (precision == PREC_DOT) return launch_resident_prec<PREC_DOT, NT>(a, G, cl, grid, stream);
-    return hipErrorNotSupported;
-}
-
-hipError_t launch_resident(const ResidentArgs &a, int precision, int G, int cl, int threads, int grid,
-                           hipStream_t stream)
-{
-    if (grid < 1 || a.n_channels < 1 || a.n_steps < 1) return hipErrorInvalidValue;
-    if (threads == 256) return launch_resident_nt<256>(a, precision, G, cl, grid, stream);
-    if (threads == 512) return launch_resident_nt<512>(a, precision, G, cl, grid, stream);
-    return hipErrorInvalidValue;
 }
 
 int amax_split_of_kernels() { return kAmaxSplitMax; }

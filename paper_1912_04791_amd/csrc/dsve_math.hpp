@@ -589,13 +589,27 @@ __device__ __forceinline__ bool in_seed_range(float gh)
 struct OuterSums {
     double P0, P1, P2, S1, S2;
 };
+// What one node adds to them: factors of the products that are summed with one rounding each.  A NaN
+// pb marks a node that the refinement does not serve.
+struct Terms64 {
+    double pb, lam, p2a, p2b, s1a, s1b, s2a, s2b;
+};
+__device__ __forceinline__ void add_terms(OuterSums &N, const Terms64 &T)
+{
+    N.P0 += T.pb;
+    N.P1 = fma(T.pb, T.lam, N.P1);
+    N.P2 = fma(T.p2a, T.p2b, N.P2);
+    N.S1 = fma(T.s1a, T.s1b, N.S1);
+    N.S2 = fma(T.s2a, T.s2b, N.S2);
+}
 
-// One node into the sums of an edge; dir = +-1 is the direction of the flow.  False where the node is
-// too close to coalescing roots (or not finite) for the refinement.
+// One node of an edge; dir = +-1 is the direction of the flow.  False where the node is too close to
+// coalescing roots (or not finite) for the refinement.
 template <int CL>
 __device__ __forceinline__ bool node_outer(const Node64 &n, const Closure &K, float dir, double w, double dh,
-                                           double dq, double eta, OuterSums &N)
+                                           double dq, double eta, Terms64 &T)
 {
+#pragma clang fp contract(off)
     constexpr double kappa = (CL == CL_MPM || CL == CL_VANRIJN) ? 7.0 / 6.0 : 1.0;
     // root o in FP32, in units of c at |Fr| (there the smallest), and 1 / p'
     const float ghf = (float)n.gh;
@@ -622,15 +636,99 @@ __device__ __forceinline__ bool node_outer(const Node64 &n, const Closure &K, fl
     // (l_o . dW) p' = g h (dh + dz) + lambda_o dq + (lambda_j lambda_k - u^2) dh
     const double no = fma(n.gh, eta, fma(lam, dq, fma(lam, l2, -sb) * dh));
     const double wn = w * (no * ip);
-    const double pb = wn * lam;
     const double ku = kappa == 1.0 ? n.u : kappa * n.u;
-    N.P0 += pb;
-    N.P1 = fma(pb, lam, N.P1);
-    N.P2 = fma(wn * n.b, lam - ku, N.P2);
     const double t = fma(-n.u, dh, dq);
-    N.S1 = fma(w * n.u, t + dq, N.S1);
-    N.S2 = fma(w * n.b, kappa == 1.0 ? t : fma(-ku, dh, dq), N.S2);
+    T.pb = wn * lam;
+    T.lam = lam;
+    T.p2a = wn * n.b;
+    T.p2b = lam - ku;
+    T.s1a = w * n.u;
+    T.s1b = t + dq;
+    T.s2a = w * n.b;
+    T.s2b = kappa == 1.0 ? t : fma(-ku, dh, dq);
     return fabsf(x) < 1.0f - kSeedBand;
+}
+
+// D^- and D^+ of an edge with flow in one direction (up: towards +x), from its sums; gh_eta is the sum
+// of w g h (dh + dz).
+__device__ __forceinline__ void outer_to_fluct(const OuterSums &N, bool up, double dq, double gh_eta, double Dm[3],
+                                               double Dp[3])
+{
+#pragma clang fp contract(off)
+    const double Q0 = dq - N.P0, Q1 = (N.S1 + gh_eta) - N.P1, Q2 = N.S2 - N.P2;
+    Dm[0] = up ? N.P0 : Q0;
+    Dm[1] = up ? N.P1 : Q1;
+    Dm[2] = up ? N.P2 : Q2;
+    Dp[0] = up ? Q0 : N.P0;
+    Dp[1] = up ? Q1 : N.P1;
+    Dp[2] = up ? Q2 : N.P2;
+}
+
+// The same where the direction may change along the path: the nodes of either direction summed apart,
+// U towards +x and D towards -x, with the sums of w and of w g h over the latter.
+struct TwoSums {
+    OuterSums U = {0.0, 0.0, 0.0, 0.0, 0.0}, D = {0.0, 0.0, 0.0, 0.0, 0.0};
+    double wd = 0.0, gd = 0.0;
+};
+__device__ __forceinline__ void add_terms(TwoSums &N, const Terms64 &T, bool u, double w, double gh)
+{
+    OuterSums S;
+    S.P0 = u ? N.U.P0 : N.D.P0;
+    S.P1 = u ? N.U.P1 : N.D.P1;
+    S.P2 = u ? N.U.P2 : N.D.P2;
+    S.S1 = u ? N.U.S1 : N.D.S1;
+    S.S2 = u ? N.U.S2 : N.D.S2;
+    add_terms(S, T);
+    N.U.P0 = u ? S.P0 : N.U.P0;
+    N.U.P1 = u ? S.P1 : N.U.P1;
+    N.U.P2 = u ? S.P2 : N.U.P2;
+    N.U.S1 = u ? S.S1 : N.U.S1;
+    N.U.S2 = u ? S.S2 : N.U.S2;
+    N.D.P0 = u ? N.D.P0 : S.P0;
+    N.D.P1 = u ? N.D.P1 : S.P1;
+    N.D.P2 = u ? N.D.P2 : S.P2;
+    N.D.S1 = u ? N.D.S1 : S.S1;
+    N.D.S2 = u ? N.D.S2 : S.S2;
+    N.wd = u ? N.wd : N.wd + w;
+    N.gd = u ? N.gd : fma(w, gh, N.gd);
+}
+// one: flow in one direction (then the bits of outer_to_fluct), up as there.
+__device__ __forceinline__ void two_to_fluct(const TwoSums &N, bool one, bool up, double dq, double gh_eta,
+                                             double eta, double Dm[3], double Dp[3])
+{
+#pragma clang fp contract(off)
+    const OuterSums &U = N.U, &D = N.D;
+    const double ed = one ? (up ? 0.0 : gh_eta) : N.gd * eta, eu = one ? (up ? gh_eta : 0.0) : gh_eta - ed;
+    const double Qd0 = one ? dq - D.P0 : fma(N.wd, dq, -D.P0);
+    const double Qd1 = (D.S1 + ed) - D.P1, Qd2 = D.S2 - D.P2;
+    const double Qu1 = (U.S1 + eu) - U.P1, Qu2 = U.S2 - U.P2;
+    Dm[0] = one ? (up ? U.P0 : Qd0) : U.P0 + Qd0;
+    Dp[0] = one && !up ? D.P0 : dq - Dm[0];
+    Dm[1] = one ? (up ? U.P1 : Qd1) : U.P1 + Qd1;
+    Dm[2] = one ? (up ? U.P2 : Qd2) : U.P2 + Qd2;
+    Dp[1] = one ? (up ? Qu1 : D.P1) : D.P1 + Qu1;
+    Dp[2] = one ? (up ? Qu2 : D.P2) : D.P2 + Qu2;
+}
+
+// An edge as fluct64 sees it: its jumps, the direction of its flow, and whether the FP32 estimate can
+// represent its depths.
+struct Edge64 {
+    double dh, dq, dz, eta, gh_eta;
+    bool up, one, ok;
+};
+__device__ __forceinline__ Edge64 edge64(double hL, double qL, double zL, double hR, double qR, double zR, double g)
+{
+#pragma clang fp contract(off)
+    Edge64 e;
+    e.dh = hR - hL;
+    e.dq = qR - qL;
+    e.dz = zR - zL;
+    e.eta = e.dh + e.dz;
+    e.gh_eta = (g * fma(0.5, e.dh, hL)) * e.eta;
+    e.up = qL >= 0.0 && qR >= 0.0;
+    e.one = e.up || (qL <= 0.0 && qR <= 0.0);
+    e.ok = in_seed_range((float)(g * hL)) && in_seed_range((float)(g * hR));
+    return e;
 }
 
 // DOT fluctuations of one edge, FP64 throughout.
@@ -669,68 +767,33 @@ __device__ __forceinline__ void fluct64(double hL, double qL, double zL, double 
                                         double zR, double g, const Closure &K, double Dm[3],
                                         double Dp[3], unsigned &bad)
 {
-    const double dh = hR - hL, dq = qR - qL, dz = zR - zL, eta = dh + dz;
-    const bool up = qL >= 0.0 && qR >= 0.0;
-    const bool one = up || (qL <= 0.0 && qR <= 0.0);
-    bool ok = in_seed_range((float)(g * hL)) && in_seed_range((float)(g * hR));
-    const double gh_eta = (g * fma(0.5, dh, hL)) * eta;
-    if (__builtin_amdgcn_ballot_w64(!one) == 0ull) {
-        const float dir = up ? 1.0f : -1.0f;
+    const Edge64 E = edge64(hL, qL, zL, hR, qR, zR, g);
+    bool ok = E.ok;
+    if (__builtin_amdgcn_ballot_w64(!E.one) == 0ull) {
+        const float dir = E.up ? 1.0f : -1.0f;
         OuterSums N = {0.0, 0.0, 0.0, 0.0, 0.0};
         DSVE_UNROLL(DSVE_NODE_UNROLL)
         for (int k = 0; k < G; ++k) {
             const double s = Gauss<G>::s[k];
-            const Node64 n = node_state64<CL>(fma(s, dh, hL), fma(s, dq, qL), g, K);
-            ok = node_outer<CL>(n, K, dir, Gauss<G>::w[k], dh, dq, eta, N) && ok;
+            const Node64 n = node_state64<CL>(fma(s, E.dh, hL), fma(s, E.dq, qL), g, K);
+            Terms64 T;
+            ok = node_outer<CL>(n, K, dir, Gauss<G>::w[k], E.dh, E.dq, E.eta, T) && ok;
+            add_terms(N, T);
         }
-        const double Q0 = dq - N.P0, Q1 = (N.S1 + gh_eta) - N.P1, Q2 = N.S2 - N.P2;
-        Dm[0] = up ? N.P0 : Q0;
-        Dm[1] = up ? N.P1 : Q1;
-        Dm[2] = up ? N.P2 : Q2;
-        Dp[0] = up ? Q0 : N.P0;
-        Dp[1] = up ? Q1 : N.P1;
-        Dp[2] = up ? Q2 : N.P2;
+        outer_to_fluct(N, E.up, E.dq, E.gh_eta, Dm, Dp);
     } else {
-        OuterSums U = {0.0, 0.0, 0.0, 0.0, 0.0}, D = U;   // nodes with flow towards +x, towards -x
-        double wd = 0.0, gd = 0.0;       // sums of w and of w g h over the latter
+        TwoSums N;
 #pragma unroll 1
         for (int k = 0; k < G; ++k) {
             const double s = Gauss<G>::s[k], w = Gauss<G>::w[k];
-            const double q = fma(s, dq, qL);
-            const Node64 n = node_state64<CL>(fma(s, dh, hL), q, g, K);
-            const bool u = one ? up : q >= 0.0;
-            OuterSums N;
-            N.P0 = u ? U.P0 : D.P0;
-            N.P1 = u ? U.P1 : D.P1;
-            N.P2 = u ? U.P2 : D.P2;
-            N.S1 = u ? U.S1 : D.S1;
-            N.S2 = u ? U.S2 : D.S2;
-            ok = node_outer<CL>(n, K, u ? 1.0f : -1.0f, w, dh, dq, eta, N) && ok;
-            U.P0 = u ? N.P0 : U.P0;
-            U.P1 = u ? N.P1 : U.P1;
-            U.P2 = u ? N.P2 : U.P2;
-            U.S1 = u ? N.S1 : U.S1;
-            U.S2 = u ? N.S2 : U.S2;
-            D.P0 = u ? D.P0 : N.P0;
-            D.P1 = u ? D.P1 : N.P1;
-            D.P2 = u ? D.P2 : N.P2;
-            D.S1 = u ? D.S1 : N.S1;
-            D.S2 = u ? D.S2 : N.S2;
-            wd = u ? wd : wd + w;
-            gd = u ? gd : fma(w, n.gh, gd);
+            const double q = fma(s, E.dq, qL);
+            const Node64 n = node_state64<CL>(fma(s, E.dh, hL), q, g, K);
+            const bool u = E.one ? E.up : q >= 0.0;
+            Terms64 T;
+            ok = node_outer<CL>(n, K, u ? 1.0f : -1.0f, w, E.dh, E.dq, E.eta, T) && ok;
+            add_terms(N, T, u, w, n.gh);
         }
-        // one direction: P and A dW less P, as above; both: D^- = P of +x and A dW less P of -x
-        const double ed = one ? (up ? 0.0 : gh_eta) : gd * eta, eu = one ? (up ? gh_eta : 0.0) : gh_eta - ed;
-        const double Qd0 = one ? dq - D.P0 : fma(wd, dq, -D.P0);
-        const double Qd1 = (D.S1 + ed) - D.P1, Qd2 = D.S2 - D.P2;
-        const double Qu1 = (U.S1 + eu) - U.P1, Qu2 = U.S2 - U.P2;
-        const bool dn = one && !up;
-        Dm[0] = one ? (up ? U.P0 : Qd0) : U.P0 + Qd0;
-        Dp[0] = dn ? D.P0 : dq - Dm[0];
-        Dm[1] = one ? (up ? U.P1 : Qd1) : U.P1 + Qd1;
-        Dm[2] = one ? (up ? U.P2 : Qd2) : U.P2 + Qd2;
-        Dp[1] = one ? (up ? Qu1 : D.P1) : D.P1 + Qu1;
-        Dp[2] = one ? (up ? Qu2 : D.P2) : D.P2 + Qu2;
+        two_to_fluct(N, E.one, E.up, E.dq, E.gh_eta, E.eta, Dm, Dp);
     }
     if (!ok) fluct64_general<G, CL>(hL, qL, zL, hR, qR, zR, g, K, Dm, Dp, bad);
 }
@@ -783,6 +846,7 @@ struct EigF {
 template <int CL>
 __device__ __forceinline__ bool eigf(float h, float q, float g, const Closure &K, EigF &E)
 {
+#pragma clang fp contract(off)
     const float gh = g * h;
     const float t = __builtin_amdgcn_rsqf(gh * h * h);
     const float Fr = q * t;
@@ -822,68 +886,97 @@ __device__ __forceinline__ bool eigf(float h, float q, float g, const Closure &K
     return true;
 }
 
-// One FP32 node: SA += w A dW (rows 1, 2), SB += w |A| dW.  eta = dh + dz (rounded from FP64):
-// (1 - Fr^2) dh + dz = eta - Fr^2 dh keeps a still free surface (eta = 0, Fr = 0) exact.
-__device__ __forceinline__ void node_accumulatef(const EigF &E, float w, float dh, float dq, float eta,
-                                                 float SA[3], float SB[3])
+// What one node of the mixed form adds to SA (w A dW, rows 1, 2) and SB (w |A| dW): factors of the
+// products that are summed with one rounding each.
+struct TermsF {
+    float wcc, A1n, wc, A2n, wcP, B0, wccP, B1, B2;
+};
+__device__ __forceinline__ void add_terms(float SA[3], float SB[3], const TermsF &T)
 {
+    SA[1] = fmaf(T.wcc, T.A1n, SA[1]);
+    SA[2] = fmaf(T.wc, T.A2n, SA[2]);
+    SB[0] = fmaf(T.wcP, T.B0, SB[0]);
+    SB[1] = fmaf(T.wccP, T.B1, SB[1]);
+    SB[2] = fmaf(T.wcP, T.B2, SB[2]);
+}
+
+// One FP32 node.  eta = dh + dz (rounded from FP64): (1 - Fr^2) dh + dz = eta - Fr^2 dh keeps a still
+// free surface (eta = 0, Fr = 0) exact.
+__device__ __forceinline__ TermsF node_termsf(const EigF &E, float w, float dh, float dq, float eta)
+{
+#pragma clang fp contract(off)
     const float Fr = E.Fr, c = E.c;
     const float mu1 = E.mu1, mu2 = E.mu2, mu3 = E.mu3;
     const float dqn = dq * E.inv_c;
     const float nF2 = -Fr * Fr;
-    const float A1n = fmaf(nF2, dh, fmaf(2.0f * Fr, dqn, eta));
-    const float A2n = E.b * fmaf(-E.kFr, dh, dqn);
+    TermsF T;
+    T.A1n = fmaf(nF2, dh, fmaf(2.0f * Fr, dqn, eta));
+    T.A2n = E.b * fmaf(-E.kFr, dh, dqn);
     const float n1 = fmaf(fmaf(mu2, mu3, nF2), dh, fmaf(mu1, dqn, eta));
     const float n2 = fmaf(fmaf(mu3, mu1, nF2), dh, fmaf(mu2, dqn, eta));
     const float n3 = fmaf(fmaf(mu1, mu2, nF2), dh, fmaf(mu3, dqn, eta));
-    const float b1 = n1 * (fabsf(mu1) * E.g32);
-    const float b2 = -n2 * (fabsf(mu2) * E.g31);
-    const float b3 = n3 * (fabsf(mu3) * E.g21);
+    const float t1 = fabsf(mu1) * E.g32, t3 = fabsf(mu3) * E.g21;
+    const float b1 = n1 * t1;
+    const float t2 = fabsf(mu2) * E.g31;
+    const float b2 = -n2 * t2;
+    const float b3 = n3 * t3;
     const float e1 = Fr - mu1, e2 = Fr - mu2, e3 = Fr - mu3;
-    const float B0 = b1 + b2 + b3;
-    const float B1 = fmaf(b1, mu1, fmaf(b2, mu2, b3 * mu3));
-    const float B2 = fmaf(b1, fmaf(e1, e1, -1.0f), fmaf(b2, fmaf(e2, e2, -1.0f), b3 * fmaf(e3, e3, -1.0f)));
-    const float wc = w * c, wcc = wc * c;
-    const float wcP = wc * E.inv_gp, wccP = wcc * E.inv_gp;
-    SA[1] = fmaf(wcc, A1n, SA[1]);
-    SA[2] = fmaf(wc, A2n, SA[2]);
-    SB[0] = fmaf(wcP, B0, SB[0]);
-    SB[1] = fmaf(wccP, B1, SB[1]);
-    SB[2] = fmaf(wcP, B2, SB[2]);
+    T.B0 = fmaf(n3, t3, fmaf(-n2, t2, b1));   // b1 + b2 + b3
+    T.B1 = fmaf(b1, mu1, fmaf(b2, mu2, b3 * mu3));
+    T.B2 = fmaf(b1, fmaf(e1, e1, -1.0f), fmaf(b2, fmaf(e2, e2, -1.0f), b3 * fmaf(e3, e3, -1.0f)));
+    T.wc = w * c;
+    T.wcc = T.wc * c;
+    T.wcP = T.wc * E.inv_gp;
+    T.wccP = T.wcc * E.inv_gp;
+    return T;
 }
 
-template <int G, int CL>
-__device__ __forceinline__ void fluct_mixed(double hL, double qL, double zL, double hR, double qR,
-                                            double zR, double g, const Closure &K, double Dm[3],
-                                            double Dp[3], unsigned &bad)
+// An edge as fluct_mixed sees it: its jumps in FP64 and FP32.
+struct EdgeF {
+    double dh, dq, dz;
+    float dhf, dqf, etaf, hLf, qLf;
+};
+__device__ __forceinline__ EdgeF edgef(double hL, double qL, double zL, double hR, double qR, double zR)
 {
-    const double dh = hR - hL, dq = qR - qL, dz = zR - zL;
-    const float dhf = (float)dh, dqf = (float)dq, etaf = (float)(dh + dz);
-    const float hLf = (float)hL, qLf = (float)qL;
-    const float gf = (float)g;
-    // the node sums in FP32 (row 0 of S_A is dq, in FP64); a node in the band is evaluated in FP64
-    // and its terms, which no longer carry the FP32 error near coalescence, are added rounded
-    float SA[3] = {0.f, 0.f, 0.f}, SB[3] = {0.f, 0.f, 0.f};
-    unsigned long long xmax = 0ull;
-    DSVE_UNROLL(DSVE_NODE_UNROLL)
-    for (int k = 0; k < G; ++k) {
-        const float sf = (float)Gauss<G>::s[k];
-        EigF E;
-        if (eigf<CL>(fmaf(sf, dhf, hLf), fmaf(sf, dqf, qLf), gf, K, E)) {
-            node_accumulatef(E, (float)Gauss<G>::w[k], dhf, dqf, etaf, SA, SB);
-        } else {
-            const double s = Gauss<G>::s[k];
-            Eig64 E64;
-            eig64<CL>(fma(s, dh, hL), fma(s, dq, qL), g, K, E64, xmax);
-            double NA[3] = {0.0, 0.0, 0.0}, NB[3] = {0.0, 0.0, 0.0};
-            node_accumulate64(E64, Gauss<G>::w[k], dh, dq, dz, NA, NB);
-            SA[1] += (float)NA[1];
-            SA[2] += (float)NA[2];
-#pragma unroll
-            for (int r = 0; r < 3; ++r) SB[r] += (float)NB[r];
-        }
-    }
-    bad |= arg_flags(xmax, true);
+    EdgeF e;
+    e.dh = hR - hL;
+    e.dq = qR - qL;
+    e.dz = zR - zL;
+    e.dhf = (float)e.dh;
+    e.dqf = (float)e.dq;
+    e.etaf = (float)(e.dh + e.dz);
+    e.hLf = (float)hL;
+    e.qLf = (float)qL;
+    return e;
+}
+
+// A node in the band: evaluated in FP64, its terms, which no longer carry the FP32 error near
+// coalescence, are added rounded.
+template <int CL>
+__device__ __forceinline__ TermsF node_band(const EdgeF &e, double s, double w, double hL, double qL, double g,
+                                            const Closure &K, unsigned long long &xmax)
+{
+    Eig64 E64;
+    eig64<CL>(fma(s, e.dh, hL), fma(s, e.dq, qL), g, K, E64, xmax);
+    double NA[3] = {0.0, 0.0, 0.0}, NB[3] = {0.0, 0.0, 0.0};
+    node_accumulate64(E64, w, e.dh, e.dq, e.dz, NA, NB);
+    return TermsF{1.0f, (float)NA[1], 1.0f, (float)NA[2], 1.0f, (float)NB[0], 1.0f, (float)NB[1], (float)NB[2]};
+}
+// One node (at s, with weight w) of the mixed form.
+template <int CL>
+__device__ __forceinline__ TermsF node_mixed(const EdgeF &e, double s, double w, double hL, double qL, double g,
+                                             const Closure &K, unsigned long long &xmax)
+{
+    EigF E;
+    if (eigf<CL>(fmaf((float)s, e.dhf, e.hLf), fmaf((float)s, e.dqf, e.qLf), (float)g, K, E))
+        return node_termsf(E, (float)w, e.dhf, e.dqf, e.etaf);
+    return node_band<CL>(e, s, w, hL, qL, g, K, xmax);
+}
+
+// D^- and D^+ from the node sums (row 0 of S_A is dq, in FP64).
+__device__ __forceinline__ void sums_to_fluctf(const float SA[3], const float SB[3], double dq, double Dm[3],
+                                               double Dp[3])
+{
     const double A[3] = {dq, (double)SA[1], (double)SA[2]};
 #pragma unroll
     for (int r = 0; r < 3; ++r) {
@@ -891,6 +984,28 @@ __device__ __forceinline__ void fluct_mixed(double hL, double qL, double zL, dou
         Dm[r] = 0.5 * (A[r] - B);
         Dp[r] = 0.5 * (A[r] + B);
     }
+}
+
+template <int G, int CL>
+__device__ __forceinline__ void fluct_mixed(double hL, double qL, double zL, double hR, double qR,
+                                            double zR, double g, const Closure &K, double Dm[3],
+                                            double Dp[3], unsigned &bad)
+{
+    const EdgeF e = edgef(hL, qL, zL, hR, qR, zR);
+    const float gf = (float)g;
+    float SA[3] = {0.f, 0.f, 0.f}, SB[3] = {0.f, 0.f, 0.f};
+    unsigned long long xmax = 0ull;
+    DSVE_UNROLL(DSVE_NODE_UNROLL)
+    for (int k = 0; k < G; ++k) {
+        const float sf = (float)Gauss<G>::s[k];
+        EigF E;
+        if (eigf<CL>(fmaf(sf, e.dhf, e.hLf), fmaf(sf, e.dqf, e.qLf), gf, K, E))
+            add_terms(SA, SB, node_termsf(E, (float)Gauss<G>::w[k], e.dhf, e.dqf, e.etaf));
+        else
+            add_terms(SA, SB, node_band<CL>(e, Gauss<G>::s[k], Gauss<G>::w[k], hL, qL, g, K, xmax));
+    }
+    bad |= arg_flags(xmax, true);
+    sums_to_fluctf(SA, SB, e.dq, Dm, Dp);
 }
 
 // CFL speed in FP32 for the mixed form (the largest root at |Fr|, as speed64); the FP64 speed
