@@ -1,14 +1,15 @@
 // dsve_api.cpp -- host side of libdsve.so: the C ABI declared in include/dsve.h.
 //
-// A context owns: per-channel records and edge offsets on the device, the tile table of the
-// fused step kernel, one ping-pong copy of the state and clocks, three rotating CFL-maximum slots
-// (each with up to 4 sub-slots per channel), a flag word for deferred device errors, and a cached
-// HIP graph of `graph_steps` fused steps, plus a few graphs of shorter lengths.  A run of n steps
-// is: clear slots -> CFL max of W^0 into slot 0 -> n / graph_steps replays of the main graph
-// (each node is one step kernel; slot and ping-pong phase repeat every 6 steps, so graph_steps
-// is a multiple of 6) -> one replay of the graph of the remaining n % graph_steps steps -> copy
-// back when n is odd.  With graph_steps = 0 every step is launched directly.  When every channel has at most kResidentCells cells the run is instead
-// one channel-resident launch for all n steps.
+// A context owns: per-channel records and edge offsets on the device, the step kernel's table of
+// segments (or the packed kernel's tile table), one ping-pong copy of the state and clocks, three
+// rotating CFL-maximum slots (each with up to 4 sub-slots per channel), a flag word for deferred device
+// errors, and cached HIP graphs of `graph_steps` fused steps and of a few shorter lengths.  A run of n
+// steps is: clear slots -> CFL max of W^0 into slot 0 and, when n is odd, the copy of the state that the
+// run then starts from -> n / graph_steps replays of the main graph (each node is one step kernel; slot
+// and ping-pong phase repeat every 6 steps, so graph_steps is a multiple of 6) -> one replay of the graph
+// of the remaining n % graph_steps steps.  With graph_steps = 0 every step is launched directly.  When
+// every channel has at most kResidentCells cells, or there are few channels (build_parts), the run is one
+// launch instead.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -63,6 +64,7 @@ struct dsve_ctx {
     int parts_grid = 0;
     bool launch_set = false;     // a launch configuration was asked for: per-step kernels where not resident
     unsigned int *d_flags = nullptr;                             // [4]
+    unsigned long long *d_acc = nullptr;                         // [2] of cfl_reduce
 
     int tile = 256, blocks_per_cu = 0, graph_steps = 60;
     bool packed = false;               // short channels: the packed step kernel (tile table)
@@ -74,7 +76,7 @@ struct dsve_ctx {
 
     // captured graphs, valid for the buffers and launch in g_key / g_*: the main graph of
     // graph_steps steps, and graphs of the remainders n % graph_steps of recent run lengths
-    hipGraphExec_t gexec = nullptr;
+    hipGraphExec_t gexec[2] = {nullptr, nullptr};   // starting from the caller's arrays, from their copy
     struct RemGraph { hipGraphExec_t exec = nullptr; int steps = 0; };
     RemGraph rem[4];
     int rem_next = 0;
@@ -178,8 +180,10 @@ static dsve_status check_channel(int law, const dsve_channel &ch, std::string &m
 
 static void free_graph(dsve_ctx *c)
 {
-    if (c->gexec) (void)hipGraphExecDestroy(c->gexec);
-    c->gexec = nullptr;
+    for (hipGraphExec_t &g : c->gexec) {
+        if (g) (void)hipGraphExecDestroy(g);
+        g = nullptr;
+    }
     for (auto &r : c->rem) {
         if (r.exec) (void)hipGraphExecDestroy(r.exec);
         r = dsve_ctx::RemGraph{};
@@ -386,6 +390,8 @@ static dsve_status setup(dsve_ctx *c, void *stream)
     if (st != DSVE_OK) return st;
     HIP_TRY(c, hipMalloc(&c->d_amax, sizeof(unsigned long long) * (3 * c->amax_slot + part_box_words(c->n_parts))));
     HIP_TRY(c, hipMalloc(&c->d_flags, sizeof(unsigned int) * 4));
+    HIP_TRY(c, hipMalloc(&c->d_acc, sizeof(unsigned long long) * 2));
+    HIP_TRY(c, launch_fill_u64(c->d_acc, 2, 0ull, c->stream));
     HIP_TRY(c, launch_fill_u64(c->d_amax, 3 * c->amax_slot, 0ull, c->stream));
     HIP_TRY(c, launch_fill_u32(c->d_flags, 4, 0u, c->stream));
     // the device address of the static scratch of adot_step_noalloc, looked up once per device
@@ -417,6 +423,7 @@ static void release(dsve_ctx *c)
     (void)hipFree(c->pp_t);
     (void)hipFree(c->d_amax);
     (void)hipFree(c->d_flags);
+    (void)hipFree(c->d_acc);
     (void)hipFree(c->d_tile_chan);
     (void)hipFree(c->d_segments);
     (void)hipFree(c->d_parts);
@@ -634,18 +641,6 @@ dsve_status cell_update(dsve_ctx *ctx, const double *Dm, const double *Dp, const
     return DSVE_OK;
 }
 
-static dsve_status enqueue_cfl(dsve_ctx *ctx, const double *h, const double *q, const double *z,
-                               unsigned long long *amax)
-{
-    HIP_TRY(ctx, launch_fill_u64(amax, ctx->n_channels, 0ull, ctx->stream));
-    CflArgs a{};
-    a.h = h; a.q = q; a.z = z; a.ch = ctx->d_ch; a.off = ctx->d_off; a.amax = amax;
-    a.flags = ctx->d_flags; a.n_cells = ctx->n_cells; a.n_channels = (int32_t)ctx->n_channels;
-    a.g = ctx->g;
-    HIP_TRY(ctx, launch_cfl(a, ctx->precision, ctx->cl, ctx->stream));
-    return DSVE_OK;
-}
-
 dsve_status cfl_reduce(dsve_ctx *ctx, const double *h, const double *q, const double *z,
                        double *amax_dev, double *dt_dev)
 {
@@ -654,13 +649,11 @@ dsve_status cfl_reduce(dsve_ctx *ctx, const double *h, const double *q, const do
     if (ctx->batched) return fail(ctx, DSVE_E_ARG, "cfl_reduce needs a single-channel context");
     if (!h || !q || !z || !amax_dev || !dt_dev) return fail(ctx, DSVE_E_ARG, "null pointer");
     if (((uintptr_t)amax_dev) & 7) return fail(ctx, DSVE_E_ARG, "amax_dev must be 8-byte aligned");
-    unsigned long long *am = reinterpret_cast<unsigned long long *>(amax_dev);
-    dsve_status st = enqueue_cfl(ctx, h, q, z, am);
-    if (st != DSVE_OK) return st;
-    HIP_TRY(ctx, launch_dt(am, ctx->d_ch, 1, dt_dev, ctx->stream));
-    HIP_TRY(ctx, launch_fill_u64(ctx->d_amax, ctx->amax_slot, 0ull, ctx->stream));
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->d_amax, am, sizeof(unsigned long long), hipMemcpyDeviceToDevice,
-                                ctx->stream));
+    CflOneArgs a{};
+    a.h = h; a.q = q; a.amax = amax_dev; a.dt = dt_dev; a.acc = ctx->d_acc;
+    a.slot = ctx->d_amax; a.slot_stride = ctx->amax_cs; a.flags = ctx->d_flags;
+    a.n = ctx->n_cells; a.g = ctx->g; a.ci = ctx->h_ch[0];
+    HIP_TRY(ctx, launch_cfl_one(a, ctx->precision, ctx->cl, ctx->stream));
     ctx->last_amax_slot = 0;
     return DSVE_OK;
 }
@@ -706,12 +699,12 @@ static RunBufs scratch_bufs(const dsve_ctx *c)
             reinterpret_cast<unsigned long long *>(base + kNoAllocOffAmax)};
 }
 
-// Arguments of step j (phase j mod 6) of a run starting from the caller's buffers.
-static StepArgs step_args(dsve_ctx *ctx, const RunBufs &b, int j, double *h, double *q, double *z,
-                          double *t)
+// Arguments of step j (phase j mod 6) of a run starting from the caller's buffers, or from their copy.
+static StepArgs step_args(dsve_ctx *ctx, const RunBufs &b, int j, bool from_copy, double *h, double *q,
+                          double *z, double *t)
 {
     StepArgs a{};
-    const bool even = (j % 2) == 0;
+    const bool even = (j % 2 == 0) != from_copy;
     a.h = even ? h : b.pp_h;
     a.q = even ? q : b.pp_q;
     a.z = even ? z : b.pp_z;
@@ -739,15 +732,51 @@ static StepArgs step_args(dsve_ctx *ctx, const RunBufs &b, int j, double *h, dou
     return a;
 }
 
+// A run of an odd number of steps would end in the ping-pong copy: over segments it starts from there
+// instead, the copy made while the CFL maxima are taken; the packed kernel's copies back at the end.
+static bool starts_from_copy(const dsve_ctx *ctx, int n_steps) { return !ctx->packed && (n_steps & 1); }
+
+// The CFL maxima of W^0 into sub-slot 0 of slot 0, all slots cleared first, and that copy.
+static dsve_status start_run(dsve_ctx *ctx, const RunBufs &b, int n_steps, double *h, double *q, double *z,
+                             double *t)
+{
+    HIP_TRY(ctx, launch_fill_u64(b.amax, 3 * ctx->amax_slot, 0ull, ctx->stream));
+    if (!ctx->packed) {
+        StepArgs a = step_args(ctx, b, 0, false, h, q, z, t);
+        a.amax_next = b.amax;
+        HIP_TRY(ctx, launch_start(a, ctx->precision, ctx->cl, starts_from_copy(ctx, n_steps), ctx->stream));
+        return DSVE_OK;
+    }
+    CflArgs a{};
+    a.h = h; a.q = q; a.z = z; a.ch = ctx->d_ch; a.off = ctx->d_off; a.amax = b.amax;
+    a.flags = ctx->d_flags; a.n_cells = ctx->n_cells; a.n_channels = (int32_t)ctx->n_channels;
+    a.g = ctx->g;
+    HIP_TRY(ctx, launch_cfl(a, ctx->precision, ctx->cl, ctx->stream));
+    return DSVE_OK;
+}
+
+// The packed kernel's result of an odd run back into the caller's arrays.
+static dsve_status finish_run(dsve_ctx *ctx, const RunBufs &b, int n_steps, double *h, double *q, double *z,
+                              double *t)
+{
+    if (!(n_steps & 1) || starts_from_copy(ctx, n_steps)) return DSVE_OK;
+    const size_t bytes = sizeof(double) * ctx->n_cells;
+    HIP_TRY(ctx, hipMemcpyAsync(h, b.pp_h, bytes, hipMemcpyDeviceToDevice, ctx->stream));
+    HIP_TRY(ctx, hipMemcpyAsync(q, b.pp_q, bytes, hipMemcpyDeviceToDevice, ctx->stream));
+    HIP_TRY(ctx, hipMemcpyAsync(z, b.pp_z, bytes, hipMemcpyDeviceToDevice, ctx->stream));
+    HIP_TRY(ctx, hipMemcpyAsync(t, b.pp_t, sizeof(double) * ctx->n_channels, hipMemcpyDeviceToDevice, ctx->stream));
+    return DSVE_OK;
+}
+
 // Capture steps 0..n-1 of a run on (h, q, z, t) into an executable graph.
-static dsve_status capture_steps(dsve_ctx *ctx, int n, int grid, double *h, double *q, double *z,
-                                 double *t, hipGraphExec_t *out)
+static dsve_status capture_steps(dsve_ctx *ctx, int n, bool from_copy, int grid, double *h, double *q,
+                                 double *z, double *t, hipGraphExec_t *out)
 {
     hipGraph_t graph = nullptr;
     HIP_TRY(ctx, hipStreamBeginCapture(ctx->cap_stream, hipStreamCaptureModeThreadLocal));
     for (int j = 0; j < n; ++j) {
-        hipError_t e = launch_step(step_args(ctx, ctx_bufs(ctx), j, h, q, z, t), ctx->precision, ctx->G,
-                                   ctx->cl, ctx->tile, grid, ctx->cap_stream);
+        hipError_t e = launch_step(step_args(ctx, ctx_bufs(ctx), j, from_copy, h, q, z, t), ctx->precision,
+                                   ctx->G, ctx->cl, ctx->tile, grid, ctx->cap_stream);
         if (e != hipSuccess) {
             (void)hipStreamEndCapture(ctx->cap_stream, &graph);
             if (graph) (void)hipGraphDestroy(graph);
@@ -792,8 +821,9 @@ static dsve_status ensure_graphs(dsve_ctx *ctx, double *h, double *q, double *z,
         std::copy(key, key + 4, ctx->g_key);
     }
     const int GS = ctx->graph_steps;
-    if (n_steps >= GS && !ctx->gexec) {
-        dsve_status st = capture_steps(ctx, GS, grid, h, q, z, t, &ctx->gexec);
+    const bool from_copy = starts_from_copy(ctx, n_steps);   // (GS is even: also that of the remainder)
+    if (n_steps >= GS && !ctx->gexec[from_copy]) {
+        dsve_status st = capture_steps(ctx, GS, from_copy, grid, h, q, z, t, &ctx->gexec[from_copy]);
         if (st != DSVE_OK) return st;
     }
     const int r = n_steps % GS;
@@ -802,7 +832,7 @@ static dsve_status ensure_graphs(dsve_ctx *ctx, double *h, double *q, double *z,
         if (slot.exec) (void)hipGraphExecDestroy(slot.exec);
         slot = dsve_ctx::RemGraph{};
         hipGraphExec_t ex = nullptr;
-        dsve_status st = capture_steps(ctx, r, grid, h, q, z, t, &ex);
+        dsve_status st = capture_steps(ctx, r, from_copy, grid, h, q, z, t, &ex);
         if (st != DSVE_OK) return st;
         slot.exec = ex;
         slot.steps = r;
@@ -863,14 +893,14 @@ static dsve_status run_steps(dsve_ctx *ctx, double *h, double *q, double *z, int
         st = ensure_graphs(ctx, h, q, z, t, n_steps);   // before any work of the run is enqueued
         if (st != DSVE_OK) return st;
     }
-    // slots: clear all three, CFL max of W^0 into sub-slot 0 of slot 0
-    HIP_TRY(ctx, launch_fill_u64(ctx->d_amax, 3 * ctx->amax_slot, 0ull, ctx->stream));
-    st = enqueue_cfl(ctx, h, q, z, ctx->d_amax);
+    const RunBufs b = ctx_bufs(ctx);
+    const bool from_copy = starts_from_copy(ctx, n_steps);
+    st = start_run(ctx, b, n_steps, h, q, z, t);
     if (st != DSVE_OK) return st;
     int done = 0, launches = 0;
     if (ctx->graph_steps > 0) {
         while (n_steps - done >= ctx->graph_steps) {
-            HIP_TRY(ctx, hipGraphLaunch(ctx->gexec, ctx->stream));
+            HIP_TRY(ctx, hipGraphLaunch(ctx->gexec[from_copy], ctx->stream));
             done += ctx->graph_steps;
             ++launches;
         }
@@ -883,21 +913,13 @@ static dsve_status run_steps(dsve_ctx *ctx, double *h, double *q, double *z, int
     const int graph_done = done;
     const int grid = grid_of(ctx);
     for (int j = done; j < n_steps; ++j)
-        HIP_TRY(ctx, launch_step(step_args(ctx, ctx_bufs(ctx), j, h, q, z, t), ctx->precision, ctx->G,
-                                 ctx->cl, ctx->tile, grid, ctx->stream));
+        HIP_TRY(ctx, launch_step(step_args(ctx, b, j, from_copy, h, q, z, t), ctx->precision, ctx->G, ctx->cl,
+                                 ctx->tile, grid, ctx->stream));
     ctx->last_graph_launches = launches;
     ctx->last_graph_steps = graph_done;
     ctx->last_direct = n_steps - graph_done;
-    if (n_steps % 2) {
-        const size_t bytes = sizeof(double) * ctx->n_cells;
-        HIP_TRY(ctx, hipMemcpyAsync(h, ctx->pp_h, bytes, hipMemcpyDeviceToDevice, ctx->stream));
-        HIP_TRY(ctx, hipMemcpyAsync(q, ctx->pp_q, bytes, hipMemcpyDeviceToDevice, ctx->stream));
-        HIP_TRY(ctx, hipMemcpyAsync(z, ctx->pp_z, bytes, hipMemcpyDeviceToDevice, ctx->stream));
-        HIP_TRY(ctx, hipMemcpyAsync(t, ctx->pp_t, sizeof(double) * ctx->n_channels,
-                                    hipMemcpyDeviceToDevice, ctx->stream));
-    }
     ctx->last_amax_slot = n_steps % 3;
-    return DSVE_OK;
+    return finish_run(ctx, b, n_steps, h, q, z, t);
 }
 
 dsve_status dsve_prepare_run(dsve_ctx *ctx, double *h, double *q, double *z, int n_steps,
@@ -976,21 +998,15 @@ dsve_status adot_step_noalloc(dsve_ctx *ctx, double *h, double *q, double *z, in
     if (ctx->packed ? (!ctx->d_tile_chan || ctx->table_tile != ctx->tile)
                     : (!ctx->d_segments || ctx->seg_tiles != segment_length(ctx, ctx->tile, ctx->blocks_per_cu)))
         return fail(ctx, DSVE_E_HIP, "adot_step_noalloc: no work table for the current launch");
-    HIP_TRY(ctx, launch_fill_u64(b.amax, 3 * ctx->amax_slot, 0ull, ctx->stream));
-    dsve_status st = enqueue_cfl(ctx, h, q, z, b.amax);
+    const bool from_copy = starts_from_copy(ctx, n_steps);
+    dsve_status st = start_run(ctx, b, n_steps, h, q, z, t_dev);
     if (st != DSVE_OK) return st;
     const int grid = grid_of(ctx);
     for (int j = 0; j < n_steps; ++j)
-        HIP_TRY(ctx, launch_step(step_args(ctx, b, j, h, q, z, t_dev), ctx->precision, ctx->G, ctx->cl,
+        HIP_TRY(ctx, launch_step(step_args(ctx, b, j, from_copy, h, q, z, t_dev), ctx->precision, ctx->G, ctx->cl,
                                  ctx->tile, grid, ctx->stream));
-    if (n_steps % 2) {
-        const size_t bytes = sizeof(double) * ctx->n_cells;
-        HIP_TRY(ctx, hipMemcpyAsync(h, b.pp_h, bytes, hipMemcpyDeviceToDevice, ctx->stream));
-        HIP_TRY(ctx, hipMemcpyAsync(q, b.pp_q, bytes, hipMemcpyDeviceToDevice, ctx->stream));
-        HIP_TRY(ctx, hipMemcpyAsync(z, b.pp_z, bytes, hipMemcpyDeviceToDevice, ctx->stream));
-        HIP_TRY(ctx, hipMemcpyAsync(t_dev, b.pp_t, sizeof(double) * ctx->n_channels,
-                                    hipMemcpyDeviceToDevice, ctx->stream));
-    }
+    st = finish_run(ctx, b, n_steps, h, q, z, t_dev);
+    if (st != DSVE_OK) return st;
     const int last = n_steps % 3;
     HIP_TRY(ctx, launch_copy_u64(ctx->d_amax + last * ctx->amax_slot, b.amax + last * ctx->amax_slot,
                                  ctx->amax_slot, ctx->stream));

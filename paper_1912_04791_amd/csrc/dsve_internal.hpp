@@ -250,6 +250,19 @@ struct CflArgs {
     double g;
 };
 
+constexpr int kCflOneThreads = 512;
+struct CflOneArgs {
+    const double *h, *q;
+    double *amax, *dt;           // results
+    unsigned long long *acc;     // [2] maximum and count of the workgroups, zero between calls
+    unsigned long long *slot;    // [kAmaxSplitMax] slot for the host's check, slot_stride apart
+    int64_t slot_stride;
+    unsigned int *flags;
+    int64_t n;
+    double g;
+    ChanInfo ci;
+};
+
 struct FluctArgs {
     const double *hL, *qL, *zL, *hR, *qR, *zR;
     double *Dm, *Dp;             // [3][n]
@@ -275,8 +288,10 @@ hipError_t launch_fluct(const FluctArgs &a, int precision, int G, int cl, hipStr
 hipError_t launch_cell_update(const double *Dm, const double *Dp, const double *dt,
                               const ChanInfo *ch, double g, int64_t N, double *h, double *q,
                               double *z, hipStream_t stream);
-hipError_t launch_dt(const unsigned long long *amax, const ChanInfo *ch, int32_t n_channels,
-                     double *dt, hipStream_t stream);
+// Start of a run over segments: CFL maxima of (h, q) into amax_next and, with `copy`, the state and the
+// clocks into (hn, qn, zn, t_next).
+hipError_t launch_start(const StepArgs &a, int precision, int cl, bool copy, hipStream_t stream);
+hipError_t launch_cfl_one(const CflOneArgs &a, int precision, int cl, hipStream_t stream);
 hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long v,
                            hipStream_t stream);
 hipError_t launch_fill_u32(unsigned int *p, int64_t n, unsigned int v, hipStream_t stream);

@@ -5,7 +5,8 @@
 //             the other ping-pong buffer, CFL speed of the new state reduced per channel (DPP lane
 //             moves -> LDS -> one global atomic max per workgroup into its CFL sub-slot).
 // k_step_packed  the same for many short channels: tiles over the flat edge space of all channels.
-// k_cfl       CFL maximum of a state (start of a run, and the cfl_reduce entry point).
+// k_start     CFL maximum of the state a run starts from (k_cfl: the same for many short channels).
+// k_cfl_one   CFL maximum and time step of one channel (cfl_reduce entry point).
 // k_fluct     pairwise fluctuations (dot_edge_fluct entry point).
 // k_update    cell update from given fluctuations (cell_update entry point).
 //
@@ -20,6 +21,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "dsve_device.hpp"
@@ -219,6 +221,31 @@ __global__ __launch_bounds__(kMaxTile, step_min_waves(PREC, CL)) void k_step_pac
 }
 
 // ---------------------------------------------------------------------------
+// Merges the lanes' maxima of a kernel of one segment per wave into the slots of their channels (-1: a
+// wave without a segment): within the wave, then the waves of the workgroup in the same channel in LDS.
+// Every thread of the workgroup calls it, once.
+__device__ __forceinline__ void merge_max(unsigned long long acc, int c, unsigned long long *amax)
+{
+    __shared__ unsigned long long s_max[kMaxTile / 64];
+    __shared__ int s_chan[kMaxTile / 64];
+    const int t = (int)threadIdx.x, waves = (int)(blockDim.x >> 6);
+    const unsigned long long m = wave_max_u64(acc);
+    if (waves == 1) {
+        if (t == 0 && c >= 0 && m != 0ull) flush_max(&amax[c], m);
+        return;
+    }
+    if ((t & 63) == 0) {
+        s_max[t >> 6] = m;
+        s_chan[t >> 6] = c;
+    }
+    __syncthreads();
+    if (t < waves && s_chan[t] >= 0 && (t == 0 || s_chan[t - 1] != s_chan[t])) {
+        unsigned long long v = s_max[t];
+        for (int w = t + 1; w < waves && s_chan[w] == s_chan[t]; ++w) v = s_max[w] > v ? s_max[w] : v;
+        if (v != 0ull) flush_max(&amax[s_chan[t]], v);
+    }
+}
+
 // Step kernel over segments: each wave takes one segment, a run of cells of one channel, in tiles of
 // 64 edges (63 cells: the first edge of a tile is the last of the tile before, computed by both).
 // Lane l computes edge e = t0 + l of the segment, the left face of cell e, and updates cell e - 1,
@@ -236,12 +263,8 @@ __global__ __launch_bounds__(kMaxTile, step_min_waves(PREC, CL)) void k_step(Ste
                                                                            const Segment *__restrict__ SEG,
                                                                            const unsigned long long *__restrict__ AM)
 {
-    __shared__ unsigned long long s_max[kMaxTile / 64];
-    __shared__ int s_chan[kMaxTile / 64];
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int waves = (int)(blockDim.x >> 6);
-    const int sidx = (int)blockIdx.x * waves + wave;
+    const int sidx = (int)blockIdx.x * (int)(blockDim.x >> 6) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     unsigned long long acc = 0ull;
     int c = -1;
     if (sidx < A.n_segments) {
@@ -330,25 +353,9 @@ __global__ __launch_bounds__(kMaxTile, step_min_waves(PREC, CL)) void k_step(Ste
         }
         raise_flag(A.flags, bad);
     }
-    // the wave's maximum; waves of one workgroup in the same channel merge theirs in LDS first
-    const unsigned long long m = wave_max_u64(acc);
     unsigned long long *const amax_mine =
         A.amax_next + (int64_t)(blockIdx.x & (unsigned)(A.amax_split - 1)) * A.amax_stride;
-    if (waves == 1) {
-        if (lane == 0 && m != 0ull) flush_max(&amax_mine[c], m);
-        return;
-    }
-    if (lane == 0) {
-        s_max[wave] = m;
-        s_chan[wave] = c;
-    }
-    __syncthreads();
-    const int t = (int)threadIdx.x;
-    if (t < waves && s_chan[t] >= 0 && (t == 0 || s_chan[t - 1] != s_chan[t])) {
-        unsigned long long v = s_max[t];
-        for (int w = t + 1; w < waves && s_chan[w] == s_chan[t]; ++w) v = s_max[w] > v ? s_max[w] : v;
-        if (v != 0ull) flush_max(&amax_mine[s_chan[t]], v);
-    }
+    merge_max(acc, c, amax_mine);
 }
 
 // ---------------------------------------------------------------------------
@@ -435,6 +442,118 @@ __global__ __launch_bounds__(kCflThreads) void k_cfl(CflArgs A)
     if (threadIdx.x == 0 && s_acc != 0ull) flush_max(&A.amax[home], s_acc);
 }
 
+// Speeds of cells base + [0, n) of a channel, kAhead cells per lane at a time so that their loads are in
+// flight together; each(i, h, q) sees every cell read.
+constexpr int kAhead = 4;
+template <int PREC, int CL, typename F>
+__device__ __forceinline__ unsigned long long speeds_of(const double *h, const double *q, int n, double g,
+                                                        const Closure &K, unsigned &bad, F each)
+{
+    const int lane = threadIdx.x & 63;
+    unsigned long long acc = 0ull;
+    for (int i0 = 0; i0 < n; i0 += 64 * kAhead) {
+        double hv[kAhead], qv[kAhead];
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) {
+            // lanes past the end read the last cell again
+            const int i = i0 + 64 * k + lane < n ? i0 + 64 * k + lane : n - 1;
+            hv[k] = ldx(h, i);
+            qv[k] = ldx(q, i);
+        }
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) {
+            if (i0 + 64 * k >= n) break;
+            each(i0 + 64 * k + lane < n ? i0 + 64 * k + lane : n - 1, hv[k], qv[k]);
+            const unsigned long long b =
+                (unsigned long long)__double_as_longlong(fabs(cell_speed<PREC, CL>(hv[k], qv[k], g, K, bad)));
+            acc = b > acc ? b : acc;
+        }
+    }
+    return acc;
+}
+
+// Start of a run over segments: the CFL maximum of the state per channel and, for a run of an odd number
+// of steps, which then ends in the caller's arrays, the copy of state and clocks that it starts from.
+//
+// Bound by HBM (16 B a cell, 48 with the copy).  Workgroups of 1024 threads over contiguous ranges, one
+// cell per lane in flight, took 895 us for 151 M cells (2.7 TB/s), and the copies after an odd run 53 us
+// for 4 M cells in four more launches.
+template <int PREC, int CL, bool COPY>
+__global__ __launch_bounds__(kMaxTile) void k_start(StepArgs A, const ChanInfo *__restrict__ CH,
+                                                    const Segment *__restrict__ SEG, int per_wave)
+{
+    const int lane = threadIdx.x & 63;
+    const int wave = (int)blockIdx.x * (kMaxTile / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    unsigned long long *const amax_mine =
+        A.amax_next + (int64_t)(blockIdx.x & (unsigned)(A.amax_split - 1)) * A.amax_stride;
+    unsigned long long acc = 0ull;
+    unsigned bad = 0u;
+    int c = -1;
+    int64_t k = (int64_t)wave * per_wave;
+    const int64_t k_end = k + per_wave < A.n_segments ? k + per_wave : A.n_segments;
+    while (k < k_end) {
+        // the wave's segments of one channel follow one another in memory: one run of cells
+        const Segment sg = SEG[k];
+        if (c >= 0) {
+            const unsigned long long m = wave_max_u64(acc);   // of the channel before
+            if (lane == 0 && m != 0ull) flush_max(&amax_mine[c], m);
+        }
+        c = sg.chan;
+        int64_t n = sg.n_flags >> 2;
+        for (++k; k < k_end && SEG[k].chan == c; ++k) n += SEG[k].n_flags >> 2;
+        const double *const z = A.z + sg.cell0;
+        double *const hn = A.hn + sg.cell0, *const qn = A.qn + sg.cell0, *const zn = A.zn + sg.cell0;
+        acc = speeds_of<PREC, CL>(A.h + sg.cell0, A.q + sg.cell0, (int)n, A.g, closure_of(CH[c]), bad,
+                                  [&](int i, double h, double q) {
+            if constexpr (COPY) {
+                stx(hn, i, h);
+                stx(qn, i, q);
+                stx(zn, i, ldx(z, i));
+            }
+        });
+        if (COPY && (sg.n_flags & 1u) && lane == 0) A.t_next[c] = A.t_cur[c];
+    }
+    raise_flag(A.flags, bad);
+    merge_max(acc, c, amax_mine);
+}
+
+// cfl_reduce of one channel in one launch: the workgroups' maxima meet in acc[0], and the last of them to
+// get there (acc[1] counts) writes the results, the slot that the host checks, and zeroes acc for the next
+// call.  Before, clearing, reduction, time step, clearing of the slot and its copy were five launches.
+template <int PREC, int CL>
+__global__ __launch_bounds__(kCflOneThreads) void k_cfl_one(CflOneArgs A)
+{
+    __shared__ unsigned long long s_w[kCflOneThreads / 64];
+    const int t = (int)threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    // even shares in whole rounds of the wave
+    const int64_t waves = (int64_t)gridDim.x * (kCflOneThreads / 64);
+    const int64_t per = ((A.n + waves - 1) / waves + 63) / 64 * 64;
+    const int64_t a = ((int64_t)blockIdx.x * (kCflOneThreads / 64) + wave) * per;
+    const int64_t left = A.n - a;
+    unsigned bad = 0u;
+    unsigned long long acc = 0ull;
+    if (left > 0)
+        acc = speeds_of<PREC, CL>(A.h + a, A.q + a, (int)(left < per ? left : per), A.g, closure_of(A.ci), bad,
+                                  [](int, double, double) {});
+    raise_flag(A.flags, bad);
+    const unsigned long long m = wave_max_u64(acc);
+    if ((t & 63) == 0) s_w[wave] = m;
+    __syncthreads();
+    if (t != 0) return;
+    unsigned long long v = s_w[0];
+    for (int w = 1; w < kCflOneThreads / 64; ++w) v = s_w[w] > v ? s_w[w] : v;
+    // both atomics return what they replaced, so each has been done when the next begins
+    const unsigned long long old = __hip_atomic_fetch_max(&A.acc[0], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("" ::"v"(old) : "memory");
+    if (__hip_atomic_fetch_add(&A.acc[1], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 != gridDim.x) return;
+    const unsigned long long top = __hip_atomic_exchange(&A.acc[0], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&A.acc[1], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const double amax = __longlong_as_double((long long)top);
+    *A.amax = amax;
+    *A.dt = A.ci.cfl_dx / amax;
+    for (int s = 0; s < kAmaxSplitMax; ++s) A.slot[s * A.slot_stride] = s ? 0ull : top;
+}
+
 template <int G, int PREC, int CL>
 __global__ __launch_bounds__(256) void k_fluct(FluctArgs A)
 {
@@ -469,12 +588,6 @@ __global__ __launch_bounds__(256) void k_update(const double *Dm, const double *
     h[i] = h0 - r * (Dm[i + 1] + Dp[i]);
     q[i] = qn;
     z[i] = z[i] - r * (Dm[2 * E + i + 1] + Dp[2 * E + i]);
-}
-
-__global__ void k_dt(const unsigned long long *amax, const ChanInfo *ch, int32_t C, double *dt)
-{
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c < C) dt[c] = ch[c].cfl_dx / __longlong_as_double((long long)amax[c]);
 }
 
 __global__ void k_fill_u64(unsigned long long *p, int64_t n, unsigned long long v)
@@ -642,11 +755,48 @@ hipError_t launch_cell_update(const double *Dm, const double *Dp, const double *
     return hipGetLastError();
 }
 
-hipError_t launch_dt(const unsigned long long *amax, const ChanInfo *ch, int32_t C, double *dt,
-                     hipStream_t stream)
+template <int PREC>
+static hipError_t launch_start_prec(const StepArgs &a, int cl, int per_wave, int grid, bool copy, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_dt, dim3(blocks_for(C, 256)), dim3(256), 0, stream, amax, ch, C, dt);
+#define DSVE_LAUNCH_START(CC)                                                                              \
+    if (copy) hipLaunchKernelGGL((k_start<PREC, CC, true>), dim3(grid), dim3(kMaxTile), 0, s, a, a.ch, a.segments, per_wave); \
+    else hipLaunchKernelGGL((k_start<PREC, CC, false>), dim3(grid), dim3(kMaxTile), 0, s, a, a.ch, a.segments, per_wave)
+    DSVE_DISPATCH_CL(cl, DSVE_LAUNCH_START)
+#undef DSVE_LAUNCH_START
     return hipGetLastError();
+}
+
+hipError_t launch_start(const StepArgs &a, int precision, int cl, bool copy, hipStream_t stream)
+{
+    // eight waves to a SIMD at once, each with an even share of the segments
+    const int per_wave = (a.n_segments + 8191) / 8192;
+    const int waves = (a.n_segments + per_wave - 1) / per_wave, grid = (waves + kMaxTile / 64 - 1) / (kMaxTile / 64);
+    if (precision == PREC_FP64) return launch_start_prec<PREC_FP64>(a, cl, per_wave, grid, copy, stream);
+    if (precision == PREC_MIXED) return launch_start_prec<PREC_MIXED>(a, cl, per_wave, grid, copy, stream);
+    if (precision == PREC_DOT) return launch_start_prec<PREC_DOT>(a, cl, per_wave, grid, copy, stream);
+    return hipErrorNotSupported;
+}
+
+template <int PREC>
+static hipError_t launch_cfl_one_prec(const CflOneArgs &a, int cl, int grid, hipStream_t stream)
+{
+#define DSVE_LAUNCH_CFL(CC) hipLaunchKernelGGL((k_cfl_one<PREC, CC>), dim3(grid), dim3(kCflOneThreads), 0, stream, a)
+    DSVE_DISPATCH_CL(cl, DSVE_LAUNCH_CFL)
+#undef DSVE_LAUNCH_CFL
+    return hipGetLastError();
+}
+
+hipError_t launch_cfl_one(const CflOneArgs &a, int precision, int cl, hipStream_t stream)
+{
+    if (a.n < 1) return hipErrorInvalidValue;
+    // one round of kAhead cells per lane in a workgroup while the chip is not full (two workgroups to a
+    // compute unit), then longer shares, whose lengths fit 32 bits to 10^12 cells
+    const int64_t round = (int64_t)kCflOneThreads * kAhead;
+    const int grid = (int)std::min<int64_t>((a.n + round - 1) / round, 512);
+    if (precision == PREC_FP64) return launch_cfl_one_prec<PREC_FP64>(a, cl, grid, stream);
+    if (precision == PREC_MIXED) return launch_cfl_one_prec<PREC_MIXED>(a, cl, grid, stream);
+    if (precision == PREC_DOT) return launch_cfl_one_prec<PREC_DOT>(a, cl, grid, stream);
+    return hipErrorNotSupported;
 }
 
 hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long v, hipStream_t s)
