@@ -74,16 +74,16 @@ __device__ __forceinline__ void reduce_channel_max(unsigned long long v, int cha
     }
 }
 
-// Atomic maximum of a workgroup's partial result into a per-channel slot, skipped when the slot
-// already holds at least the value.  Slot values only grow while a kernel runs, so a load that
-// returns an older (smaller) value only costs an atomic that was not needed; the load bypasses
-// the compute unit's cache.  Most workgroups do not hold their channel's maximum, so most
-// flushes skip the atomic, which would otherwise serialise on the one address at the end of
-// the kernel.
-__device__ __forceinline__ void flush_max(unsigned long long *slot, unsigned long long v)
+// Atomic maximum of a workgroup's partial result into a per-channel slot, with `check` skipped when the
+// slot already holds at least the value.  Slot values only grow while a kernel runs, so a load that
+// returns an older (smaller) value only costs an atomic that was not needed; the load bypasses the
+// compute unit's cache.  Most workgroups do not hold their channel's maximum, so most skip the atomic,
+// which would otherwise serialise on the one address where many workgroups end together; but the
+// workgroup waits for the load, and for the atomic alone it does not.
+__device__ __forceinline__ void flush_max(unsigned long long *slot, unsigned long long v, bool check = true)
 {
-    const unsigned long long cur = __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (v > cur) atomicMax(slot, v);
+    if (check && v <= __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
+    (void)__hip_atomic_fetch_max(slot, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // CFL maximum of channel c: the largest of its S sub-slots, as a double.  The floating-point

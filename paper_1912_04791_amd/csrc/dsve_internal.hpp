@@ -10,8 +10,8 @@
 //   tile_chan  int32 per tile: channel of the tile's first edge
 //   amax       uint64 [3][4][Cs]: bit patterns of the per-channel CFL maximum, rotated
 //              through three slots (read n%3, atomic-max (n+1)%3, clear (n+2)%3); each slot
-//              holds up to 4 sub-slots per channel, Cs = C rounded up to 512 entries (4 KiB)
-//              apart, and the channel's maximum is the maximum over its sub-slots.  With S
+//              holds up to 4 sub-slots per channel (entries 2^amax_shift apart), Cs = their
+//              number rounded up to 512 entries (4 KiB) apart, and the channel's maximum is the maximum over its sub-slots.  With S
 //              sub-slots in use a workgroup merges its partial maximum into sub-slot
 //              (workgroup index mod S), so the atomics of one step spread over S addresses
 //              instead of queueing on one (S = 1, 2 or 4, a launch parameter).
@@ -145,7 +145,15 @@ template <> struct Gauss<5> {
 };
 
 constexpr int kAmaxSplitMax = 4;   // CFL sub-slots per channel allocated in each slot
-inline int64_t amax_stride(int64_t n_channels) { return (n_channels + 511) / 512 * 512; }
+// Entries of a slot lie 2^amax_shift apart: with few channels each has a cache line of its own (128 B),
+// or as near to that as 4096 entries allow.
+inline int amax_shift(int64_t n_channels)
+{
+    int s = 0;
+    while (s < 4 && (n_channels << (s + 1)) <= 4096) ++s;
+    return s;
+}
+inline int64_t amax_stride(int64_t entries) { return (entries + 511) / 512 * 512; }
 
 constexpr int kSegTile = 63;     // cells per tile of the step kernel (64 edges, one shared)
 
@@ -170,6 +178,8 @@ struct StepArgs {
     unsigned long long *amax_clear;      // [S][Cs] slot to clear for step n+1
     int64_t amax_stride;                 // Cs
     int32_t amax_split;                  // S: sub-slots in use (1, 2 or 4)
+    int32_t amax_shift;                  // a channel's entry is at (channel << amax_shift)
+    int32_t amax_check;                  // look at a slot before the atomic (see flush_max)
     const double *t_cur;         // [C] clocks at the start of the step
     double *t_next;              // [C] clocks after it
     unsigned int *flags;
@@ -192,10 +202,11 @@ struct ResidentArgs {
     double *t;                   // [C] clocks
     const ChanInfo *ch;
     const int64_t *off;          // [C+1] cell offsets
-    unsigned long long *amax;    // [C] CFL maximum of the final state (bit patterns)
+    unsigned long long *amax;    // CFL maximum of the final state (bit patterns), at (channel << amax_shift)
     unsigned int *flags;
     int32_t n_channels;
     int32_t n_steps;
+    int32_t amax_shift;
     double g;
 };
 
@@ -228,10 +239,11 @@ struct PartArgs {
     const ChanInfo *ch;
     const Part *parts;           // [grid]
     unsigned long long *box;     // mailboxes, zero at the start of the run
-    unsigned long long *amax;    // [C] CFL maximum of the final state (bit patterns), zero at the start
+    unsigned long long *amax;    // as ResidentArgs, zero at the start
     unsigned int *flags;
     int32_t n_parts;             // P
     int32_t n_steps;
+    int32_t amax_shift;
     double g;
 };
 constexpr int kPartThreads = 512;   // per workgroup

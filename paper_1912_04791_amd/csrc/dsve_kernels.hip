@@ -224,14 +224,14 @@ __global__ __launch_bounds__(kMaxTile, step_min_waves(PREC, CL)) void k_step_pac
 // Merges the lanes' maxima of a kernel of one segment per wave into the slots of their channels (-1: a
 // wave without a segment): within the wave, then the waves of the workgroup in the same channel in LDS.
 // Every thread of the workgroup calls it, once.
-__device__ __forceinline__ void merge_max(unsigned long long acc, int c, unsigned long long *amax)
+__device__ __forceinline__ void merge_max(unsigned long long acc, int c, unsigned long long *amax, int shift, bool check)
 {
     __shared__ unsigned long long s_max[kMaxTile / 64];
     __shared__ int s_chan[kMaxTile / 64];
     const int t = (int)threadIdx.x, waves = (int)(blockDim.x >> 6);
     const unsigned long long m = wave_max_u64(acc);
     if (waves == 1) {
-        if (t == 0 && c >= 0 && m != 0ull) flush_max(&amax[c], m);
+        if (t == 0 && c >= 0 && m != 0ull) flush_max(&amax[c << shift], m, check);
         return;
     }
     if ((t & 63) == 0) {
@@ -242,7 +242,7 @@ __device__ __forceinline__ void merge_max(unsigned long long acc, int c, unsigne
     if (t < waves && s_chan[t] >= 0 && (t == 0 || s_chan[t - 1] != s_chan[t])) {
         unsigned long long v = s_max[t];
         for (int w = t + 1; w < waves && s_chan[w] == s_chan[t]; ++w) v = s_max[w] > v ? s_max[w] : v;
-        if (v != 0ull) flush_max(&amax[s_chan[t]], v);
+        if (v != 0ull) flush_max(&amax[s_chan[t] << shift], v, check);
     }
 }
 
@@ -275,7 +275,7 @@ __global__ __launch_bounds__(kMaxTile, step_min_waves(PREC, CL)) void k_step(Ste
         const ChanInfo &ci = CH[c];
         const Closure K = closure_of(ci);
         const double fric = ci.fric;
-        const double dt = ci.cfl_dx * rcp_h(amax_of(AM, c, A.amax_stride, A.amax_split));
+        const double dt = ci.cfl_dx * rcp_h(amax_of(AM, c << A.amax_shift, A.amax_stride, A.amax_split));
         const double r = dt * ci.inv_dx;
         // cell i of the segment is at index i + 1 from these bases (cell -1, the left neighbour of
         // a segment inside a channel, at 0; a segment at its channel's start does not read it)
@@ -346,16 +346,17 @@ __global__ __launch_bounds__(kMaxTile, step_min_waves(PREC, CL)) void k_step(Ste
         }
         if (first && lane == 0) {
             A.t_next[c] = A.t_cur[c] + dt;
-            A.amax_clear[c] = 0ull;
+            const int at = c << A.amax_shift;
+            A.amax_clear[at] = 0ull;
 #pragma unroll
             for (int s = 1; s < kAmaxSplitMax; ++s)
-                if (s < A.amax_split) A.amax_clear[c + s * A.amax_stride] = 0ull;
+                if (s < A.amax_split) A.amax_clear[at + s * A.amax_stride] = 0ull;
         }
         raise_flag(A.flags, bad);
     }
     unsigned long long *const amax_mine =
         A.amax_next + (int64_t)(blockIdx.x & (unsigned)(A.amax_split - 1)) * A.amax_stride;
-    merge_max(acc, c, amax_mine);
+    merge_max(acc, c, amax_mine, A.amax_shift, A.amax_check != 0);
 }
 
 // ---------------------------------------------------------------------------
@@ -496,7 +497,7 @@ __global__ __launch_bounds__(kMaxTile) void k_start(StepArgs A, const ChanInfo *
         const Segment sg = SEG[k];
         if (c >= 0) {
             const unsigned long long m = wave_max_u64(acc);   // of the channel before
-            if (lane == 0 && m != 0ull) flush_max(&amax_mine[c], m);
+            if (lane == 0 && m != 0ull) flush_max(&amax_mine[c << A.amax_shift], m);
         }
         c = sg.chan;
         int64_t n = sg.n_flags >> 2;
@@ -514,7 +515,7 @@ __global__ __launch_bounds__(kMaxTile) void k_start(StepArgs A, const ChanInfo *
         if (COPY && (sg.n_flags & 1u) && lane == 0) A.t_next[c] = A.t_cur[c];
     }
     raise_flag(A.flags, bad);
-    merge_max(acc, c, amax_mine);
+    merge_max(acc, c, amax_mine, A.amax_shift, true);
 }
 
 // cfl_reduce of one channel in one launch: the workgroups' maxima meet in acc[0], and the last of them to

@@ -108,7 +108,7 @@ void k_resident(ResidentArgs A)
         const unsigned long long amax_bits = block_max_u64(sp, s_w);
         if (t == 0) {
             A.t[c] = tc;
-            A.amax[c] = amax_bits;
+            A.amax[c << A.amax_shift] = amax_bits;
         }
         __syncthreads();   // the next channel reuses the LDS
     }
@@ -495,7 +495,7 @@ void k_parts(PartArgs A)
     // the maximum of the final state, for the host's check of the run
     if (role == G) {
         const unsigned long long m = wave_max_u64(sp);
-        if (lane == 0 && m != 0ull) atomicMax(&A.amax[P.chan], m);
+        if (lane == 0 && m != 0ull) atomicMax(&A.amax[P.chan << A.amax_shift], m);
     }
     if (P.index == 0 && threadIdx.x == 64 * NW * G) A.t[P.chan] = tc;
     raise_flag(A.flags, bad);
