@@ -137,38 +137,39 @@ __device__ __forceinline__ T ipow15(T a, int n)
     r = (n & 4) ? r * a4 : r;
     return (n & 8) ? r * a8 : r;
 }
-// a^1.1 = a^2 y^9 with y = a^(-1/10), a > 0: y from an FP32 estimate 2^(-log2(a)/10) and two
-// Newton steps for y^-10 = a in FP64, y <- y (11 - a y^10) / 10 (each takes a relative error e
-// to about 5.5 e^2: 4e-7 -> 1e-12 -> the rounding of y^9, a few ulp); no division
+// a^1.1 = a^2 y^9 with y = a^(-1/10), a > 0: y from an FP32 estimate 2^(-log2(a)/10) and one step of
+// the third-order iteration for y^-10 = a in FP64, y <- y (1 + e/10 + 11e^2/200), e = 1 - a y^10 (a
+// relative error d of y is an e of 10 d: 4e-7 -> 77/2000 e^3, below 1e-17); no division
 __device__ __forceinline__ double pow_1p1(double a);
 __device__ __forceinline__ float pow_1p1(float a) { return m_pow(a, 1.1f); }
-// a^(-1/3), a > 0: FP32 estimate 2^(-log2(a)/3) from the hardware base-2 logarithm and
-// exponential, then two Newton steps for y^-3 = a, y <- y (4 - a y^3) / 3, in FP64 (each takes a
-// relative error e to about 2 e^2: 1e-6 -> 2e-12 -> the rounding of the last step); no division
+// a^(-1/3), a > 0: FP32 estimate 2^(-log2(a)/3) from the hardware base-2 logarithm and exponential
+// (relative error about 1e-6), then one step of the third-order iteration for y^-3 = a in FP64,
+// y <- y (1 + e/3 + 2e^2/9), e = 1 - a y^3, the Taylor terms of (1 - e)^(-1/3): it leaves 14/81 e^3,
+// below 1e-17; no division.  (Two Newton steps, each to about 2 e^2, took ten FP64 instructions, this
+// takes six.)
 __device__ __forceinline__ double rcbrt_h(double a)
 {
-    double y = (double)__builtin_amdgcn_exp2f(-(1.0f / 3.0f) * __builtin_amdgcn_logf((float)a));
-#pragma unroll
-    for (int it = 0; it < 2; ++it) y = (y * (1.0 / 3.0)) * fma(-a, y * y * y, 4.0);
-    return y;
+    const double y = (double)__builtin_amdgcn_exp2f(-(1.0f / 3.0f) * __builtin_amdgcn_logf((float)a));
+    const double e = fma(-a, y * y * y, 1.0);
+    return fma(y * e, fma(e, 2.0 / 9.0, 1.0 / 3.0), y);
 }
 __device__ __forceinline__ double m_rcbrt(double a) { return rcbrt_h(a); }
 __device__ __forceinline__ float m_rcbrt(float a)
 {
     return __builtin_amdgcn_exp2f(-(1.0f / 3.0f) * __builtin_amdgcn_logf(a));
 }
-__device__ __forceinline__ double m_sqrt(double a) { return sqrt(a); }
+// sqrt(a), a > 0, as a times its refined reciprocal square root (within about 1 ulp; the library's
+// correctly rounded one handles zeros and infinities too and takes more than twice the instructions)
+__device__ __forceinline__ double m_sqrt(double a) { return a * rsqrt_h(a); }
 __device__ __forceinline__ float m_sqrt(float a) { return sqrtf(a); }
 __device__ __forceinline__ double m_abs(double a) { return fabs(a); }
 __device__ __forceinline__ float m_abs(float a) { return fabsf(a); }
 __device__ __forceinline__ double pow_1p1(double a)
 {
     double y = (double)__builtin_amdgcn_exp2f(-0.1f * __builtin_amdgcn_logf((float)fmax(a, 1e-30)));
-#pragma unroll
-    for (int it = 0; it < 2; ++it) {
-        const double y2 = y * y, y5 = y2 * y2 * y;
-        y = (y * 0.1) * fma(-a, y5 * y5, 11.0);
-    }
+    const double s2 = y * y, s5 = s2 * s2 * y;
+    const double e = fma(-a, s5 * s5, 1.0);
+    y = fma(y * e, fma(e, 0.055, 0.1), y);
     const double y2 = y * y, y4 = y2 * y2;
     return (a * a) * (y4 * y4 * y);
 }
