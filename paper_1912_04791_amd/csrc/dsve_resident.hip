@@ -28,8 +28,12 @@ __device__ __forceinline__ unsigned long long block_max_u64(unsigned long long v
 // Two barriers per step: the first publishes the state, the second the D^- and the waves' CFL maxima
 // of that same state, whose speeds are taken beside the fluctuations that need no time step; only the
 // update waits for both.
+//
+// Compiled for 4 waves per SIMD where k_step runs 3 or more: with many channels the barriers leave
+// waves waiting, and the fourth makes up for the 36 bytes the FP64 Grass form then spills (2048
+// channels of 100-255 cells 8.1 -> 7.4 us a step, 3000 of 150-400 27 -> 20 us).
 template <int G, int PREC, int CL, int NT>
-__global__ __launch_bounds__(NT, step_min_waves(PREC, CL) < 3 ? step_min_waves(PREC, CL) : 3)
+__global__ __launch_bounds__(NT, step_min_waves(PREC, CL) < 3 ? step_min_waves(PREC, CL) : 4)
 void k_resident(ResidentArgs A)
 {
     __shared__ double s_st[3][NT];        // h, q, z of the cells
