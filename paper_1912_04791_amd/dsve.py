@@ -146,7 +146,6 @@ def _ptr(t, numel: int | None = None, at_least: int | None = None, device: int |
     """Device pointer of a contiguous float64 CUDA tensor, after checking its element count
     (exactly ``numel``, or at least ``at_least``) and its device: the library takes raw
     pointers and trusts the sizes it was given."""
-    import torch
     if not isinstance(t, torch.Tensor):
         raise TypeError("expected a torch.Tensor")
     if not t.is_cuda or t.dtype != torch.float64 or not t.is_contiguous():
@@ -158,6 +157,14 @@ def _ptr(t, numel: int | None = None, at_least: int | None = None, device: int |
     if device is not None and t.device.index != device:
         raise ValueError(f"tensor on cuda:{t.device.index}, context on cuda:{device}")
     return t.data_ptr()
+
+
+def _ptrs(ts, numel: int, device: int, _T=torch.Tensor, _f64=torch.float64):
+    """``_ptr`` of tensors of ``numel`` elements each, the same checks without a call per tensor
+    (a caller's own time loop is bound by the time these calls take on the host)."""
+    return [t.data_ptr() if isinstance(t, _T) and t.is_cuda and t.dtype is _f64 and t.numel() == numel
+            and t.get_device() == device and t.is_contiguous() else _ptr(t, numel, device=device)
+            for t in ts]
 
 
 def _stream_handle(stream) -> int:
@@ -236,8 +243,7 @@ class Context:
         self.device = torch.cuda.current_device()   # the device the library bound it to
 
     def _state(self, h, q, z):
-        n, d = self.n_cells, self.device
-        return _ptr(h, n, device=d), _ptr(q, n, device=d), _ptr(z, n, device=d)
+        return _ptrs((h, q, z), self.n_cells, self.device)
 
     # -- construction -----------------------------------------------------
     @classmethod
@@ -306,16 +312,14 @@ class Context:
     def dot_edge_fluct(self, hL, qL, zL, hR, qR, zR, Dm, Dp):
         """n edges: six states of n elements each; Dm, Dp hold [3][n]."""
         n, d = hL.numel(), self.device
-        ins = [_ptr(x, n, device=d) for x in (hL, qL, zL, hR, qR, zR)]
-        self._check(lib.dot_edge_fluct(self._h, *ins, n, _ptr(Dm, 3 * n, device=d),
-                                       _ptr(Dp, 3 * n, device=d)), "dot_edge_fluct")
+        ins = _ptrs((hL, qL, zL, hR, qR, zR), n, d)
+        self._check(lib.dot_edge_fluct(self._h, *ins, n, *_ptrs((Dm, Dp), 3 * n, d)), "dot_edge_fluct")
 
     def cell_update(self, Dm, Dp, dt, h, q, z):
         """Dm, Dp hold [3][N+1] edge fluctuations of an N-cell channel; dt one value."""
         e, d = 3 * (self.n_cells + 1), self.device
-        self._check(lib.cell_update(self._h, _ptr(Dm, e, device=d), _ptr(Dp, e, device=d),
-                                    _ptr(dt, at_least=1, device=d), *self._state(h, q, z)),
-                    "cell_update")
+        self._check(lib.cell_update(self._h, *_ptrs((Dm, Dp), e, d), _ptr(dt, at_least=1, device=d),
+                                    *_ptrs((h, q, z), self.n_cells, d)), "cell_update")
 
     def cfl_reduce(self, h, q, z, amax, dt):
         d = self.device
