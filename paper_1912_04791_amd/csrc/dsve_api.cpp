@@ -8,7 +8,7 @@
 // run then starts from -> n / graph_steps replays of the main graph (each node is one step kernel; slot
 // and ping-pong phase repeat every 6 steps, so graph_steps is a multiple of 6) -> one replay of the graph
 // of the remaining n % graph_steps steps.  With graph_steps = 0 every step is launched directly.  When
-// every channel has at most kResidentCells cells, or there are few channels (build_parts), the run is one
+// every channel has at most kResidentCells cells, or there are few channels (plan_parts), the run is one
 // launch instead.
 #include <hip/hip_runtime.h>
 
@@ -46,12 +46,13 @@ struct dsve_ctx {
     int64_t n_channels = 0, n_cells = 0, n_edges = 0;
     std::vector<ChanInfo> h_ch;
     std::vector<int64_t> h_off, h_eoff;
+    char *d_tables = nullptr;            // one buffer: d_ch, d_off, d_eoff, d_parts
     ChanInfo *d_ch = nullptr;
     int64_t *d_off = nullptr, *d_eoff = nullptr;
 
-    double *pp_h = nullptr, *pp_q = nullptr, *pp_z = nullptr;   // ping-pong copy
-    double *pp_t = nullptr;                                      // ping-pong clocks [C]
-    unsigned long long *d_amax = nullptr;                        // [3][S][Cs], then the mailboxes of the parts
+    double *pp_h = nullptr, *pp_q = nullptr, *pp_z = nullptr;   // ping-pong copy (one buffer)
+    double *pp_t = nullptr;                                      // ping-pong clocks [C], its end
+    unsigned long long *d_amax = nullptr;                        // [3][S][Cs], the mailboxes, d_acc, d_flags
     int64_t amax_cs = 0;                                         // Cs (sub-slot stride)
     int amax_sh = 0;                                             // entries 2^amax_sh apart (0: packed kernel)
     int64_t amax_slot = 0;                                       // kAmaxSplitMax * Cs (one slot)
@@ -59,7 +60,7 @@ struct dsve_ctx {
     bool resident_ok = false;    // every channel has at most kResidentCells cells
     int resident_threads = 256;  // workgroup size of resident runs: 256, or 512 past 255 cells
     int resident_mode = 0;       // 0: channel-resident runs when resident_ok; 1: never
-    // few channels: the run in one launch of k_parts (see build_parts)
+    // few channels: the run in one launch of k_parts (see plan_parts)
     Part *d_parts = nullptr;
     int64_t n_parts = 0;         // 0: the context does not run that way
     int parts_grid = 0;
@@ -83,6 +84,7 @@ struct dsve_ctx {
     int rem_next = 0;
     bool g_keyed = false;
     const void *g_key[4] = {nullptr, nullptr, nullptr, nullptr};
+    const void *last_key[4] = {nullptr, nullptr, nullptr, nullptr};   // arrays of the last run
     int g_steps = 0, g_tile = 0, g_grid = 0, g_split = 0;
     // the last run: graph replays, the steps they ran, steps launched directly
     int last_graph_launches = 0, last_graph_steps = 0, last_direct = 0;
@@ -278,7 +280,7 @@ static dsve_status build_table(dsve_ctx *c, int tile, int blocks_per_cu)
 // Past kMaxParts (about 7000 cells) the per-step kernels take over, on a stream restricted to some of
 // the compute units too.  Channels of 127 to 255 cells stay with one workgroup of k_resident, as fast
 // as three parts (250 cells: 1.79 against 1.89 us a step), except with the numerical eigensolver.
-static dsve_status build_parts(dsve_ctx *c)
+static dsve_status plan_parts(dsve_ctx *c, std::vector<Part> &table)
 {
     int64_t longest = 0;
     for (int64_t k = 0; k < c->n_channels; ++k) longest = std::max<int64_t>(longest, c->h_off[k + 1] - c->h_off[k]);
@@ -335,12 +337,10 @@ static dsve_status build_parts(dsve_ctx *c)
     }
     size_t rows = 0;
     for (const auto &l : lists) rows = std::max(rows, l.size());
-    std::vector<Part> table(8 * rows);   // blocks without work end at once
+    table.resize(8 * rows);   // blocks without work end at once
     for (size_t r = 0; r < rows; ++r)
         for (size_t j = 0; j < 8; ++j)
             if (r < lists[j].size()) table[8 * r + j] = lists[j][r];
-    HIP_TRY(c, hipMalloc(&c->d_parts, sizeof(Part) * table.size()));
-    HIP_TRY(c, hipMemcpy(c->d_parts, table.data(), sizeof(Part) * table.size(), hipMemcpyHostToDevice));
     c->n_parts = id;
     c->parts_grid = (int)table.size();
     return DSVE_OK;
@@ -373,18 +373,11 @@ static dsve_status setup(dsve_ctx *c, void *stream)
     for (int64_t k = 0; k < C; ++k) longest = std::max<int64_t>(longest, c->h_off[k + 1] - c->h_off[k]);
     c->resident_ok = longest <= kResidentCells;
     c->resident_threads = longest <= kResidentSmall ? 256 : 512;
-    HIP_TRY(c, hipMalloc(&c->d_ch, sizeof(ChanInfo) * C));
-    HIP_TRY(c, hipMalloc(&c->d_off, sizeof(int64_t) * (C + 1)));
-    HIP_TRY(c, hipMalloc(&c->d_eoff, sizeof(int64_t) * (C + 1)));
-    HIP_TRY(c, hipMemcpy(c->d_ch, c->h_ch.data(), sizeof(ChanInfo) * C, hipMemcpyHostToDevice));
-    HIP_TRY(c, hipMemcpy(c->d_off, c->h_off.data(), sizeof(int64_t) * (C + 1), hipMemcpyHostToDevice));
-    HIP_TRY(c, hipMemcpy(c->d_eoff, c->h_eoff.data(), sizeof(int64_t) * (C + 1), hipMemcpyHostToDevice));
-    HIP_TRY(c, hipMalloc(&c->pp_h, sizeof(double) * c->n_cells));
-    HIP_TRY(c, hipMalloc(&c->pp_q, sizeof(double) * c->n_cells));
-    HIP_TRY(c, hipMalloc(&c->pp_z, sizeof(double) * c->n_cells));
-    HIP_TRY(c, hipMalloc(&c->pp_t, sizeof(double) * C));
     if (amax_split_of_kernels() != kAmaxSplitMax)
         return fail(c, DSVE_E_HIP, "kernels built with another CFL sub-slot count than the host code");
+    std::vector<Part> parts;
+    dsve_status st = plan_parts(c, parts);
+    if (st != DSVE_OK) return st;
     // a wave of the segment kernel works on one channel: where that leaves more than a fifth of the
     // lanes without an edge (most channels shorter than about 250 cells), the packed kernel, whose
     // tiles hold several channels, runs instead
@@ -393,14 +386,36 @@ static dsve_status setup(dsve_ctx *c, void *stream)
     c->amax_sh = c->packed ? 0 : amax_shift(C);
     c->amax_cs = amax_stride(C << c->amax_sh);
     c->amax_slot = (int64_t)kAmaxSplitMax * c->amax_cs;
-    dsve_status st = build_parts(c);
-    if (st != DSVE_OK) return st;
-    HIP_TRY(c, hipMalloc(&c->d_amax, sizeof(unsigned long long) * (3 * c->amax_slot + part_box_words(c->n_parts))));
-    HIP_TRY(c, hipMalloc(&c->d_flags, sizeof(unsigned int) * 4));
-    HIP_TRY(c, hipMalloc(&c->d_acc, sizeof(unsigned long long) * 2));
-    HIP_TRY(c, launch_fill_u64(c->d_acc, 2, 0ull, c->stream));
-    HIP_TRY(c, launch_fill_u64(c->d_amax, 3 * c->amax_slot, 0ull, c->stream));
-    HIP_TRY(c, launch_fill_u32(c->d_flags, 4, 0u, c->stream));
+
+    // the tables in one buffer and one upload (each starts at a multiple of 256 bytes)
+    auto up = [](size_t v) { return (v + 255) / 256 * 256; };
+    const size_t n_ch = sizeof(ChanInfo) * C, n_off = sizeof(int64_t) * (C + 1), n_parts = sizeof(Part) * parts.size();
+    const size_t o_off = up(n_ch), o_eoff = o_off + up(n_off), o_parts = o_eoff + up(n_off);
+    std::vector<char> blob(o_parts + n_parts);
+    std::memcpy(blob.data(), c->h_ch.data(), n_ch);
+    std::memcpy(blob.data() + o_off, c->h_off.data(), n_off);
+    std::memcpy(blob.data() + o_eoff, c->h_eoff.data(), n_off);
+    if (n_parts) std::memcpy(blob.data() + o_parts, parts.data(), n_parts);
+    HIP_TRY(c, hipMalloc(&c->d_tables, blob.size()));
+    HIP_TRY(c, hipMemcpy(c->d_tables, blob.data(), blob.size(), hipMemcpyHostToDevice));
+    c->d_ch = reinterpret_cast<ChanInfo *>(c->d_tables);
+    c->d_off = reinterpret_cast<int64_t *>(c->d_tables + o_off);
+    c->d_eoff = reinterpret_cast<int64_t *>(c->d_tables + o_eoff);
+    c->d_parts = reinterpret_cast<Part *>(c->d_tables + o_parts);
+
+    // the ping-pong copy
+    const int64_t N = (c->n_cells + 31) / 32 * 32;
+    HIP_TRY(c, hipMalloc(&c->pp_h, sizeof(double) * (3 * N + C)));
+    c->pp_q = c->pp_h + N;
+    c->pp_z = c->pp_q + N;
+    c->pp_t = c->pp_z + N;
+
+    // what starts as zeros: CFL slots, mailboxes, the words of cfl_reduce, error flags
+    const int64_t words = 3 * c->amax_slot + part_box_words(c->n_parts);
+    HIP_TRY(c, hipMalloc(&c->d_amax, sizeof(unsigned long long) * (words + 4)));
+    c->d_acc = c->d_amax + words;
+    c->d_flags = reinterpret_cast<unsigned int *>(c->d_acc + 2);
+    HIP_TRY(c, launch_fill_u64(c->d_amax, words + 4, 0ull, c->stream));
     // the device address of the static scratch of adot_step_noalloc, looked up once per device
     // (a failure leaves it null: that entry point then reports it, the others do not use it)
     if (noalloc_scratch(c->device, &c->scratch) != hipSuccess) c->scratch = nullptr;
@@ -416,19 +431,11 @@ static void release(dsve_ctx *c)
     if (c->stream) (void)hipStreamSynchronize(c->stream);
     else (void)hipDeviceSynchronize();
     free_graph(c);
-    (void)hipFree(c->d_ch);
-    (void)hipFree(c->d_off);
-    (void)hipFree(c->d_eoff);
+    (void)hipFree(c->d_tables);
     (void)hipFree(c->pp_h);
-    (void)hipFree(c->pp_q);
-    (void)hipFree(c->pp_z);
-    (void)hipFree(c->pp_t);
     (void)hipFree(c->d_amax);
-    (void)hipFree(c->d_flags);
-    (void)hipFree(c->d_acc);
     (void)hipFree(c->d_tile_chan);
     (void)hipFree(c->d_segments);
-    (void)hipFree(c->d_parts);
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
     delete c;
 }
@@ -904,8 +911,17 @@ static dsve_status run_steps(dsve_ctx *ctx, double *h, double *q, double *z, int
     }
     dsve_status st = build_table(ctx, ctx->tile, ctx->blocks_per_cu);
     if (st != DSVE_OK) return st;
-    if (ctx->graph_steps > 0) {
-        st = ensure_graphs(ctx, h, q, z, t, n_steps);   // before any work of the run is enqueued
+    // Steps replay graphs, captured before any work of the run is enqueued, but for the first run on
+    // arrays that no graph was captured for, unless a launch was asked for: launching its steps one by
+    // one takes as long on the device (20 000 cells, 60 steps: 320 us against 312), and capturing them
+    // longer than running them (2^20 cells, 20 steps: 0.32 ms on top of 0.42).
+    const void *const key[4] = {h, q, z, t};
+    const bool known = ctx->launch_set || std::equal(key, key + 4, ctx->last_key) ||
+                       (ctx->g_keyed && std::equal(key, key + 4, ctx->g_key));
+    std::copy(key, key + 4, ctx->last_key);
+    const bool replay = ctx->graph_steps > 0 && known;
+    if (replay) {
+        st = ensure_graphs(ctx, h, q, z, t, n_steps);
         if (st != DSVE_OK) return st;
     }
     const RunBufs b = ctx_bufs(ctx);
@@ -913,7 +929,7 @@ static dsve_status run_steps(dsve_ctx *ctx, double *h, double *q, double *z, int
     st = start_run(ctx, b, n_steps, h, q, z, t);
     if (st != DSVE_OK) return st;
     int done = 0, launches = 0;
-    if (ctx->graph_steps > 0) {
+    if (replay) {
         while (n_steps - done >= ctx->graph_steps) {
             HIP_TRY(ctx, hipGraphLaunch(ctx->gexec[from_copy], ctx->stream));
             done += ctx->graph_steps;
