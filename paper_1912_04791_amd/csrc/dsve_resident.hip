@@ -184,13 +184,13 @@ __device__ __forceinline__ void terms_to_fluct(const double (*t)[NodeOf<PREC>::w
         v[k] = u.v;
     }
     if constexpr (PREC == PREC_FP64) {
-        bool ok = E.ok;
+        bool ok = true;
 #pragma unroll
         for (int k = 0; k < G; ++k) ok = ok && v[k].pb == v[k].pb;
         if (__builtin_amdgcn_ballot_w64(!E.one) == 0ull) {
-            OuterSums N = {0.0, 0.0, 0.0, 0.0, 0.0};
+            OuterSums N = first_terms(v[0]);
 #pragma unroll
-            for (int k = 0; k < G; ++k) add_terms(N, v[k]);
+            for (int k = 1; k < G; ++k) add_terms(N, v[k]);
             outer_to_fluct(N, E.up, E.dq, E.gh_eta, Dm, Dp);
         } else {
             TwoSums N;

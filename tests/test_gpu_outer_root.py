@@ -93,3 +93,21 @@ def test_every_kind_of_edge_alone_and_mixed(dsve, G, A_g):
         size = np.abs(rm).max(axis=0) + np.abs(rp).max(axis=0)
         for got, ref in ((gm[:, s] / f, rm), (gp[:, s] / f, rp)):
             assert (np.abs(got - ref).max(axis=0) / size).max() <= TOL, kind
+
+
+@pytest.mark.parametrize("G", [1, 3, 5])
+def test_an_end_below_the_range_of_the_estimate(dsve, G):
+    # the nodes are within the range, one end of the path is not (a dry side): the same bound
+    rng = np.random.default_rng(G)
+    n = 64 * 5
+    h = rng.uniform(0.3, 3.0, n)
+    q = rng.uniform(0.02, 0.25, n) * np.sqrt(9.81 * h) * h
+    wet, dry = (h, q, 0.1 * h), (np.full(n, 1e-25), np.zeros(n), 0.2 * h)
+    flip = rng.random(n) < 0.5
+    WL = tuple(np.where(flip, a, b) for a, b in zip(wet, dry))
+    WR = tuple(np.where(flip, b, a) for a, b in zip(wet, dry))
+    gm, gp = fluct(dsve, WL, WR, 0.05, G)
+    rm, rp = oracle.fluct(WL, WR, 9.81, 1.0 / 0.6, 0.05, G=G)
+    size = np.abs(rm).max(axis=0) + np.abs(rp).max(axis=0)
+    for got, ref in ((gm, rm), (gp, rp)):
+        assert (np.abs(got - ref).max(axis=0) / size).max() <= TOL
