@@ -254,9 +254,9 @@ __device__ __forceinline__ void merge_max(unsigned long long acc, int c, unsigne
 // Waves share nothing until their CFL maxima are merged, so no wave waits for another at a tile, and
 // everything of the channel is the same for the whole wave (scalar registers and branches; the lanes
 // at a channel's ends fix up their ghost cell in a branch that other tiles skip).  Bound by VALU issue
-// in FP64 and by the waits of each wave on its loads and dependent instructions.  Against tiles of 256
-// edges with D^- through LDS, a barrier per tile and per-lane channel lookups, the same arithmetic
-// took, FP64: 65 536 channels of 512-4096 cells 3.12 -> 2.47 ms a step, one channel of 2^20 cells
+// in FP64 and by the waits of each wave on its dependent instructions.  Against tiles of 256 edges with
+// D^- through LDS, a barrier per tile and per-lane channel lookups, the same arithmetic (that of the
+// time) took, FP64: 65 536 channels of 512-4096 cells 3.12 -> 2.47 ms a step, one channel of 2^20 cells
 // 24.5 -> 22.3 us; mixed: one of 4 000 001 cells 65 -> 56 us.
 template <int G, int PREC, int CL>
 __global__ __launch_bounds__(kMaxTile, step_min_waves(PREC, CL)) void k_step(StepArgs A, const ChanInfo *__restrict__ CH,
@@ -275,21 +275,36 @@ __global__ __launch_bounds__(kMaxTile, step_min_waves(PREC, CL)) void k_step(Ste
         const ChanInfo &ci = CH[c];
         const Closure K = closure_of(ci);
         const double fric = ci.fric;
-        const double dt = ci.cfl_dx * rcp_h(amax_of(AM, c << A.amax_shift, A.amax_stride, A.amax_split));
-        const double r = dt * ci.inv_dx;
         // cell i of the segment is at index i + 1 from these bases (cell -1, the left neighbour of
         // a segment inside a channel, at 0; a segment at its channel's start does not read it)
         const int64_t base = sg.cell0 - 1;
         const double *const h = A.h + base, *const q = A.q + base, *const z = A.z + base;
         double *const hn = A.hn + base, *const qn = A.qn + base, *const zn = A.zn + base;
         const int il_min = first ? 1 : 0, ir_max = last ? n : n + 1;
+        // FP64: each tile's states are under way while the tile before is computed, the first tile's
+        // while the time step is formed (120 registers, still four waves a SIMD: 65 536 channels 1.92
+        // -> 1.90 ms a step, 2^20 cells 19.9 -> 19.6 us).  Mixed keeps its fifth wave instead (99
+        // registers with it, 93 without).
+        struct Sides {
+            double hL, qL, zL, hR, qR, zR;
+        };
+        const auto load = [&](int t) {
+            // lanes past the segment's last edge compute it again; they update nothing
+            const int e = t + lane < n ? t + lane : n;
+            const int il = e > il_min ? e : il_min, ir = e + 1 < ir_max ? e + 1 : ir_max;
+            return Sides{ldx(h, il), ldx(q, il), ldx(z, il), ldx(h, ir), ldx(q, ir), ldx(z, ir)};
+        };
+        Sides next;
+        if constexpr (PREC == PREC_FP64) next = load(0);
+        const double dt = ci.cfl_dx * rcp_h(amax_of(AM, c << A.amax_shift, A.amax_stride, A.amax_split));
+        const double r = dt * ci.inv_dx;
         unsigned bad = 0u;
         for (int t0 = 0; t0 < n; t0 += kSegTile) {
-            // lanes past the segment's last edge compute it again; they update nothing
             const int e = t0 + lane < n ? t0 + lane : n;
-            const int il = e > il_min ? e : il_min, ir = e + 1 < ir_max ? e + 1 : ir_max;
-            double hL = ldx(h, il), qL = ldx(q, il), zL = ldx(z, il);
-            double hR = ldx(h, ir), qR = ldx(q, ir), zR = ldx(z, ir);
+            if constexpr (PREC != PREC_FP64) next = load(t0);
+            double hL = next.hL, qL = next.qL, zL = next.zL, hR = next.hR, qR = next.qR, zR = next.zR;
+            if constexpr (PREC == PREC_FP64)
+                if (t0 + kSegTile < n) next = load(t0 + kSegTile);
             const double h0 = hL, q0 = qL, z0 = zL;
             if (first && t0 == 0) {
                 // ghost cell left of the channel's first cell (which every lane of edge 0 holds as R)
