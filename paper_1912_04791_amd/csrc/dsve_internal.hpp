@@ -49,24 +49,23 @@ constexpr unsigned kFlagNonfinite = 4u;  // a non-finite arccos argument (an ove
 constexpr int kMaxGauss = 5;
 constexpr int kMaxTile = 256;     // threads (= edges) per workgroup of the step kernel, at most
 constexpr int kCflThreads = 1024;  // threads per workgroup of the CFL-maximum kernel
-// Waves per SIMD the step kernel is compiled for (bounds its registers per lane).
+// Waves per SIMD the step kernel is compiled for, at least (bounds its registers per lane).  The FP64
+// forms stay within 120 registers and run 4 (a 96-register cap for 5 spills: 0.90 of the rate), the
+// mixed ones 93 and run 5 (capped for 6: 0.77); the power law with a general exponent (143, with its
+// FP64 exp2 and log2) and the DOT variants (157) run 3.
 #ifndef DSVE_MINW_FP64
 #define DSVE_MINW_FP64 3
 #endif
 #ifndef DSVE_MINW_MIXED
 #define DSVE_MINW_MIXED 4
 #endif
-// The other closures carry their laws' power and root evaluations: fewer waves, more
-// registers per lane.
+// The other closures may take more registers for their laws' powers and roots.
 #ifndef DSVE_MINW_LAW_FP64
 #define DSVE_MINW_LAW_FP64 2
 #endif
 #ifndef DSVE_MINW_LAW_MIXED
 #define DSVE_MINW_LAW_MIXED 2
 #endif
-// The FP64 integer-exponent power law runs the 3 waves its 146 registers allow: capped for 4
-// waves it spills 140 bytes and its ensemble steps 26% slower.  MPM and Van Rijn keep the floor
-// of 2 and run 3 waves as well (157 registers).
 #ifndef DSVE_MINW_POWINT_FP64
 #define DSVE_MINW_POWINT_FP64 3
 #endif

@@ -1,13 +1,13 @@
 """Summarise rocprofv3 output of bench.py runs into the text files kept under profiles/.
 
-    python -m paper_1912_04791_amd.profsum --name k_step_c5_fp64 --kernel "k_step<3, 0, 0, false>" \
+    python -m paper_1912_04791_amd.profsum --name k_step_c5_fp64 --kernel "k_step<3, 0, 0>" \
         --workload c5 --precision fp64 --trace DIR --bench-log FILE --bench-json FILE \
         [--fetch DIR --write DIR --calib-mib 256] [--flops DIR] [--valu DIR] [--stall DIR ...] \
         [--clock DIR] \
         --cmd "<the profiling commands>"
 
-Kernel trace (``--kernel-trace``): every GPU run bench.py makes is one ``k_cfl`` dispatch (the
-CFL maximum of the initial state) followed by its step-kernel dispatches, and bench.py logs each
+Kernel trace (``--kernel-trace``): every GPU run bench.py makes is one ``k_start`` dispatch (the
+CFL maximum of the initial state; ``k_cfl`` where channels are packed) followed by its step-kernel dispatches, and bench.py logs each
 run to stderr as a ``[run]`` line (workload, precision, solver, steps, kind) in the order it
 makes them.  The trace's runs are matched to those lines in order, so the durations of the
 timed run of one workload and precision are read apart from its warm-up run, from its
@@ -60,8 +60,8 @@ def read_runs(log_path: str):
 
 
 def trace_runs(trace_dir: str):
-    """The trace's dispatches in order, grouped into runs: each k_cfl dispatch opens a run, and
-    the step-kernel dispatches after it belong to it.  Returns a list of (step kernel name,
+    """The trace's dispatches in order, grouped into runs: each k_start dispatch (k_cfl where the
+    channels are packed) opens a run, and the step-kernel dispatches after it belong to it.  Returns a list of (step kernel name,
     [durations in ns]) for the runs with at least one step dispatch."""
     path = _one(os.path.join(trace_dir, "**", "*kernel_trace.csv"))
     rows = list(csv.DictReader(open(path)))
@@ -70,11 +70,11 @@ def trace_runs(trace_dir: str):
     out, cur = [], None
     for r in rows:
         name = r["Kernel_Name"]
-        if "k_cfl<" in name:
+        if "k_start<" in name or "k_cfl<" in name:
             if cur and cur[1]:
                 out.append(cur)
             cur = [None, []]
-        elif "k_step<" in name and cur is not None:
+        elif ("k_step<" in name or "k_step_packed<" in name) and cur is not None:
             if cur[0] is None:
                 cur[0] = name
             cur[1].append(int(r["End_Timestamp"]) - int(r["Start_Timestamp"]))
