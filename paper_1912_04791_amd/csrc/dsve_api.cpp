@@ -681,25 +681,31 @@ static int grid_of(const dsve_ctx *ctx)
     return (int)std::min<int64_t>(ctx->n_tiles, (int64_t)bpc * ctx->cus);
 }
 
-// CFL sub-slots in use.  Automatic choice: spread the per-workgroup merges over 4 sub-slots
-// when many workgroups share a channel and each merges after a few tiles (the merges of one
-// step then come close together on one address); one sub-slot otherwise, which keeps the
-// per-tile read of the maximum to one load.
+// CFL sub-slots in use.  Automatic choice: spread the per-workgroup merges over 4 sub-slots when many
+// workgroups share a channel and each merges after a few tiles (the merges of one step then come close
+// together on one address); one sub-slot otherwise, where there is little to spread.  One channel, a
+// step with 1 and with 4: 15 000 cells (60 workgroups) 5.0 and 5.15 us, 30 000 (119) 5.7 and 5.3, 60 000
+// 7.2 and 5.7, 2^20 32 and 19.
 static int split_of(const dsve_ctx *ctx, int grid)
 {
     if (ctx->cfl_split > 0) return ctx->cfl_split;
     const double wg_per_channel = (double)grid / (double)ctx->n_channels;
     const double tiles_per_wg = (double)ctx->n_tiles / (double)grid / (ctx->packed ? 1 : ctx->tile / 64);
-    return (wg_per_channel >= 256.0 && tiles_per_wg <= 4.0) ? 4 : 1;
+    return (wg_per_channel >= 96.0 && tiles_per_wg <= 4.0) ? 4 : 1;
 }
 
-// Whether a workgroup looks at its slot before it merges (flush_max): where many waves of one channel
-// run in about one round and end together.  300 000 cells (4762 waves) 8.9 us a step with the look, 9.7
-// without; 4 000 001 cells in four rounds (15 874 waves, mixed) 57 against 54 us; 256 channels of uneven
-// length (13 000 waves) 41 against 40 us.
+// Whether a workgroup looks at its slot before it merges (flush_max): where so many merges crowd a
+// sub-slot that leaving some out pays for the look, 100 where they come about together (one round of
+// waves), 3000 else.  A step of one channel without and with the look: 60 000 cells, 59 merges to a
+// sub-slot, 5.7 and 6.2 us; 200 000 cells, 198: 7.6 and 7.2, 300 000, 298: 9.4 and 8.7 (flow over a hump,
+// where the maxima of the waves differ most: 9.4 and 9.6); 2^20 cells in four rounds, 1041: 18.9 and
+// 20.0, 2081: 20.5 and 23.5, 4162: 32 and 24 to 27.
 static bool check_before_merge(const dsve_ctx *ctx)
 {
-    return ctx->n_segments <= 8192 && ctx->n_segments >= 1024 * ctx->n_channels;
+    if (ctx->packed) return false;
+    const int grid = grid_of(ctx);
+    const int64_t merges = grid / (ctx->n_channels * split_of(ctx, grid));
+    return merges >= (ctx->n_segments <= 8192 ? 100 : 3000);
 }
 
 // The buffers a run rotates through besides the caller's: the ping-pong copy of the state and

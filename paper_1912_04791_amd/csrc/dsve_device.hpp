@@ -93,10 +93,17 @@ __device__ __forceinline__ void flush_max(unsigned long long *slot, unsigned lon
 __device__ __forceinline__ double amax_of(const unsigned long long *__restrict__ AM, int c,
                                          int64_t stride, int split)
 {
+    // every load goes out before the first is waited for (split is a power of two): one channel of 2^20
+    // cells 20.6 -> 18.9 us a step, 100 000 cells 7.0 -> 6.4, against a branch and a wait per sub-slot
     double m = __longlong_as_double((long long)AM[c]);
+    if (split > 1) {
+        double v[kAmaxSplitMax];
 #pragma unroll
-    for (int s = 1; s < kAmaxSplitMax; ++s)
-        if (s < split) m = fmax(m, __longlong_as_double((long long)AM[c + s * stride]));
+        for (int s = 1; s < kAmaxSplitMax; ++s)
+            v[s] = __longlong_as_double((long long)AM[c + (s & (split - 1)) * stride]);
+#pragma unroll
+        for (int s = 1; s < kAmaxSplitMax; ++s) m = fmax(m, v[s]);
+    }
     return m;
 }
 

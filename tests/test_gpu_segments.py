@@ -79,3 +79,15 @@ def test_one_channel_in_many_segments(dsve, n_cells):
         for a, b in zip(o, outs[0]):
             assert np.array_equal(a, b)
     assert per_channel_rel_l1(outs[0], oracle_run(wl), wl.offsets).max() <= 1e-12
+
+
+@pytest.mark.parametrize("n_cells,split", [(23_940, 1), (23_941, 4), (100_548, 4), (100_549, 4)])
+def test_where_sub_slots_and_the_look_begin(dsve, n_cells, split):
+    # 96 workgroups on the channel: 4 sub-slots; 400: a look at the slot before the merge
+    wl = inputs.make_c2(n_cells=n_cells, steps=7, length=1000.0 * n_cells / (1 << 20))
+    ctx = dsve.Context.from_workload(wl)
+    assert ctx.get_cfl_split() == split
+    ctx.close()
+    outs = [run(dsve, wl, "fp64", launch) for launch in [(256, 0, 60), (64, 1, 0)]]
+    for a, b in zip(*outs):
+        assert np.array_equal(a, b)
