@@ -291,8 +291,8 @@ dsve_status dsve_get_launch(const dsve_ctx *ctx, int *tile, int *blocks_per_cu, 
 /* CFL sub-slots of the fused step kernel: each workgroup merges its partial
  * CFL maximum with an atomic into one of `split` sub-slots per channel (1, 2 or
  * 4; 0, the default, picks 4 when many workgroups share a channel and each
- * merges after a few tiles, else 1), and a workgroup reads the maximum over them
- * when its run of tiles enters a channel.
+ * merges after a few tiles, else 1), and a wave reads the maximum over them when it
+ * enters a channel.
  * More sub-slots spread the atomics of a step over more addresses; fewer keep
  * the read to fewer loads.  The results do not depend on it.  The getter reports
  * the count in effect for the current launch configuration. */
