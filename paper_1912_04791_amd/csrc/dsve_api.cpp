@@ -275,9 +275,10 @@ static dsve_status build_table(dsve_ctx *c, int tile, int blocks_per_cu)
 // Parts of a context with few channels (k_parts): one per channel that a workgroup holds, up to one per
 // compute unit (with more channels the workgroups fill the chip, and k_resident, with fewer waves per
 // channel, does more of them at once); with longer channels among them, cut into parts that wait for
-// one another, at most kMaxParts in all, eight on an XCD.  An XCD has a compute unit for each of 32, so
-// launches from four hardware queues, of which each may be partly on the chip, always all get there.
-// Past kMaxParts (about 7000 cells) the per-step kernels take over, on a stream restricted to some of
+// one another, at most max_parts in all: a quarter of what the device holds at once, so that launches
+// from four hardware queues, of which each may be partly on the chip, all get there; and 64, eight on each
+// of eight XCDs.
+// Past that limit (about 7000 cells) the per-step kernels take over, on a stream restricted to some of
 // the compute units too.  Channels of 127 to 255 cells stay with one workgroup of k_resident, as fast
 // as three parts (250 cells: 1.79 against 1.89 us a step), except with the numerical eigensolver.
 static dsve_status plan_parts(dsve_ctx *c, std::vector<Part> &table)
@@ -293,6 +294,7 @@ static dsve_status plan_parts(dsve_ctx *c, std::vector<Part> &table)
     }
     if (parts > (cut ? kMaxParts : (int64_t)c->cus)) return DSVE_OK;
     if (cut && longest <= kResidentSmall && c->precision != PREC_DOT) return DSVE_OK;
+    if (cut && parts > max_parts(c->cus, parts_per_cu(c->precision, c->G, c->cl))) return DSVE_OK;
     if (cut) {
         uint32_t mask[32] = {0};
         int on = 0;

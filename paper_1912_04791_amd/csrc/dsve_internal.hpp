@@ -214,6 +214,13 @@ struct ResidentArgs {
 // global memory.
 constexpr int kPartHalo = 8;
 constexpr int64_t kMaxParts = 64;   // parts of a context with channels of several parts, at most
+// ... on a device of `cus` compute units that holds `per_cu` workgroups of k_parts on each: a quarter of
+// what it holds at once, so that launches from four hardware queues get there whole.
+inline int64_t max_parts(int cus, int per_cu)
+{
+    const int64_t quarter = (int64_t)cus * per_cu / 4;
+    return quarter < kMaxParts ? quarter : kMaxParts;
+}
 struct Part {
     int64_t cell0;      // first cell of the channel in the concatenated state
     int64_t ncell;      // cells of the channel
@@ -310,6 +317,8 @@ hipError_t launch_fill_u32(unsigned int *p, int64_t n, unsigned int v, hipStream
 // workgroups of `threads` (256 or 512) threads, more than the longest channel has cells.
 hipError_t launch_resident(const ResidentArgs &a, int precision, int G, int cl, int threads, int grid,
                            hipStream_t stream);
+// Workgroups of k_parts that fit on one compute unit at once (occupancy query; 0 if it fails).
+int parts_per_cu(int precision, int G, int cl);
 // All n_steps of a run of the parts in one launch.
 hipError_t launch_parts(const PartArgs &a, int precision, int G, int cl, int grid, hipStream_t stream);
 // kAmaxSplitMax as compiled into the kernels (the host code checks it against its own).

@@ -542,6 +542,26 @@ static hipError_t launch_parts_prec(const PartArgs &a, int G, int cl, int grid, 
     return hipGetLastError();
 }
 
+template <int PREC>
+static hipError_t parts_occupancy(int G, int cl, int &n)
+{
+    hipError_t e = hipErrorInvalidValue;
+#define DSVE_OCC(GG, CC) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_parts<GG, PREC, CC>, kPartThreads, 0)
+    DSVE_DISPATCH_G_CL(G, cl, DSVE_OCC)
+#undef DSVE_OCC
+    return e;
+}
+
+int parts_per_cu(int precision, int G, int cl)
+{
+    int n = 0;
+    const hipError_t e = precision == PREC_MIXED ? parts_occupancy<PREC_MIXED>(G, cl, n)
+                       : precision == PREC_DOT   ? parts_occupancy<PREC_DOT>(G, cl, n)
+                                                 : parts_occupancy<PREC_FP64>(G, cl, n);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e == hipSuccess && n > 0 ? n : 0;
+}
+
 hipError_t launch_parts(const PartArgs &a, int precision, int G, int cl, int grid, hipStream_t stream)
 {
     if (grid < 1 || a.n_steps < 1) return hipErrorInvalidValue;

@@ -1,0 +1,98 @@
+"""Host tests of the library's host code (dsve_api.cpp), compiled against a HIP runtime and launchers that
+do nothing (host_hip.cpp): which kernels a run takes on devices and streams of other sizes.
+"""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1912_04791_amd", "csrc")
+LIB = os.path.join(ROOT, "paper_1912_04791_amd", "libdsve.so")
+
+pytestmark = pytest.mark.skipif(not os.path.exists(LIB), reason="libdsve.so not built")
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("host") / "libhost.so")
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__",
+                           "-Wl,-Bsymbolic", "-I", CSRC, "-I", "/opt/rocm/include",
+                           os.path.join(ROOT, "tests", "host_hip.cpp"), os.path.join(CSRC, "dsve_api.cpp"), "-o", so])
+    return ctypes.CDLL(so)
+
+
+class Host:
+    """One context of the host build, of one channel or of channels of the given lengths."""
+
+    def __init__(self, lib, lengths, fake=None, reset=True, **kw):
+        from paper_1912_04791_amd import dsve
+        self.lib, self.ctx = lib, ctypes.c_void_p()
+        lib.fake_get.restype = ctypes.c_long
+        lib.fake_set.argtypes = [ctypes.c_char_p, ctypes.c_long]
+        if reset:
+            lib.fake_reset()
+        for k, v in (fake or {}).items():
+            self.set(k, v)
+        n = int(np.sum(lengths))
+        p = dsve.make_params(dx=0.1, **kw)
+        if np.ndim(lengths) == 0:
+            st = lib.dsve_init(ctypes.byref(self.ctx), ctypes.byref(p), ctypes.c_int64(n), None)
+        else:
+            C = len(lengths)
+            off = (ctypes.c_int64 * (C + 1))(*np.concatenate([[0], np.cumsum(lengths)]).tolist())
+            ch = dsve.make_channels([0.01] * C, [0.4] * C, [0.1] * C, [0] * C, [0] * C)
+            st = lib.dsve_batch_init(ctypes.byref(self.ctx), ctypes.c_int64(C), off, ch, ctypes.byref(p), None)
+        self.status = st
+        self.state = [np.ones(n) for _ in range(3)]
+        self.t = np.zeros(np.size(lengths))
+
+    def set(self, name, v):
+        self.lib.fake_set(name.encode(), v)
+
+    def count(self, name):
+        return self.lib.fake_get(name.encode())
+
+    def call(self, f, *args):
+        return getattr(self.lib, f)(self.ctx, *args)
+
+    def ptrs(self):
+        return [ctypes.c_void_p(x.ctypes.data) for x in (*self.state, self.t)]
+
+    def run(self, n_steps, f="adot_step_batched"):
+        h, q, z, t = self.ptrs()
+        return self.call(f, h, q, z, n_steps, t)
+
+    def in_parts(self, n_steps=5):
+        before = self.count("parts")
+        assert self.run(n_steps) == 0
+        return self.count("parts") == before + 1
+
+    def close(self):
+        assert self.call("dsve_destroy") == 0
+
+
+def in_parts(lib, lengths, **fake):
+    h = Host(lib, lengths, fake)
+    assert h.status == 0
+    got = h.in_parts()
+    h.close()
+    return got
+
+
+def test_parts_stay_within_what_the_device_holds(host):
+    # a quarter of the workgroups that the device holds at once, 64 at most; 110 cells a part (G = 3)
+    for cus, per_cu, most in [(256, 1, 64), (256, 2, 64), (64, 1, 16), (64, 2, 32), (32, 1, 8), (32, 2, 16)]:
+        fake = dict(cus=cus, mask=cus, per_cu=per_cu)
+        assert in_parts(host, most * 110, **fake), fake
+        assert not in_parts(host, most * 110 + 1, **fake), fake
+        assert in_parts(host, [880] * (most // 8), **fake), fake
+        assert not in_parts(host, [880] * (most // 8) + [100], **fake), fake
+    # a kernel that does not fit, or a stream that may use part of the device
+    assert not in_parts(host, 2000, per_cu=0)
+    assert not in_parts(host, 2000, mask=255)
+    # channels of one workgroup each wait for none: one per compute unit
+    assert in_parts(host, [100] * 32, cus=32, mask=32)
+    assert not in_parts(host, [100] * 33, cus=32, mask=32)
