@@ -313,8 +313,9 @@ dsve_status dsve_get_cfl_split(const dsve_ctx *ctx, int *split);
  * With few channels (at most 256 short ones, or about 7000 cells in all) the run is spread over more
  * of the chip: each channel is held by one or several workgroups that exchange their CFL maxima and
  * end cells, also channels of more than 511 cells unless a launch was set; same results, one launch.
- * Those workgroups wait for one another; should they not come to run together within 20 s on a device
- * held by others, the run fails with DSVE_E_HIP at dsve_sync. */
+ * Those workgroups wait for one another; where they do not come to run together, on a device held by
+ * others, one of them does the work of its channel alone, with the same results but in up to 40 times
+ * the time. */
 dsve_status dsve_set_resident(dsve_ctx *ctx, int mode);
 dsve_status dsve_get_resident(const dsve_ctx *ctx, int *active);
 

@@ -64,6 +64,8 @@ struct dsve_ctx {
     Part *d_parts = nullptr;
     int64_t n_parts = 0;         // 0: the context does not run that way
     int parts_grid = 0;
+    int64_t wait_ticks = 0;   // for tests (dsve_test_hold_part): see PartArgs; 0: automatic
+    int hold_part = -1, hold_step = 0;
     bool launch_set = false;     // a launch configuration was asked for: per-step kernels where not resident
     unsigned int *d_flags = nullptr;                             // [4]
     unsigned long long *d_acc = nullptr;                         // [2] of cfl_reduce
@@ -274,10 +276,11 @@ static dsve_status build_table(dsve_ctx *c, int tile, int blocks_per_cu)
 
 // Parts of a context with few channels (k_parts): one per channel that a workgroup holds, up to one per
 // compute unit (with more channels the workgroups fill the chip, and k_resident, with fewer waves per
-// channel, does more of them at once); with longer channels among them, cut into parts that wait for
-// one another, at most max_parts in all: a quarter of what the device holds at once, so that launches
-// from four hardware queues, of which each may be partly on the chip, all get there; and 64, eight on each
-// of eight XCDs.
+// channel, does more of them at once; none waits for another); with longer channels among them, cut into
+// parts that wait for one another, at most max_parts in all: a quarter of what the device holds and 64 of
+// it, eight on each of eight XCDs, whose 32 compute units then take launches from four hardware queues
+// whole.  That is so that parts seldom wait, not what a run's end rests on: where they do not all come (more
+// queues, other processes, long kernels beside them), one part takes the channel over (k_parts).
 // Past that limit (about 7000 cells) the per-step kernels take over, on a stream restricted to some of
 // the compute units too.  Channels of 127 to 255 cells stay with one workgroup of k_resident, as fast
 // as three parts (250 cells: 1.79 against 1.89 us a step), except with the numerical eigensolver.
@@ -869,6 +872,22 @@ static dsve_status ensure_graphs(dsve_ctx *ctx, double *h, double *q, double *z,
     return DSVE_OK;
 }
 
+// All parts of a channel on the device, none of their waits has a reason to last; should one all the
+// same, it ends after these ticks of the 100 MHz clock (20 s).
+constexpr int64_t kStallTicks = 2000000000;
+
+// Ticks that a part waits for the others to come to the device: about what the channel takes on one
+// workgroup (200 + 130 per 8 tiles a step, eight times that with the numerical eigensolver), so that the
+// waiting at most doubles it; 1 ms at least, and 20 s at most.
+static int64_t takeover_ticks(const dsve_ctx *ctx, int n_steps)
+{
+    int64_t longest = 0;
+    for (int64_t k = 0; k < ctx->n_channels; ++k) longest = std::max(longest, ctx->h_off[k + 1] - ctx->h_off[k]);
+    const int64_t rounds = (longest + 8 * kSegTile - 1) / (8 * kSegTile);
+    const int64_t step = (200 + 130 * rounds) * (ctx->precision == PREC_DOT ? 8 : 1);
+    return std::min(kStallTicks, std::max<int64_t>(100000, step * n_steps));
+}
+
 // The whole run in one launch of k_parts; the final CFL maxima land in sub-slot 0 of slot 0 for the
 // check in dsve_sync.
 static dsve_status run_parts(dsve_ctx *ctx, double *h, double *q, double *z, int n_steps, double *t)
@@ -876,12 +895,17 @@ static dsve_status run_parts(dsve_ctx *ctx, double *h, double *q, double *z, int
     HIP_TRY(ctx, launch_fill_u64(ctx->d_amax, 3 * ctx->amax_slot + part_box_words(ctx->n_parts), 0ull, ctx->stream));
     PartArgs a{};
     a.h = h; a.q = q; a.z = z; a.t = t;
+    a.hp = ctx->pp_h; a.qp = ctx->pp_q; a.zp = ctx->pp_z;
     a.ch = ctx->d_ch; a.parts = ctx->d_parts; a.box = ctx->d_amax + 3 * ctx->amax_slot; a.amax = ctx->d_amax;
     a.flags = ctx->d_flags;
     a.n_parts = (int32_t)ctx->n_parts;
     a.n_steps = n_steps;
     a.amax_shift = ctx->amax_sh;
     a.g = ctx->g;
+    a.wait_ticks = (unsigned long long)(ctx->wait_ticks > 0 ? ctx->wait_ticks : takeover_ticks(ctx, n_steps));
+    a.stall_ticks = (unsigned long long)(ctx->wait_ticks > 0 ? ctx->wait_ticks : kStallTicks);
+    a.hold_part = ctx->hold_part;
+    a.hold_step = ctx->hold_step;
     HIP_TRY(ctx, launch_parts(a, ctx->precision, ctx->G, ctx->cl, ctx->parts_grid, ctx->stream));
     ctx->last_amax_slot = 0;
     ctx->last_graph_launches = 0;
@@ -1154,6 +1178,16 @@ dsve_status dsve_get_cfl_split(const dsve_ctx *ctx, int *split)
 {
     if (!ctx || !split) return DSVE_E_ARG;
     *split = split_of(ctx, grid_of(ctx));
+    return DSVE_OK;
+}
+
+// For tests of runs in parts, not part of the interface: see PartArgs.
+dsve_status dsve_test_hold_part(dsve_ctx *ctx, int part, int step, int wait_us)
+{
+    if (!ctx || part < -1 || step < 0 || wait_us < 0 || wait_us > 100000) return DSVE_E_ARG;
+    ctx->hold_part = part;
+    ctx->hold_step = step;
+    ctx->wait_ticks = 100 * (int64_t)wait_us;
     return DSVE_OK;
 }
 

@@ -234,14 +234,16 @@ struct Part {
     int32_t cut;        // 1: another part's cells lie left of it, 2: right of it
 };
 // Mailboxes of a context with P parts, in 64-bit words {tag, 32 bits of data}: [2][P][kMaxWords] CFL
-// maxima, [2][P][2][kHaloWords] cells next to the left and the right cut.
+// maxima, [2][P][2][kHaloWords] cells next to the left and the right cut; then [P] words, of which that
+// of a channel's first part counts the channel's parts on the device.
 constexpr int kPartMaxWords = 2 * 8;                  // two words per wave that takes CFL speeds
 constexpr int kPartHaloWords = kPartHalo * 3 * 2;
-inline int64_t part_box_words(int64_t parts) { return 2 * parts * (kPartMaxWords + 2 * kPartHaloWords); }
+inline int64_t part_box_words(int64_t parts) { return parts * (2 * (kPartMaxWords + 2 * kPartHaloWords) + 1); }
 
 struct PartArgs {
     double *h, *q, *z;           // state, updated in place
     double *t;                   // [C] clocks
+    double *hp, *qp, *zp;        // copy of the state, for a channel that one part takes over
     const ChanInfo *ch;
     const Part *parts;           // [grid]
     unsigned long long *box;     // mailboxes, zero at the start of the run
@@ -251,6 +253,12 @@ struct PartArgs {
     int32_t n_steps;
     int32_t amax_shift;
     double g;
+    // ticks of the 100 MHz clock that a part waits in the first step for all parts of its channel to be on
+    // the device before it takes the channel over, and, beyond those, in any step before it gives up
+    unsigned long long wait_ticks, stall_ticks;
+    // for tests: this part of every channel of several starts 4 wait_ticks late (hold_step 0), or leaves
+    // after hold_step steps; -1 for none
+    int32_t hold_part, hold_step;
 };
 constexpr int kPartThreads = 512;   // per workgroup
 // Waves per role (G nodes, and the rest of the step) and cells held by a workgroup.

@@ -225,22 +225,161 @@ __device__ __forceinline__ unsigned long long peek(const unsigned long long *w)
 {
     return __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// A wait ends after this many ticks of the 100 MHz clock (20 s): the workgroups of a launch all fit on
-// the chip at once, so only a chip held by others for that long makes a part wait in vain.
-constexpr unsigned long long kWaitTicks = 2000000000ull;
-// (The clock is first read after 256 looks, which most waits do not need.)
+// Waits on another workgroup are looked at every 256 looks: true then (most waits end before that).
 struct Wait {
-    unsigned long long t0 = 0ull;
+    unsigned long long t0 = 0ull, t = 0ull;
     int looks = 0;
-    __device__ __forceinline__ bool over()
+    __device__ __forceinline__ bool pause()
     {
         if ((++looks & 255) != 0) return false;
-        const unsigned long long t = wall_clock64();
+        t = wall_clock64();
         if (t0 == 0ull) t0 = t;
-        return t - t0 > kWaitTicks;
+        return true;
     }
+    __device__ __forceinline__ bool past(unsigned long long ticks) const { return t - t0 > ticks; }
 };
+// Why a part stopped before the run's last step (s_stop).
+enum { kAllThere = 0, kGone = 1, kAlone = 2, kStalled = 3 };
 constexpr unsigned long long kGaveUp = ~0ull;   // in place of a maximum (whose sign bit is clear)
+
+// The arguments of k_parts, read again: what only the paths that are hardly ever taken need would else be
+// held in registers through every step (200 steps of 500 cells: 403 -> 387 us).
+__device__ __forceinline__ const PartArgs &args_again()
+{
+    auto *p = (const __attribute__((address_space(4))) PartArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));   // opaque to the compiler
+    return *(const PartArgs *)p;
+}
+// The word that counts the parts of a channel on the device.
+__device__ __forceinline__ unsigned long long *there_word(const PartArgs &A, const Part &P)
+{
+    return A.box + 2 * (int64_t)A.n_parts * (kPartMaxWords + 2 * kPartHaloWords) + (P.id - P.index);
+}
+
+// What becomes of part `id` of a channel whose parts have not all shown up in its first step.  Every part
+// counts itself once in the low half of `word` before its first post; the high half holds 1 + the part
+// that has taken the channel over.  Only while the count is short can a part take over (`late`: it has
+// waited long enough), and a part that finds the channel taken leaves, so either every part is on the
+// device, and then stays there to the end, or one part does the channel's work and no other waits.
+__device__ __forceinline__ int fate_of(unsigned long long *word, unsigned n_parts, unsigned id, bool late)
+{
+    int fate = kAllThere;
+    if ((threadIdx.x & 63) == 0) {
+        unsigned long long v = peek(word);
+        // (the word changes at most n_parts + 1 times)
+        while (late && (v >> 32) == 0ull && (unsigned)v < n_parts) {
+            const unsigned long long taken = v | ((unsigned long long)(id + 1u) << 32);
+            if (__hip_atomic_compare_exchange_strong(word, &v, taken, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT))
+                v = taken;
+        }
+        if ((v >> 32) != 0ull) fate = (unsigned)(v >> 32) == id + 1u ? kAlone : kGone;
+    }
+    return __builtin_amdgcn_readfirstlane(fate);
+}
+
+// Whether a wait of part P goes on (kAllThere) or how it ends; looked at while the first maxima of a run
+// are waited for (first) or after that.
+__device__ __forceinline__ int wait_ends(const Wait &wait, bool first)
+{
+    const PartArgs &A = args_again();
+    const Part &P = A.parts[blockIdx.x];
+    // the first maxima are there when every part is; from then on all of them stay
+    int stop = kAllThere;
+    if (first) stop = fate_of(there_word(A, P), (unsigned)P.n_parts, (unsigned)P.id, wait.past(A.wait_ticks));
+    return stop == kAllThere && wait.past(A.wait_ticks + A.stall_ticks) ? kStalled : stop;
+}
+
+// A whole channel on this workgroup through global memory, all steps from the state in (h, q, z): tiles
+// of 64 edges as in k_step, same operations, each wave every kPartThreads / 64-th tile.  For the part
+// that took its channel over, which then waits for no other (1800 cells 4.5 us a step, 7040 cells 22,
+// against 1.8 and 1.9 of all parts; numerical eigensolver 75 and 240 against 6.6 and 6.7).
+template <int G, int PREC, int CL>
+__device__ __forceinline__ void run_alone(unsigned &bad)
+{
+    const PartArgs &A = args_again();
+    const int c = A.parts[blockIdx.x].chan;
+    const ChanInfo &ci = A.ch[c];
+    const Closure K = closure_of(ci);
+    double tc = A.t[c];
+    constexpr int WAVES = kPartThreads / 64;
+    __shared__ unsigned long long s_m[2][WAVES];   // CFL maxima of the waves in even and odd steps
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int N = (int)ci.ncell;                   // (a channel of several parts is short)
+    double *src[3] = {A.h + ci.cell0, A.q + ci.cell0, A.z + ci.cell0};
+    double *dst[3] = {A.hp + ci.cell0, A.qp + ci.cell0, A.zp + ci.cell0};
+    unsigned long long acc = 0ull;
+    const auto see = [&](double h, double q) {
+        const unsigned long long b = (unsigned long long)__double_as_longlong(fabs(cell_speed<PREC, CL>(h, q, A.g, K, bad)));
+        acc = b > acc ? b : acc;
+    };
+    const auto swap_state = [&] {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            double *const p = src[k];
+            src[k] = dst[k];
+            dst[k] = p;
+        }
+    };
+    // an odd run starts from the copy, so that it ends in (h, q, z)
+    for (int i = (int)threadIdx.x; i < N; i += kPartThreads) {
+        const double h = src[0][i], q = src[1][i];
+        see(h, q);
+        if (A.n_steps & 1) {
+            dst[0][i] = h;
+            dst[1][i] = q;
+            dst[2][i] = src[2][i];
+        }
+    }
+    if (A.n_steps & 1) swap_state();
+    for (int n = 0; n < A.n_steps; ++n) {
+        const unsigned long long m = wave_max_u64(acc);
+        if (lane == 0) s_m[n & 1][wave] = m;
+        __syncthreads();                           // and the state of the step is written
+        unsigned long long top = 0ull;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) top = s_m[n & 1][w] > top ? s_m[n & 1][w] : top;
+        const double dt = ci.cfl_dx * rcp_h(__longlong_as_double((long long)top));
+        const double r = dt * ci.inv_dx;
+        acc = 0ull;
+        for (int t0 = kSegTile * wave; t0 < N; t0 += kSegTile * WAVES) {
+            const int e = t0 + lane < N ? t0 + lane : N;   // lanes past the last edge compute it again
+            const int il = e > 0 ? e - 1 : ci.bcl == BC_PERIODIC ? N - 1 : 0;
+            const int ir = e < N ? e : ci.bcr == BC_PERIODIC ? 0 : N - 1;
+            double hL = src[0][il], qL = src[1][il], zL = src[2][il];
+            double hR = src[0][ir], qR = src[1][ir], zR = src[2][ir];
+            const double h0 = hL, q0 = qL, z0 = zL;
+            if (e == 0) {
+                hL = ghost_h(ci.bcl, ci.bl, hL);
+                qL = ghost_q(ci.bcl, ci.bl, qL);
+                if (ci.bcl == BC_DIRICHLET) zL = ghost_z(ci.bcl, ci.bl, zL, tc);
+            } else if (e == N) {
+                hR = ghost_h(ci.bcr, ci.br, hR);
+                qR = ghost_q(ci.bcr, ci.br, qR);
+                if (ci.bcr == BC_DIRICHLET) zR = ghost_z(ci.bcr, ci.br, zR, tc);
+            }
+            double Dm[3], Dp[3];
+            edge_fluct<G, PREC, CL>(hL, qL, zL, hR, qR, zR, A.g, K, Dm, Dp, bad);
+            const double p0 = lane_below(Dp[0]), p1 = lane_below(Dp[1]), p2 = lane_below(Dp[2]);
+            if (lane > 0 && t0 + lane <= N) {
+                // W_i^{n+1} = W_i^n - dt/dx (D^-_{i+1/2} + D^+_{i-1/2}) + dt S(W_i^n) (Sec. 3, Eq. scheme)
+                const double hv = h0 - r * (Dm[0] + p0);
+                double qv = q0 - r * (Dm[1] + p1);
+                const double zv = z0 - r * (Dm[2] + p2);
+                if (ci.fric > 0.0) qv = fma(dt, friction_source(h0, q0, A.g, ci.fric), qv);
+                dst[0][e - 1] = hv;
+                dst[1][e - 1] = qv;
+                dst[2][e - 1] = zv;
+                see(hv, qv);
+            }
+        }
+        swap_state();
+        tc += dt;
+    }
+    const unsigned long long m = wave_max_u64(acc);
+    if (lane == 0 && m != 0ull) atomicMax(&A.amax[c << A.amax_shift], m);
+    if (threadIdx.x == 0) A.t[c] = tc;
+}
 
 // A run of few channels, all n steps in one launch: one workgroup per part of a channel.
 //
@@ -250,6 +389,11 @@ constexpr unsigned long long kGaveUp = ~0ull;   // in place of a maximum (whose 
 // of the nodes' terms (in the order of the per-step kernels, so the results are bitwise theirs), the
 // exchange of D^+ with the lane above by a DPP move, and the update: lane l of its wave w takes edge
 // 63 w + l and updates cell 63 w + l - 1, as in k_step.  Two barriers per step.
+//
+// Parts wait for one another, so they all have to be on the chip.  Each counts itself in at its start, at
+// no cost but an atomic's way there and back beside the first loads; should one be missing when the others
+// have waited for it about as long as the run takes on one workgroup (wait_ticks), one of them takes the
+// channel over (fate_of, run_alone) and the rest end.  From the first step's maxima on all are there.
 //
 // A channel longer than one workgroup holds is cut into parts, which take the maximum of their CFL
 // maxima through mailboxes once a step (its latency runs beside the nodes), and keep kPartHalo cells of
@@ -303,31 +447,59 @@ void k_parts(PartArgs A)
         s_st[2][i] = z = A.z[cell];
     }
     double tc = A.t[P.chan];
+    const int first = P.id - P.index;                 // the channel's first part
     // (the clock has been read when the first barrier is passed: a part that ends writes it)
     if (threadIdx.x == 0) {
         s_tc = tc;
-        s_stop = 0;
+        int stop = kAllThere;
+        if (many) {
+            if (P.index == A.hold_part && A.hold_step == 0) {
+                const unsigned long long t0 = wall_clock64();
+                while (wall_clock64() - t0 < 4ull * A.wait_ticks) __builtin_amdgcn_s_sleep(8);
+            }
+            // here, unless the channel has been taken over (fate_of)
+            const unsigned long long was = __hip_atomic_fetch_add(there_word(A, P), 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if ((was >> 32) != 0ull) stop = kGone;
+        }
+        s_stop = stop;
     }
     unsigned bad = 0u;
-    const int first = P.id - P.index;                 // the channel's first part
     const int left = first + (P.index > 0 ? P.index - 1 : P.n_parts - 1);
     const int right = first + (P.index + 1 < P.n_parts ? P.index + 1 : 0);
     // mailboxes of the maxima: this wave's word, and up to kLooks words per lane that it reads
     constexpr int kLooks = kMaxParts * 2 * NW / 64;
     const int words = P.n_parts * 2 * NW, looks = (words + 63) / 64;
-    unsigned long long *const box_max = A.box, *const my_word = box_max + (int64_t)P.id * kPartMaxWords + 2 * gw + lane;
-    int64_t look[kLooks];
+    unsigned long long *my_word = A.box + (int64_t)P.id * kPartMaxWords + 2 * gw + lane;
+    unsigned long long *look[kLooks];
 #pragma unroll
     for (int k = 0; k < kLooks; ++k) {
         const int j = 64 * k + lane < words ? 64 * k + lane : lane & 1;
-        look[k] = (int64_t)(first + j / (2 * NW)) * kPartMaxWords + j % (2 * NW);
+        look[k] = A.box + (int64_t)(first + j / (2 * NW)) * kPartMaxWords + j % (2 * NW);
+        asm volatile("" : "+v"(look[k]));   // kept, not formed again from the arguments in every step
     }
-    unsigned long long *const box_halo = A.box + 2 * (int64_t)A.n_parts * kPartMaxWords;
+    asm volatile("" : "+v"(my_word));
+    // and of the cells next to the cuts: where this lane's cell goes on either side, and where it comes from
+    unsigned long long *halo_out[2], *halo_in;
+    {
+        unsigned long long *const box_halo = A.box + 2 * (int64_t)A.n_parts * kPartMaxWords;
+        const bool lo_side = mine && cutL && i < P.own0, hi_side = mine && cutR && i >= P.own1;
+#pragma unroll
+        for (int side = 0; side < 2; ++side) {
+            const int at = side ? i - (P.own1 - kPartHalo) : i - P.own0;
+            halo_out[side] = box_halo + ((int64_t)P.id * 2 + side) * kPartHaloWords + at * 6;
+            asm volatile("" : "+v"(halo_out[side]));
+        }
+        // the left neighbour's cells next to its right cut, the right one's next to its left
+        const int64_t from = lo_side ? ((int64_t)left * 2 + 1) * kPartHaloWords : (int64_t)right * 2 * kPartHaloWords;
+        halo_in = box_halo + from + (lo_side ? i : hi_side ? i - P.own1 : 0) * 6;
+        asm volatile("" : "+v"(halo_in));
+    }
     // The waves of role G are what a step waits for: they go first where waves share a SIMD.
     if (role == G) __builtin_amdgcn_s_setprio(3);
     int v0 = 0, v1 = n;                               // cells whose state is that of the step
+    const int n_steps = many && P.index == A.hold_part && A.hold_step > 0 && A.hold_step < A.n_steps ? A.hold_step : A.n_steps;
     int step = 0;
-    for (; step < A.n_steps; ++step) {
+    for (; step < n_steps; ++step) {
         __syncthreads();
         if (many && s_stop) break;
         const int w0 = v0 + (cutL ? 1 : 0), w1 = v1 - (cutR ? 1 : 0);   // cells of the next state
@@ -392,24 +564,27 @@ void k_parts(PartArgs A)
             const double s0 = Dm[0] + lane_below(Dp[0]), s1 = Dm[1] + lane_below(Dp[1]), s2 = Dm[2] + lane_below(Dp[2]);
             if (many) {
                 Wait wait;
+                int stop = kAllThere;
                 unsigned long long v[kLooks];
                 for (;;) {
                     bool ready = true;
 #pragma unroll
                     for (int k = 0; k < kLooks; ++k)
-                        if (k < looks) v[k] = peek(box_max + parity + look[k]);
+                        if (k < looks) v[k] = peek(look[k] + parity);
 #pragma unroll
                     for (int k = 0; k < kLooks; ++k)
                         if (k < looks) ready = ready && (unsigned)(v[k] >> 32) == tag;
                     if (__builtin_amdgcn_ballot_w64(!ready) == 0ull) break;
-                    if (wait.over()) {
+                    if (__builtin_expect(!wait.pause(), 1)) continue;
+                    stop = wait_ends(wait, step == 0);
+                    if (stop != kAllThere) {
                         amax = kGaveUp;
                         break;
                     }
                 }
                 if (amax == kGaveUp) {
-                    if (lane == 0) s_stop = 1;
-                    bad |= kFlagTimeout;
+                    if (lane == 0) s_stop = stop;
+                    if (stop == kStalled) bad |= kFlagTimeout;
                 } else {
                     // even lanes read high halves, odd lanes the low halves below them
 #pragma unroll
@@ -440,16 +615,15 @@ void k_parts(PartArgs A)
         if (needed) bad |= edge_bad;
         v0 = w0;
         v1 = w1;
-        if (many && role == G && (step + 1) % kPartHalo == 0 && step + 1 < A.n_steps) {
+        if (many && role == G && (step + 1) % kPartHalo == 0 && step + 1 < n_steps) {
             // own cells next to a cut go out, the neighbours' come in
-            unsigned long long *const hb =
-                box_halo + (int64_t)(((step + 1) / kPartHalo) & 1) * A.n_parts * 2 * kPartHaloWords;
+            const int64_t hb = (int64_t)(((step + 1) / kPartHalo) & 1) * A.n_parts * 2 * kPartHaloWords;
             const double v[3] = {h, q, z};
 #pragma unroll
             for (int side = 0; side < 2; ++side) {
                 const int at = side ? i - (P.own1 - kPartHalo) : i - P.own0;
                 if (own && (side ? cutR : cutL) && at >= 0 && at < kPartHalo) {
-                    unsigned long long *const w = &hb[((int64_t)P.id * 2 + side) * kPartHaloWords + at * 6];
+                    unsigned long long *const w = halo_out[side] + hb;
 #pragma unroll
                     for (int k = 0; k < 3; ++k) {
                         const unsigned long long x = (unsigned long long)__double_as_longlong(v[k]);
@@ -460,9 +634,7 @@ void k_parts(PartArgs A)
             }
             const bool lo_side = mine && cutL && i < P.own0, hi_side = mine && cutR && i >= P.own1;
             if (__builtin_amdgcn_ballot_w64(lo_side || hi_side) != 0ull) {
-                // the left neighbour's cells next to its right cut, the right one's next to its left
-                const int64_t from = lo_side ? ((int64_t)left * 2 + 1) * kPartHaloWords : (int64_t)right * 2 * kPartHaloWords;
-                const unsigned long long *const w = &hb[from + (lo_side ? i : hi_side ? i - P.own1 : 0) * 6];
+                const unsigned long long *const w = halo_in + hb;
                 unsigned long long x[6];
                 Wait wait;
                 for (;;) {
@@ -472,7 +644,7 @@ void k_parts(PartArgs A)
 #pragma unroll
                     for (int k = 0; k < 6; ++k) ready = ready && (unsigned)(x[k] >> 32) == tag;
                     if (__builtin_amdgcn_ballot_w64((lo_side || hi_side) && !ready) == 0ull) break;
-                    if (wait.over()) {
+                    if (wait.pause() && wait_ends(wait, false) != kAllThere) {
                         bad |= kFlagTimeout;
                         break;
                     }
@@ -489,20 +661,33 @@ void k_parts(PartArgs A)
             v1 = n;
         }
     }
+    const PartArgs &B = args_again();
+    const Part &PB = B.parts[blockIdx.x];
+    if (many) {
+        // nothing of a run that did not come to its end is written: the part that finds another missing
+        // in a step leaves, and so do all others in that step or the next
+        __syncthreads();
+        const int stop = s_stop;
+        if (stop == kAlone) run_alone<G, PREC, CL>(bad);
+        if (stop != kAllThere || step < B.n_steps) {
+            raise_flag(B.flags, bad);
+            return;
+        }
+    }
     unsigned long long sp = 0ull;
     if (own) {
-        A.h[cell] = h;
-        A.q[cell] = q;
-        A.z[cell] = z;
-        sp = (unsigned long long)__double_as_longlong(fabs(cell_speed<PREC, CL>(h, q, A.g, K, bad)));
+        B.h[cell] = h;
+        B.q[cell] = q;
+        B.z[cell] = z;
+        sp = (unsigned long long)__double_as_longlong(fabs(cell_speed<PREC, CL>(h, q, B.g, K, bad)));
     }
     // the maximum of the final state, for the host's check of the run
     if (role == G) {
         const unsigned long long m = wave_max_u64(sp);
-        if (lane == 0 && m != 0ull) atomicMax(&A.amax[P.chan << A.amax_shift], m);
+        if (lane == 0 && m != 0ull) atomicMax(&B.amax[PB.chan << B.amax_shift], m);
     }
-    if (P.index == 0 && threadIdx.x == 64 * NW * G) A.t[P.chan] = tc;
-    raise_flag(A.flags, bad);
+    if (PB.index == 0 && threadIdx.x == 64 * NW * G) B.t[PB.chan] = tc;
+    raise_flag(B.flags, bad);
 }
 
 template <int PREC, int NT>

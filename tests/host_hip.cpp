@@ -160,6 +160,8 @@ int parts_per_cu(int, int, int) { return (int)V["per_cu"]; }
 hipError_t launch_parts(const PartArgs &a, int, int, int, int, hipStream_t)
 {
     a.flags[0] |= (unsigned)V["raise"];
+    V["wait"] = (long)a.wait_ticks;
+    V["hold"] = a.hold_part;
     return launched("parts", 1e-3f * (float)V["us_parts"] * (float)a.n_steps);
 }
 int amax_split_of_kernels() { return kAmaxSplitMax; }

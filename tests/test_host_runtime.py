@@ -96,3 +96,17 @@ def test_parts_stay_within_what_the_device_holds(host):
     # channels of one workgroup each wait for none: one per compute unit
     assert in_parts(host, [100] * 32, cus=32, mask=32)
     assert not in_parts(host, [100] * 33, cus=32, mask=32)
+
+
+def test_how_long_parts_wait_for_one_another(host):
+    # about the run's time on one workgroup, in ticks of 10 ns: longer with the steps and the cells, 1 ms at
+    # least, 20 s at most
+    waits = {}
+    for n, steps in [(1800, 1), (1800, 1000), (7000, 1000), (7000, 2**31 - 1)]:
+        h = Host(host, n)
+        assert h.in_parts(steps) and h.count("hold") == -1
+        waits[n, steps] = h.count("wait")
+        h.close()
+    assert waits[1800, 1] == 100_000
+    assert 300_000 < waits[1800, 1000] < waits[7000, 1000] < 4_000_000
+    assert waits[7000, 2**31 - 1] == 2_000_000_000
