@@ -315,7 +315,8 @@ dsve_status dsve_get_cfl_split(const dsve_ctx *ctx, int *split);
  * end cells, also channels of more than 511 cells unless a launch was set; same results, one launch.
  * Those workgroups wait for one another; where they do not come to run together, on a device held by
  * others, one of them does the work of its channel alone, with the same results but in up to 40 times
- * the time. */
+ * the time.  Should one that did come not answer the others for 20 s, which nothing known makes it do, the
+ * run fails with DSVE_E_HIP at dsve_sync, and the arrays and clocks of that channel are those of its start. */
 dsve_status dsve_set_resident(dsve_ctx *ctx, int mode);
 dsve_status dsve_get_resident(const dsve_ctx *ctx, int *active);
 

@@ -1089,6 +1089,9 @@ dsve_status dsve_sync(dsve_ctx *ctx)
     if (ctx->sticky != DSVE_OK) return ctx->sticky;
     unsigned int flags[4];
     HIP_TRY(ctx, hipMemcpy(flags, ctx->d_flags, sizeof flags, hipMemcpyDeviceToHost));
+    // first: what else such a run saw says nothing of the caller's state
+    if (flags[0] & kFlagTimeout)
+        return fail(ctx, DSVE_E_HIP, "a workgroup of a run in one launch did not answer the others for 20 s");
     if (flags[0] & kFlagNonfinite)
         return fail(ctx, DSVE_E_NONFINITE, "non-finite cubic parameters (an overflowed or NaN state)");
     if (flags[0] & kFlagComplex)
@@ -1096,8 +1099,6 @@ dsve_status dsve_sync(dsve_ctx *ctx)
     if (flags[0] & kFlagCoalesce)
         return fail(ctx, DSVE_E_NONHYPERBOLIC,
                     "coalescing eigenvalues at a quadrature node (arccos argument +-1: R^-1 undefined)");
-    if (flags[0] & kFlagTimeout)
-        return fail(ctx, DSVE_E_HIP, "the workgroups of a channel-resident run were not on the device together");
     if (ctx->last_amax_slot >= 0) {
         const int64_t C = ctx->n_channels;
         std::vector<unsigned long long> am(ctx->amax_slot);

@@ -43,7 +43,7 @@ enum { CL_GRASS = LAW_GRASS, CL_GRASS_THR = LAW_GRASS_THR, CL_POWER = LAW_POWER,
 constexpr unsigned kFlagComplex = 1u;    // complex eigenvalues: arccos argument past 1 + tol, or k1 <= 0
 constexpr unsigned kFlagCoalesce = 2u;   // a quadrature node whose arccos argument is +-1 to working
                                          // precision: two eigenvalues equal, R^-1 does not exist
-constexpr unsigned kFlagTimeout = 8u;    // a part of a channel waited in vain for another (k_parts)
+constexpr unsigned kFlagTimeout = 8u;    // a part of a channel waited in vain for another that was there (k_parts)
 constexpr unsigned kFlagNonfinite = 4u;  // a non-finite arccos argument (an overflowed or NaN state)
 
 constexpr int kMaxGauss = 5;

@@ -637,6 +637,7 @@ void k_parts(PartArgs A)
                 const unsigned long long *const w = halo_in + hb;
                 unsigned long long x[6];
                 Wait wait;
+                bool got = true;
                 for (;;) {
                     bool ready = true;
 #pragma unroll
@@ -645,11 +646,15 @@ void k_parts(PartArgs A)
                     for (int k = 0; k < 6; ++k) ready = ready && (unsigned)(x[k] >> 32) == tag;
                     if (__builtin_amdgcn_ballot_w64((lo_side || hi_side) && !ready) == 0ull) break;
                     if (wait.pause() && wait_ends(wait, false) != kAllThere) {
-                        bad |= kFlagTimeout;
+                        got = false;
                         break;
                     }
                 }
-                if (lo_side || hi_side) {
+                if (!got) {
+                    // (read after the next barrier)
+                    if (lane == 0) s_stop = kStalled;
+                    bad |= kFlagTimeout;
+                } else if (lo_side || hi_side) {
                     s_st[0][i] = h = __longlong_as_double((long long)((x[0] << 32) | (unsigned)x[1]));
                     s_st[1][i] = q = __longlong_as_double((long long)((x[2] << 32) | (unsigned)x[3]));
                     s_st[2][i] = z = __longlong_as_double((long long)((x[4] << 32) | (unsigned)x[5]));

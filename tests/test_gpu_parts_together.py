@@ -1,5 +1,6 @@
 """Runs in parts (k_parts) whose parts are not on the device together, forced from the host: one part
-comes late, and another takes its channel over; bitwise the run of all parts.
+comes late, and another takes its channel over, bitwise the run of all parts; or one leaves between two
+steps, and the run ends with an error, its arrays as they were.
 """
 import ctypes
 
@@ -85,3 +86,34 @@ def test_more_launches_than_the_device_takes_whole(dsve):
         c.sync()
         assert same(tuple(x.cpu().numpy() for x in st), ref)
         c.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("step", [1, 7, 8, 16, 19])     # before a maximum, and (8, 16) before cells of a neighbour
+def test_a_part_that_stops_answering(dsve, step, precision):
+    import numpy as np
+    wl = channels([700, 100, 880], seed=3, steps=20)
+    ctx = dsve.Context.from_workload(wl, precision=precision)
+    h, q, z, t = dsve.upload(wl)
+    before = [x.cpu().numpy() for x in (h, q, z, t)]
+    hold(dsve, ctx, 1, step)
+    ctx.adot_step(h, q, z, wl.steps, t)
+    with pytest.raises(dsve.DsveError) as ex:
+        ctx.sync()
+    assert ex.value.status == dsve.E_HIP and "did not answer" in str(ex.value)
+    after = [x.cpu().numpy() for x in (h, q, z, t)]
+    # the channel of one workgroup has run, the others are as they were
+    ref = run(dsve, wl, precision, per_step=True)
+    for a, b, r in zip(after[:3], before[:3], ref[:3]):
+        want = b.copy()
+        want[700:800] = r[700:800]
+        assert np.array_equal(a, want)
+    assert np.array_equal(after[3], [before[3][0], ref[3][1], before[3][2]])
+    # and the context goes on when the error is cleared
+    hold(dsve, ctx, -1)
+    ctx.clear_error()
+    h, q, z, t = dsve.upload(wl)
+    ctx.adot_step(h, q, z, wl.steps, t)
+    ctx.sync()
+    assert same([x.cpu().numpy() for x in (h, q, z, t)], ref)
+    ctx.close()

@@ -24,6 +24,9 @@ def host(tmp_path_factory):
     return ctypes.CDLL(so)
 
 
+E_HIP = -2   # dsve_status
+
+
 class Host:
     """One context of the host build, of one channel or of channels of the given lengths."""
 
@@ -70,6 +73,10 @@ class Host:
         assert self.run(n_steps) == 0
         return self.count("parts") == before + 1
 
+    def error(self):
+        self.lib.dsve_last_error.restype = ctypes.c_char_p
+        return self.call("dsve_last_error")
+
     def close(self):
         assert self.call("dsve_destroy") == 0
 
@@ -110,3 +117,13 @@ def test_how_long_parts_wait_for_one_another(host):
     assert waits[1800, 1] == 100_000
     assert 300_000 < waits[1800, 1000] < waits[7000, 1000] < 4_000_000
     assert waits[7000, 2**31 - 1] == 2_000_000_000
+
+
+def test_a_wait_in_vain_is_what_is_reported(host):
+    # whatever else the run that gave up has flagged: complex 1, coalescing 2, non-finite 4, in vain 8
+    for flags in (8, 12, 15):
+        h = Host(host, 2000, dict(**{"raise": flags}))
+        assert h.in_parts()
+        assert h.call("dsve_sync") == E_HIP
+        assert b"did not answer" in h.error()
+        h.close()
