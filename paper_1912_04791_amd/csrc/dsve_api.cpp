@@ -1272,15 +1272,16 @@ extern "C" dsve_status dsve_autotune(dsve_ctx *ctx, const double *h, const doubl
     // channel-resident runs are timed against the per-step kernels only where the caller
     // left them on
     const bool try_resident = ctx->resident_ok && ctx->resident_mode == 0;
-    const std::string key = tune_key(ctx) + (try_resident ? "|res" : "");
     // longer channels that can run in parts (k_parts) are timed that way too
     const bool try_parts = ctx->n_parts > 0 && !ctx->resident_ok && ctx->resident_mode == 0;
+    const std::string key = tune_key(ctx) + (try_resident ? "|res" : try_parts ? "|parts" : "");
     int tile = 0, bpc = 0, split = 0, resident = ctx->resident_mode, parts = 0;
     if (cache_lookup(cache_path, key, tile, bpc, split, resident, parts)) {
         dsve_status st = dsve_set_launch(ctx, tile, bpc, ctx->graph_steps);
-        ctx->launch_set = parts == 0;
+        ctx->launch_set = !(try_parts && parts != 0);
         if (st == DSVE_OK) st = dsve_set_cfl_split(ctx, split);
-        return st != DSVE_OK ? st : dsve_set_resident(ctx, resident);
+        // (the caller's choice stands where it is not what the entry was tuned for)
+        return st != DSVE_OK || !try_resident ? st : dsve_set_resident(ctx, resident);
     }
 
     // the work already enqueued finishes first and its deferred errors are reported here, so

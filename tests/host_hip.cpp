@@ -15,7 +15,7 @@ using namespace dsve;
 static std::map<std::string, long> V;
 static std::set<const void *> live;
 static hipError_t last = hipSuccess;   // as the runtime keeps it: until it is asked for
-static float clock_ms = 0.f;
+static double clock_ms = 0.0;
 
 static hipError_t give(hipError_t e)
 {
@@ -34,6 +34,7 @@ extern "C" {
 void fake_reset()
 {
     V.clear();
+    clock_ms = 0.0;
     last = hipSuccess;
     V["cus"] = V["mask"] = 256;   // compute units, and those the stream may use
     V["per_cu"] = 1;              // workgroups of k_parts on each
@@ -92,13 +93,13 @@ hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipSt
     std::memcpy(d, s, n);
     return hipSuccess;
 }
-hipError_t hipEventCreate(hipEvent_t *e) { *e = (hipEvent_t) new float(0.f); return hipSuccess; }
-hipError_t hipEventDestroy(hipEvent_t e) { delete (float *)e; return hipSuccess; }
-hipError_t hipEventRecord(hipEvent_t e, hipStream_t) { *(float *)e = clock_ms; return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t *e) { *e = (hipEvent_t) new double(0.0); return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t e) { delete (double *)e; return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t) { *(double *)e = clock_ms; return hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventElapsedTime(float *ms, hipEvent_t a, hipEvent_t b)
 {
-    *ms = *(float *)b - *(float *)a;
+    *ms = (float)(*(double *)b - *(double *)a);
     return hipSuccess;
 }
 hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { V["recording"] = 1; V["recorded"] = 0; return hipSuccess; }

@@ -68,6 +68,9 @@ class Host:
         h, q, z, t = self.ptrs()
         return self.call(f, h, q, z, n_steps, t)
 
+    def autotune(self, cache):
+        return self.call("dsve_autotune", *self.ptrs()[:3], 10, str(cache).encode())
+
     def in_parts(self, n_steps=5):
         before = self.count("parts")
         assert self.run(n_steps) == 0
@@ -126,4 +129,25 @@ def test_a_wait_in_vain_is_what_is_reported(host):
         assert h.in_parts()
         assert h.call("dsve_sync") == E_HIP
         assert b"did not answer" in h.error()
+        h.close()
+
+
+@pytest.mark.parametrize("first", [0, 1])
+def test_one_cache_for_runs_in_parts_and_without(host, tmp_path, first):
+    # where runs in parts are the faster ones, a context that has them switched off neither gets nor sets that
+    cache = tmp_path / "tune.json"
+    for mode in (first, 1 - first, 0, 1):
+        h = Host(host, 2000, dict(us_parts=1, us_step=5))
+        assert h.call("dsve_set_resident", mode) == 0
+        assert h.autotune(cache) == 0
+        assert h.in_parts() == (mode == 0)
+        h.close()
+    assert len(cache.read_text().splitlines()) == 2
+    # and the other way round: the entry says per-step kernels
+    cache = tmp_path / "other.json"
+    for mode in (first, 1 - first, 0, 1):
+        h = Host(host, 2000, dict(us_parts=5, us_step=1))
+        assert h.call("dsve_set_resident", mode) == 0
+        assert h.autotune(cache) == 0
+        assert not h.in_parts()
         h.close()
