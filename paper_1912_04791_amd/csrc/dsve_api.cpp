@@ -1196,6 +1196,11 @@ dsve_status dsve_test_hold_part(dsve_ctx *ctx, int part, int step, int wait_us)
 
 // ---------------------------------------------------------------------------
 // Autotuner.
+
+// Part of every key, raised when the kernels that a launch configures change: an entry tuned for others is
+// not used.  (Without one: tiles of the flat edge space, 2: segments and runs in parts.)
+constexpr int kTuneVersion = 2;
+
 static std::string tune_key(const dsve_ctx *ctx)
 {
     // problem shape: channel count and a coarse histogram of channel lengths (log2 buckets)
@@ -1207,7 +1212,7 @@ static std::string tune_key(const dsve_ctx *ctx)
         ++hist[b];
     }
     std::ostringstream os;
-    os << ctx->arch << "|cu" << ctx->cus << "|p" << ctx->precision << "|law" << ctx->law << "|cl" << ctx->cl
+    os << ctx->arch << "|v" << kTuneVersion << "|cu" << ctx->cus << "|p" << ctx->precision << "|law" << ctx->law << "|cl" << ctx->cl
        << "|G" << ctx->G << "|C"
        << ctx->n_channels << "|N" << ctx->n_cells << "|h";
     for (int b = 0; b < 40; ++b)

@@ -56,7 +56,7 @@ hipError_t hipGetDeviceProperties(hipDeviceProp_t *p, int)
 {
     std::memset(p, 0, sizeof *p);
     p->multiProcessorCount = (int)V["cus"];
-    std::strcpy(p->gcnArchName, "gfx950");
+    std::strcpy(p->gcnArchName, "gfx950:sramecc+:xnack-");
     return hipSuccess;
 }
 hipError_t hipDeviceSynchronize(void) { return hipSuccess; }

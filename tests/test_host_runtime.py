@@ -151,3 +151,37 @@ def test_one_cache_for_runs_in_parts_and_without(host, tmp_path, first):
         assert h.autotune(cache) == 0
         assert not h.in_parts()
         h.close()
+
+
+def launch_of(h):
+    v = [ctypes.c_int() for _ in range(3)]
+    assert h.call("dsve_get_launch", *[ctypes.byref(x) for x in v]) == 0
+    return tuple(x.value for x in v)
+
+
+@pytest.mark.parametrize("n_cells", [2000, 20_000])
+def test_entries_of_other_kernels_are_not_used(host, tmp_path, n_cells):
+    # a cache written for the kernels of tiles, whose launches mean something else
+    cache = tmp_path / "tune.json"
+    bucket = n_cells.bit_length() - 1
+    old = (f'{{"key": "gfx950:sramecc+:xnack-|cu256|p0|law0|cl0|G3|C1|N{n_cells}|h{bucket}:1,", "tile": 64, '
+           '"blocks_per_cu": 7, "cfl_split": 2, "resident_mode": 0, "ms_per_step": 0.1}\n')
+    cache.write_text(old)
+    h = Host(host, n_cells, dict(us_parts=1, us_step=5))
+    assert h.autotune(cache) == 0
+    assert launch_of(h)[1] != 7 and h.count("captures") > 0
+    assert h.in_parts() == (n_cells == 2000)
+    h.close()
+    # what the file held stays, and what was found is used from now on
+    lines = cache.read_text().splitlines()
+    assert len(lines) == 2 and lines[0] + "\n" == old
+    h = Host(host, n_cells)
+    assert h.autotune(cache) == 0 and h.count("captures") == 0
+    h.close()
+
+
+def test_the_shipped_cache_is_for_these_kernels(host):
+    h = Host(host, 1 << 20)
+    assert h.autotune(os.path.join(ROOT, "paper_1912_04791_amd", "tuned_launch.json")) == 0
+    assert h.count("captures") == 0 and launch_of(h)[:2] == (128, 16)
+    h.close()
