@@ -301,7 +301,10 @@ static dsve_status plan_parts(dsve_ctx *c, std::vector<Part> &table)
     if (cut) {
         uint32_t mask[32] = {0};
         int on = 0;
-        if (hipExtStreamGetCUMask(c->stream, 32, mask) != hipSuccess) return DSVE_OK;
+        if (hipExtStreamGetCUMask(c->stream, 32, mask) != hipSuccess) {
+            (void)hipGetLastError();   // not an error of the launch that would report it next
+            return DSVE_OK;
+        }
         for (uint32_t m : mask) on += __builtin_popcount(m);
         if (on < c->cus) return DSVE_OK;
     }
@@ -423,7 +426,10 @@ static dsve_status setup(dsve_ctx *c, void *stream)
     HIP_TRY(c, launch_fill_u64(c->d_amax, words + 4, 0ull, c->stream));
     // the device address of the static scratch of adot_step_noalloc, looked up once per device
     // (a failure leaves it null: that entry point then reports it, the others do not use it)
-    if (noalloc_scratch(c->device, &c->scratch) != hipSuccess) c->scratch = nullptr;
+    if (noalloc_scratch(c->device, &c->scratch) != hipSuccess) {
+        c->scratch = nullptr;
+        (void)hipGetLastError();
+    }
     st = build_table(c, c->tile, c->blocks_per_cu);
     if (st != DSVE_OK) return st;
     HIP_TRY(c, hipStreamSynchronize(c->stream));

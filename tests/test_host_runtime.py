@@ -185,3 +185,14 @@ def test_the_shipped_cache_is_for_these_kernels(host):
     assert h.autotune(os.path.join(ROOT, "paper_1912_04791_amd", "tuned_launch.json")) == 0
     assert h.count("captures") == 0 and launch_of(h)[:2] == (128, 16)
     h.close()
+
+
+def test_failures_that_are_tolerated_leave_no_error_behind(host):
+    # no CU mask to be had: the per-step kernels; no static scratch: only the call that needs it says so
+    h = Host(host, 2000, dict(mask_error=1))
+    assert h.status == 0 and not h.in_parts() and h.call("dsve_sync") != E_HIP
+    h.close()
+    h = Host(host, 20_000, dict(scratch_error=1))
+    assert h.status == 0 and h.run(5) == 0
+    assert h.run(5, "adot_step_noalloc") == E_HIP and b"static scratch" in h.error()
+    h.close()
