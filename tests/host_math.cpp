@@ -1,0 +1,34 @@
+// The arithmetic of dsve_math.hpp compiled for the host, for tests: the hardware estimates stand in as
+// correctly rounded values, off by a relative error that the test chooses.
+#include <hip/hip_runtime.h>
+#include <math.h>
+#include <stdint.h>
+#include <string.h>
+
+static double off = 0.0;   // relative error of the estimates
+static float __builtin_amdgcn_rcpf(float x) { return (float)((1.0 / x) * (1.0 + off)); }
+static float __builtin_amdgcn_rsqf(float x) { return (float)((1.0 / sqrt((double)x)) * (1.0 + off)); }
+static float __builtin_amdgcn_sqrtf(float x) { return (float)(sqrt((double)x) * (1.0 + off)); }
+static float __builtin_amdgcn_exp2f(float x) { return (float)(exp2((double)x) * (1.0 + off)); }
+static float __builtin_amdgcn_logf(float x) { return (float)log2((double)x); }
+static double __builtin_amdgcn_rcp(double x) { return (double)(float)(1.0 / x) * (1.0 + off); }
+static double __builtin_amdgcn_rsq(double x) { return (double)(float)(1.0 / sqrt(x)) * (1.0 + off); }
+static uint64_t __builtin_amdgcn_ballot_w64(bool b) { return b; }   // a wave of one lane
+static double __longlong_as_double(long long v) { double d; memcpy(&d, &v, 8); return d; }
+static long long __double_as_longlong(double d) { long long v; memcpy(&v, &d, 8); return v; }
+
+#include "dsve_math.hpp"
+
+using namespace dsve;
+
+#define EACH(NAME, EXPR) \
+    void NAME(const double *in, double *out, long n, double err) \
+    { \
+        off = err; \
+        for (long i = 0; i < n; ++i) { const double a = in[i]; out[i] = EXPR; } \
+    }
+extern "C" {
+EACH(host_rcbrt, rcbrt_h(a))
+EACH(host_pow_1p1, pow_1p1(a))
+EACH(host_sqrt, m_sqrt(a))
+}

@@ -196,3 +196,18 @@ def test_failures_that_are_tolerated_leave_no_error_behind(host):
     assert h.status == 0 and h.run(5) == 0
     assert h.run(5, "adot_step_noalloc") == E_HIP and b"static scratch" in h.error()
     h.close()
+
+
+@pytest.mark.parametrize("n_cells,split,want,look", [
+    (23_940, 0, 1, 0), (23_941, 0, 4, 0),          # 95 and 96 workgroups on the channel: 4 sub-slots from 96
+    (100_548, 0, 4, 0), (100_549, 0, 4, 1),        # 99 and 100 merges to a sub-slot: a look before from 100,
+    (516_096, 0, 4, 1), (516_097, 0, 4, 0),        # but past 8192 segments (more than a round of waves)
+    (755_748, 1, 1, 0), (755_749, 1, 1, 1),        # from 3000
+])
+def test_sub_slots_and_the_look_before_a_merge(host, n_cells, split, want, look):
+    h = Host(host, n_cells)
+    assert h.call("dsve_set_cfl_split", split) == 0
+    got = ctypes.c_int()
+    assert h.call("dsve_get_cfl_split", ctypes.byref(got)) == 0 and got.value == want
+    assert h.run(1) == 0 and h.count("look") == look
+    h.close()
