@@ -147,13 +147,15 @@ __device__ __forceinline__ float pow_1p1(float a) { return m_pow(a, 1.1f); }
 // y <- y (1 + e/3 + 2e^2/9), e = 1 - a y^3, the Taylor terms of (1 - e)^(-1/3): it leaves 14/81 e^3,
 // below 1e-17; no division.  (Two Newton steps, each to about 2 e^2, took ten FP64 instructions, this
 // takes six.)
-__device__ __forceinline__ double rcbrt_h(double a)
+__device__ __forceinline__ double rcbrt_h(double a, float af)   // af: a in FP32
 {
-    const double y = (double)__builtin_amdgcn_exp2f(-(1.0f / 3.0f) * __builtin_amdgcn_logf((float)a));
+    const double y = (double)__builtin_amdgcn_exp2f(-(1.0f / 3.0f) * __builtin_amdgcn_logf(af));
     const double e = fma(-a, y * y * y, 1.0);
     return fma(y * e, fma(e, 2.0 / 9.0, 1.0 / 3.0), y);
 }
-__device__ __forceinline__ double m_rcbrt(double a) { return rcbrt_h(a); }
+__device__ __forceinline__ double rcbrt_h(double a) { return rcbrt_h(a, (float)a); }
+// (a depth below FP32's range must not give an infinite estimate, which would end as an infinite b)
+__device__ __forceinline__ double m_rcbrt(double a) { return rcbrt_h(a, fmaxf((float)a, 1.17549435e-38f)); }
 __device__ __forceinline__ float m_rcbrt(float a)
 {
     return __builtin_amdgcn_exp2f(-(1.0f / 3.0f) * __builtin_amdgcn_logf(a));

@@ -31,4 +31,14 @@ extern "C" {
 EACH(host_rcbrt, rcbrt_h(a))
 EACH(host_pow_1p1, pow_1p1(a))
 EACH(host_sqrt, m_sqrt(a))
+// b at depth a and |Fr| = 1/2, laws of the Shields stress (K_s = 40, d50 = 0.3 mm, S_g = 2.6)
+static Closure shields(double lp0, double lp1)
+{
+    Closure K{};
+    K.lp0 = lp0;
+    K.lp1 = lp1;
+    return K;
+}
+EACH(host_mpm, (law_b<CL_MPM, double>(shields(1.3, 2e-4), a, 0.5 * sqrt(9.81 * a) * a, 1.0 / a)))
+EACH(host_vanrijn, (law_b<CL_VANRIJN, double>(shields(26.0, 4e-6), a, 0.5 * sqrt(9.81 * a) * a, 1.0 / a)))
 }

@@ -54,3 +54,14 @@ def test_square_root(roots):
     a = np.concatenate([np.logspace(-12, 6, 20001), np.linspace(0.5, 4.0, 2001)])
     exact = np.sqrt(a.astype(np.longdouble))
     assert worst(roots, "host_sqrt", a, exact, (0.0, 2.0 ** -24, -2.0 ** -24)) <= 3
+
+
+def test_depths_outside_the_range_of_the_estimate(roots):
+    # no transport where the stress vanishes with the depth, however small, and finite where it is large
+    a = np.concatenate([np.logspace(-290, -10, 1401), np.logspace(30, 90, 301)])
+    for name in ("host_mpm", "host_vanrijn"):
+        f = getattr(roots, name)
+        f.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_long, ctypes.c_double]
+        out = np.empty_like(a)
+        f(a.ctypes.data, out.ctypes.data, a.size, 0.0)
+        assert np.isfinite(out).all() and (out[a < 1] == 0).all()
