@@ -77,6 +77,8 @@ struct dsve_ctx {
     int table_tile = 0;
     Segment *d_segments = nullptr;     // otherwise: the segments, of at most seg_tiles tiles each
     int64_t n_segments = 0, seg_tiles = 0;
+    bool table_held = false;           // the caller captured launches that read the present work table
+    std::vector<void *> held;          // such tables replaced since, kept until the context ends
 
     // captured graphs, valid for the buffers and launch in g_key / g_*: the main graph of
     // graph_steps steps, and graphs of the remainders n % graph_steps of recent run lengths
@@ -197,6 +199,25 @@ static void free_graph(dsve_ctx *c)
     c->g_steps = 0;
 }
 
+// The work table at p has been replaced.  A graph that the caller captured over a run reads it in every
+// replay, so it stays then.
+static void drop_table(dsve_ctx *c, void *p)
+{
+    if (!p) return;
+    if (c->table_held) c->held.push_back(p);
+    else (void)hipFree(p);
+    c->table_held = false;
+}
+
+// To be called before launches that read the work table.
+static void note_capture(dsve_ctx *c)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (!c->stream || c->table_held) return;   // (the null stream cannot be captured)
+    if (hipStreamIsCapturing(c->stream, &status) != hipSuccess) (void)hipGetLastError();
+    c->table_held = status == hipStreamCaptureStatusActive;
+}
+
 static dsve_status build_tile_table(dsve_ctx *c, int tile)
 {
     if (c->d_tile_chan && c->table_tile == tile) return DSVE_OK;
@@ -211,7 +232,7 @@ static dsve_status build_tile_table(dsve_ctx *c, int tile)
         while (ch + 1 < c->n_channels && g0 >= c->h_eoff[ch + 1]) ++ch;
         tab[k] = (int32_t)ch;
     }
-    if (c->d_tile_chan) (void)hipFree(c->d_tile_chan);
+    drop_table(c, c->d_tile_chan);
     c->d_tile_chan = nullptr;
     HIP_TRY(c, hipMalloc(&c->d_tile_chan, sizeof(int32_t) * nt));
     HIP_TRY(c, hipMemcpy(c->d_tile_chan, tab.data(), sizeof(int32_t) * nt, hipMemcpyHostToDevice));
@@ -258,7 +279,7 @@ static dsve_status build_segments(dsve_ctx *c, int tile, int blocks_per_cu)
         }
     }
     if (seg.size() >= ((size_t)1 << 31)) return fail(c, DSVE_E_ARG, "too many segments for this launch");
-    if (c->d_segments) (void)hipFree(c->d_segments);
+    drop_table(c, c->d_segments);
     c->d_segments = nullptr;
     HIP_TRY(c, hipMalloc(&c->d_segments, sizeof(Segment) * seg.size()));
     HIP_TRY(c, hipMemcpy(c->d_segments, seg.data(), sizeof(Segment) * seg.size(), hipMemcpyHostToDevice));
@@ -447,6 +468,7 @@ static void release(dsve_ctx *c)
     (void)hipFree(c->d_amax);
     (void)hipFree(c->d_tile_chan);
     (void)hipFree(c->d_segments);
+    for (void *p : c->held) (void)hipFree(p);
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
     delete c;
 }
@@ -962,6 +984,7 @@ static dsve_status run_steps(dsve_ctx *ctx, double *h, double *q, double *z, int
         st = ensure_graphs(ctx, h, q, z, t, n_steps);
         if (st != DSVE_OK) return st;
     }
+    note_capture(ctx);
     const RunBufs b = ctx_bufs(ctx);
     const bool from_copy = starts_from_copy(ctx, n_steps);
     st = start_run(ctx, b, n_steps, h, q, z, t);
@@ -1068,6 +1091,7 @@ dsve_status adot_step_noalloc(dsve_ctx *ctx, double *h, double *q, double *z, in
     if (ctx->packed ? (!ctx->d_tile_chan || ctx->table_tile != ctx->tile)
                     : (!ctx->d_segments || ctx->seg_tiles != segment_length(ctx, ctx->tile, ctx->blocks_per_cu)))
         return fail(ctx, DSVE_E_HIP, "adot_step_noalloc: no work table for the current launch");
+    note_capture(ctx);
     const bool from_copy = starts_from_copy(ctx, n_steps);
     dsve_status st = start_run(ctx, b, n_steps, h, q, z, t_dev);
     if (st != DSVE_OK) return st;

@@ -83,6 +83,7 @@ hipError_t hipMalloc(void **p, size_t n)
 }
 hipError_t hipFree(void *p)
 {
+    V["freed"] = (long)p;
     live.erase(p);
     std::free(p);
     return hipSuccess;
@@ -125,7 +126,7 @@ namespace dsve {
 
 hipError_t launch_step(const StepArgs &a, int, int, int, int, int, hipStream_t)
 {
-    V["segments"] = (long)a.segments;
+    V["table"] = a.segments ? (long)a.segments : (long)a.tile_chan;
     V["look"] = a.amax_check;
     if (V["recording"]) {
         ++V["recorded"];

@@ -30,10 +30,11 @@ E_HIP = -2   # dsve_status
 class Host:
     """One context of the host build, of one channel or of channels of the given lengths."""
 
-    def __init__(self, lib, lengths, fake=None, reset=True, **kw):
+    def __init__(self, lib, lengths, fake=None, reset=True, stream=None, **kw):
         from paper_1912_04791_amd import dsve
         self.lib, self.ctx = lib, ctypes.c_void_p()
         lib.fake_get.restype = ctypes.c_long
+        lib.fake_live.argtypes = [ctypes.c_long]
         lib.fake_set.argtypes = [ctypes.c_char_p, ctypes.c_long]
         if reset:
             lib.fake_reset()
@@ -42,12 +43,13 @@ class Host:
         n = int(np.sum(lengths))
         p = dsve.make_params(dx=0.1, **kw)
         if np.ndim(lengths) == 0:
-            st = lib.dsve_init(ctypes.byref(self.ctx), ctypes.byref(p), ctypes.c_int64(n), None)
+            st = lib.dsve_init(ctypes.byref(self.ctx), ctypes.byref(p), ctypes.c_int64(n), ctypes.c_void_p(stream))
         else:
             C = len(lengths)
             off = (ctypes.c_int64 * (C + 1))(*np.concatenate([[0], np.cumsum(lengths)]).tolist())
             ch = dsve.make_channels([0.01] * C, [0.4] * C, [0.1] * C, [0] * C, [0] * C)
-            st = lib.dsve_batch_init(ctypes.byref(self.ctx), ctypes.c_int64(C), off, ch, ctypes.byref(p), None)
+            st = lib.dsve_batch_init(ctypes.byref(self.ctx), ctypes.c_int64(C), off, ch, ctypes.byref(p),
+                                     ctypes.c_void_p(stream))
         self.status = st
         self.state = [np.ones(n) for _ in range(3)]
         self.t = np.zeros(np.size(lengths))
@@ -211,3 +213,24 @@ def test_sub_slots_and_the_look_before_a_merge(host, n_cells, split, want, look)
     assert h.call("dsve_get_cfl_split", ctypes.byref(got)) == 0 and got.value == want
     assert h.run(1) == 0 and h.count("look") == look
     h.close()
+
+
+@pytest.mark.parametrize("f", ["adot_step_noalloc", "adot_step_batched"])
+@pytest.mark.parametrize("lengths", [[20_000], [30] * 700])     # segments; the packed kernel's tiles
+def test_a_captured_work_table_outlives_a_new_launch(host, lengths, f):
+    # a graph that the caller captured over a run reads the run's work table whenever it is replayed
+    h = Host(host, lengths, stream=64)
+    assert h.call("dsve_set_resident", 1) == 0
+    h.set("capturing", 1)
+    assert h.run(3, f) == 0
+    h.set("capturing", 0)
+    captured = h.count("table")
+    assert h.call("dsve_set_launch", 64, 1, 60) == 0
+    assert h.run(3, "adot_step_noalloc") == 0
+    second = h.count("table")
+    assert second != captured and host.fake_live(captured) == host.fake_live(second) == 1
+    # one that no graph reads goes at once, and all of them with the context
+    assert h.call("dsve_set_launch", 128, 1, 60) == 0
+    assert host.fake_live(captured) == 1 and h.count("freed") == second
+    h.close()
+    assert host.fake_live(captured) == 0
