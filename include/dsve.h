@@ -220,8 +220,8 @@ dsve_status cfl_reduce(dsve_ctx *ctx, const double *h, const double *q, const do
  * channel-resident or runs in parts (dsve_set_resident).  With graph_steps > 0 (dsve_set_launch) the steps
  * are replayed from captured HIP graphs: n_steps / graph_steps replays of a graph of
  * graph_steps steps, then one replay of a graph of the remaining n_steps % graph_steps
- * steps; the graphs are captured at the first run that needs them (the second on the same
- * arrays, unless a launch was set) and kept while the arrays and the launch configuration
+ * steps; the graphs are captured at the first run that needs them (a run of fewer than 300
+ * steps on new arrays does not, unless a launch was set) and kept while the arrays and the launch configuration
  * stay the same (dsve_prepare_run captures them ahead).  *t_dev (device) is
  * increased by the sum of the time steps.  The result is in (h, q, z) when the
  * enqueued work completes, bitwise independent of the launch configuration. */

@@ -942,6 +942,8 @@ static dsve_status run_parts(dsve_ctx *ctx, double *h, double *q, double *z, int
     return DSVE_OK;
 }
 
+constexpr int kDirectSteps = 300;   // first runs on new arrays launch fewer steps than these directly
+
 static dsve_status run_steps(dsve_ctx *ctx, double *h, double *q, double *z, int n_steps, double *t)
 {
     if (ctx->sticky != DSVE_OK) return ctx->sticky;
@@ -974,9 +976,12 @@ static dsve_status run_steps(dsve_ctx *ctx, double *h, double *q, double *z, int
     // Steps replay graphs, captured before any work of the run is enqueued, but for the first run on
     // arrays that no graph was captured for, unless a launch was asked for: launching its steps one by
     // one takes as long on the device (20 000 cells, 60 steps: 320 us against 312), and capturing them
-    // longer than running them (2^20 cells, 20 steps: 0.32 ms on top of 0.42).
+    // longer than running them (2^20 cells, 20 steps: 0.32 ms on top of 0.42).  From 300 steps on a first
+    // run replays too: the capture is paid for by then, and launching holds the calling thread for most of
+    // the run (9000 cells, launched and captured: 120 steps 0.66 and 0.75 ms, 300 steps 1.62 and 1.58,
+    // 600 steps 3.3 and 2.9, 2400 steps 11.5 and 11.1, of which 9.2 and 1.9 before the call returns).
     const void *const key[4] = {h, q, z, t};
-    const bool known = ctx->launch_set || std::equal(key, key + 4, ctx->last_key) ||
+    const bool known = ctx->launch_set || n_steps >= kDirectSteps || std::equal(key, key + 4, ctx->last_key) ||
                        (ctx->g_keyed && std::equal(key, key + 4, ctx->g_key));
     std::copy(key, key + 4, ctx->last_key);
     const bool replay = ctx->graph_steps > 0 && known;

@@ -234,3 +234,15 @@ def test_a_captured_work_table_outlives_a_new_launch(host, lengths, f):
     assert host.fake_live(captured) == 1 and h.count("freed") == second
     h.close()
     assert host.fake_live(captured) == 0
+
+
+def test_a_long_first_run_replays_graphs(host):
+    # launching every step holds the caller for the length of the run; short first runs are not worth a capture
+    for n_steps, captures, graphs, steps in [(60, 0, 0, 60), (299, 0, 0, 299), (300, 1, 5, 0), (3001, 2, 51, 0)]:
+        h = Host(host, 20_000)
+        assert h.run(n_steps) == 0
+        assert (h.count("captures"), h.count("graphs"), h.count("steps")) == (captures, graphs, steps)
+        # known arrays: graphs
+        assert h.run(n_steps) == 0
+        assert h.count("graphs") == graphs + -(-n_steps // 60) and h.count("steps") == steps
+        h.close()
