@@ -120,19 +120,45 @@ void k_resident(ResidentArgs A)
 }
 
 // ---------------------------------------------------------------------------
-// Node terms and their sums for each arithmetic, as 64-bit words for the exchange through LDS.
+// Node terms for each arithmetic, as 64-bit words for the exchange through LDS.
 template <int PREC> struct NodeOf;
 template <> struct NodeOf<PREC_FP64> {
     using T = Terms64;
     static constexpr int words = 8;
+    static __device__ __forceinline__ void pack(const T &v, double w[words])
+    {
+        w[0] = v.pb, w[1] = v.lam, w[2] = v.p2a, w[3] = v.p2b;
+        w[4] = v.s1a, w[5] = v.s1b, w[6] = v.s2a, w[7] = v.s2b;
+    }
+    static __device__ __forceinline__ T unpack(const double w[words])
+    {
+        return T{w[0], w[1], w[2], w[3], w[4], w[5], w[6], w[7]};
+    }
 };
 template <> struct NodeOf<PREC_MIXED> {
     using T = TermsF;
     static constexpr int words = 5;
+    static __device__ __forceinline__ double two(float a, float b) { return __hiloint2double(__float_as_int(b), __float_as_int(a)); }
+    static __device__ __forceinline__ float lo(double w) { return __int_as_float(__double2loint(w)); }
+    static __device__ __forceinline__ float hi(double w) { return __int_as_float(__double2hiint(w)); }
+    static __device__ __forceinline__ void pack(const T &v, double w[words])
+    {
+        w[0] = two(v.wcc, v.A1n), w[1] = two(v.wc, v.A2n), w[2] = two(v.wcP, v.B0), w[3] = two(v.wccP, v.B1);
+        w[4] = two(v.B2, 0.0f);
+    }
+    static __device__ __forceinline__ T unpack(const double w[words])
+    {
+        return T{lo(w[0]), hi(w[0]), lo(w[1]), hi(w[1]), lo(w[2]), hi(w[2]), lo(w[3]), hi(w[3]), lo(w[4])};
+    }
 };
 template <> struct NodeOf<PREC_DOT> {
     using T = TermsDot;
     static constexpr int words = 6;
+    static __device__ __forceinline__ void pack(const T &v, double w[words])
+    {
+        w[0] = v.a[0], w[1] = v.a[1], w[2] = v.a[2], w[3] = v.aa[0], w[4] = v.aa[1], w[5] = v.aa[2];
+    }
+    static __device__ __forceinline__ T unpack(const double w[words]) { return T{{w[0], w[1], w[2]}, {w[3], w[4], w[5]}}; }
 };
 
 // Node K of the edge.
@@ -178,10 +204,10 @@ __device__ __forceinline__ void terms_to_fluct(const double (*t)[NodeOf<PREC>::w
     T v[G];
 #pragma unroll
     for (int k = 0; k < G; ++k) {
-        union { T v; double w[NodeOf<PREC>::words]; } u;
+        double w[NodeOf<PREC>::words];
 #pragma unroll
-        for (int j = 0; j < NodeOf<PREC>::words; ++j) u.w[j] = t[k][j][slot];
-        v[k] = u.v;
+        for (int j = 0; j < NodeOf<PREC>::words; ++j) w[j] = t[k][j][slot];
+        v[k] = NodeOf<PREC>::unpack(w);
     }
     if constexpr (PREC == PREC_FP64) {
         bool ok = true;
@@ -538,10 +564,11 @@ void k_parts(PartArgs A)
                 if (ci.bcr == BC_DIRICHLET) zR = ghost_z(ci.bcr, ci.br, zR, s_tc);
             }
             if (role < G) {
-                union { typename NodeOf<PREC>::T v; double w[NWORDS]; } u;
-                u.v = node_terms<G, PREC, CL>(role, hL, qL, zL, hR, qR, zR, A.g, K, edge_bad);
+                const typename NodeOf<PREC>::T v = node_terms<G, PREC, CL>(role, hL, qL, zL, hR, qR, zR, A.g, K, edge_bad);
+                double w[NWORDS];
+                NodeOf<PREC>::pack(v, w);
 #pragma unroll
-                for (int j = 0; j < NWORDS; ++j) s_t[role][j][slot] = u.w[j];
+                for (int j = 0; j < NWORDS; ++j) s_t[role][j][slot] = w[j];
             } else {
                 E = edge64(hL, qL, zL, hR, qR, zR, A.g);
                 if (ci.fric > 0.0) fs = friction_source(h, q, A.g, ci.fric);
