@@ -927,6 +927,7 @@ static dsve_status run_parts(dsve_ctx *ctx, double *h, double *q, double *z, int
     a.ch = ctx->d_ch; a.parts = ctx->d_parts; a.box = ctx->d_amax + 3 * ctx->amax_slot; a.amax = ctx->d_amax;
     a.flags = ctx->d_flags;
     a.n_parts = (int32_t)ctx->n_parts;
+    a.n_channels = (int32_t)ctx->n_channels;
     a.n_steps = n_steps;
     a.amax_shift = ctx->amax_sh;
     a.g = ctx->g;

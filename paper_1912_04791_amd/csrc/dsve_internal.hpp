@@ -250,6 +250,7 @@ struct PartArgs {
     unsigned long long *amax;    // as ResidentArgs, zero at the start
     unsigned int *flags;
     int32_t n_parts;             // P
+    int32_t n_channels;          // fewer: some channel is cut
     int32_t n_steps;
     int32_t amax_shift;
     double g;

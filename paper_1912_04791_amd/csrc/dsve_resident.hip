@@ -416,24 +416,28 @@ __device__ __forceinline__ void run_alone(unsigned &bad)
 // exchange of D^+ with the lane above by a DPP move, and the update: lane l of its wave w takes edge
 // 63 w + l and updates cell 63 w + l - 1, as in k_step.  Two barriers per step.
 //
+// A channel longer than one workgroup holds is cut into parts, which take the maximum of their CFL
+// maxima through mailboxes once a step (its latency runs beside the nodes), and keep kPartHalo cells of
+// their neighbours on either side, of which every step spoils one, refreshed every kPartHalo steps.
+//
 // Parts wait for one another, so they all have to be on the chip.  Each counts itself in at its start, at
 // no cost but an atomic's way there and back beside the first loads; should one be missing when the others
 // have waited for it about as long as the run takes on one workgroup (wait_ticks), one of them takes the
 // channel over (fate_of, run_alone) and the rest end.  From the first step's maxima on all are there.
 //
-// A channel longer than one workgroup holds is cut into parts, which take the maximum of their CFL
-// maxima through mailboxes once a step (its latency runs beside the nodes), and keep kPartHalo cells of
-// their neighbours on either side, of which every step spoils one, refreshed every kPartHalo steps.
-//
 // Bound by latency: of the 4500 cycles of a step of 17 parts about 2500 pass between the post of a
 // part's maximum and the last part's arrival, beside them the nodes; the rest is the speeds' chain
 // before it, the update after it, and the barriers.  The waves of role G run at raised priority: they
 // share SIMDs with node waves and were held up by them (1.72 -> 1.37 us a step for 100 cells).  One
-// channel, per step, against one workgroup per channel or a launch per step: 100 cells with friction
-// 1.7 -> 1.32 us, 500 cells 2.5 -> 1.9 us, 1800 cells 4.7 -> 1.8 us, 7000 cells 5.2 -> 1.95 us; 100
-// cells with the numerical eigensolver 14.5 -> 6.6 us.  At 128 registers per lane (two workgroups to a
-// compute unit) it spills and takes half as long again.
-template <int G, int PREC, int CL>
+// channel, per step, against one workgroup per channel or a launch per step: 100 cells 1.6 -> 0.95 us, 500
+// cells 2.6 -> 1.7 us, 1800 cells 4.7 -> 1.8 us, 7000 cells 5.2 -> 1.9 us; 100 cells with the numerical
+// eigensolver 13.4 -> 5.9 us.  At 128 registers per lane (two workgroups to a compute unit) it spills and
+// takes half as long again.
+//
+// CUT: some channel of the context is cut.  Without, the kernel has nothing of the exchange between parts,
+// whose values took registers and scalar moves in every step even of runs that exchange nothing: 100 cells
+// 1.23 -> 0.96 us a step, with one node 1.14 -> 0.92, where k_resident took 1.05.
+template <int G, int PREC, int CL, bool CUT>
 __global__ __launch_bounds__(kPartThreads, 2)
 void k_parts(PartArgs A)
 {
@@ -460,7 +464,7 @@ void k_parts(PartArgs A)
     asm volatile("v_mov_b32 %0, 0" : "=v"(vzero));
     const ChanInfo ci = A.ch[P.chan + vzero];
     const Closure K = closure_of(ci);
-    const bool cutL = (P.cut & 1) != 0, cutR = (P.cut & 2) != 0, many = P.n_parts > 1;
+    const bool cutL = CUT && (P.cut & 1) != 0, cutR = CUT && (P.cut & 2) != 0, many = CUT && P.n_parts > 1;
     const bool ring = ci.bcl == BC_PERIODIC && !many;
     double h = 0.0, q = 0.0, z = 0.0;
     int64_t cell = 0;
@@ -700,7 +704,8 @@ void k_parts(PartArgs A)
         // in a step leaves, and so do all others in that step or the next
         __syncthreads();
         const int stop = s_stop;
-        if (stop == kAlone) run_alone<G, PREC, CL>(bad);
+        if constexpr (CUT)
+            if (stop == kAlone) run_alone<G, PREC, CL>(bad);
         if (stop != kAllThere || step < B.n_steps) {
             raise_flag(B.flags, bad);
             return;
@@ -750,10 +755,10 @@ hipError_t launch_resident(const ResidentArgs &a, int precision, int G, int cl, 
     return hipErrorInvalidValue;
 }
 
-template <int PREC>
+template <int PREC, bool CUT>
 static hipError_t launch_parts_prec(const PartArgs &a, int G, int cl, int grid, hipStream_t s)
 {
-#define DSVE_LAUNCH_PARTS(GG, CC) hipLaunchKernelGGL((k_parts<GG, PREC, CC>), dim3(grid), dim3(kPartThreads), 0, s, a)
+#define DSVE_LAUNCH_PARTS(GG, CC) hipLaunchKernelGGL((k_parts<GG, PREC, CC, CUT>), dim3(grid), dim3(kPartThreads), 0, s, a)
     DSVE_DISPATCH_G_CL(G, cl, DSVE_LAUNCH_PARTS)
 #undef DSVE_LAUNCH_PARTS
     return hipGetLastError();
@@ -763,7 +768,7 @@ template <int PREC>
 static hipError_t parts_occupancy(int G, int cl, int &n)
 {
     hipError_t e = hipErrorInvalidValue;
-#define DSVE_OCC(GG, CC) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_parts<GG, PREC, CC>, kPartThreads, 0)
+#define DSVE_OCC(GG, CC) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_parts<GG, PREC, CC, true>, kPartThreads, 0)
     DSVE_DISPATCH_G_CL(G, cl, DSVE_OCC)
 #undef DSVE_OCC
     return e;
@@ -779,13 +784,20 @@ int parts_per_cu(int precision, int G, int cl)
     return e == hipSuccess && n > 0 ? n : 0;
 }
 
+template <bool CUT>
+static hipError_t launch_parts_cut(const PartArgs &a, int precision, int G, int cl, int grid, hipStream_t stream)
+{
+    if (precision == PREC_FP64) return launch_parts_prec<PREC_FP64, CUT>(a, G, cl, grid, stream);
+    if (precision == PREC_MIXED) return launch_parts_prec<PREC_MIXED, CUT>(a, G, cl, grid, stream);
+    if (precision == PREC_DOT) return launch_parts_prec<PREC_DOT, CUT>(a, G, cl, grid, stream);
+    return hipErrorNotSupported;
+}
+
 hipError_t launch_parts(const PartArgs &a, int precision, int G, int cl, int grid, hipStream_t stream)
 {
     if (grid < 1 || a.n_steps < 1) return hipErrorInvalidValue;
-    if (precision == PREC_FP64) return launch_parts_prec<PREC_FP64>(a, G, cl, grid, stream);
-    if (precision == PREC_MIXED) return launch_parts_prec<PREC_MIXED>(a, G, cl, grid, stream);
-    if (precision == PREC_DOT) return launch_parts_prec<PREC_DOT>(a, G, cl, grid, stream);
-    return hipErrorNotSupported;
+    return a.n_channels < a.n_parts ? launch_parts_cut<true>(a, precision, G, cl, grid, stream)
+                                    : launch_parts_cut<false>(a, precision, G, cl, grid, stream);
 }
 
 }  // namespace dsve

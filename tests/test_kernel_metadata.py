@@ -38,3 +38,12 @@ def test_parts_hold_nothing_in_lds_but_what_they_exchange():
         assert exchanged <= k[".group_segment_fixed_size"] <= exchanged + 256, name
         seen += 1
     assert seen >= 90
+
+
+def test_parts_without_a_cut_carry_nothing_of_the_exchange():
+    # k_parts<G, arithmetic, closure, cut>: fewer registers where no channel of the context is cut
+    k = kernels()
+    cut = [n for n in k if re.match(r"_ZN4dsve7k_partsILi\d(ELi\d){2}ELb1E", n)]
+    assert len(cut) == 5 * 3 * 6
+    for n in cut:
+        assert k[n.replace("ELb1E", "ELb0E")][".vgpr_count"] < k[n][".vgpr_count"], n
