@@ -304,7 +304,9 @@ static dsve_status build_table(dsve_ctx *c, int tile, int blocks_per_cu)
 // queues, other processes, long kernels beside them), one part takes the channel over (k_parts).
 // Past that limit (about 7000 cells) the per-step kernels take over, on a stream restricted to some of
 // the compute units too.  Channels of 127 to 255 cells stay with one workgroup of k_resident, as fast
-// as three parts (250 cells: 1.79 against 1.89 us a step), except with the numerical eigensolver.
+// as three parts (250 cells: 1.79 against 1.89 us a step), and with one quadrature node, which leaves
+// little to spread, those up to 511 (511 cells: 1.49 against 1.81, mixed 1.49 against 1.80), except with
+// the numerical eigensolver (10.1 against 6.1).
 static dsve_status plan_parts(dsve_ctx *c, std::vector<Part> &table)
 {
     int64_t longest = 0;
@@ -317,7 +319,7 @@ static dsve_status plan_parts(dsve_ctx *c, std::vector<Part> &table)
         parts += N <= room ? 1 : (N + own - 1) / own;
     }
     if (parts > (cut ? kMaxParts : (int64_t)c->cus)) return DSVE_OK;
-    if (cut && longest <= kResidentSmall && c->precision != PREC_DOT) return DSVE_OK;
+    if (cut && longest <= (c->G == 1 ? kResidentCells : kResidentSmall) && c->precision != PREC_DOT) return DSVE_OK;
     if (cut && parts > max_parts(c->cus, parts_per_cu(c->precision, c->G, c->cl))) return DSVE_OK;
     if (cut) {
         uint32_t mask[32] = {0};

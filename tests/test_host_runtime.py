@@ -246,3 +246,17 @@ def test_a_long_first_run_replays_graphs(host):
         assert h.run(n_steps) == 0
         assert h.count("graphs") == graphs + -(-n_steps // 60) and h.count("steps") == steps
         h.close()
+
+
+def test_where_one_workgroup_is_faster_than_parts(host):
+    def parts(n, **kw):
+        h = Host(host, n, **kw)
+        got = h.in_parts()
+        assert got or n > 511 or h.count("resident") == 1
+        h.close()
+        return got
+
+    # a workgroup holds 126 cells with 3 nodes, 252 with one
+    assert [parts(n) for n in (126, 127, 255, 256, 511, 512)] == [True, False, False, True, True, True]
+    assert [parts(n, n_gauss=1) for n in (252, 253, 511, 512)] == [True, False, False, True]
+    assert [parts(n, n_gauss=1, solver="dot") for n in (252, 253, 511, 512)] == [True] * 4
