@@ -307,7 +307,9 @@ dsve_status dsve_get_cfl_split(const dsve_ctx *ctx, int *split);
  * bitwise those of the per-step kernels; the per-step launch latency, which bounds such
  * small problems, is paid once.  mode 0: automatic (resident when eligible); 1: always
  * per-step kernels.  The launch configuration and CFL sub-slots do not apply to resident
- * runs.  dsve_get_resident reports whether the next run will be resident.  Resident runs
+ * runs.  dsve_get_resident reports whether the next run will be resident: 1 where every channel has at most
+ * 511 cells and the mode is 0, whether one workgroup or several hold a channel; 0 for longer channels that
+ * run in parts (below), which dsve_get_last_run shows afterwards.  Resident runs
  * leave lanes idle in channels much shorter than their workgroup; dsve_autotune compares
  * them with the per-step kernels.
  * With few channels (at most 256 short ones, or about 7000 cells in all) the run is spread over more
@@ -326,11 +328,11 @@ dsve_status dsve_get_resident(const dsve_ctx *ctx, int *active);
  * over tiles of 64..256 threads and 0..128 workgroups per compute unit, then the three
  * fastest with 1 and with 4 CFL sub-slots -- the caller's arrays are read, never written
  * -- and keep the fastest in the context.  If cache_path is not NULL, a JSON cache keyed
- * by device, precision, law, kernel closure and problem shape is read first (a hit sets the
- * launch and returns at once) and updated after tuning.
- * When the context can run channel-resident (and that is not turned off), a resident run
- * is timed too: it stays on if it is the fastest, else it is turned off (mode 1) for the
- * context.  Waits for completion.  Before the trials it waits for the work already
+ * by device, version of the step kernels, precision, law, kernel closure, problem shape and whether runs
+ * in one launch are tried is read first (a hit sets the launch and returns at once) and updated after tuning.
+ * When the context can run channel-resident or in parts (and that is not turned off), such a run
+ * is timed too: it stays on if it is the fastest, else it is turned off for the context
+ * (resident mode 1; for channels of more than 511 cells by the launch that is then set).  Waits for completion.  Before the trials it waits for the work already
  * enqueued and returns that work's deferred error, as dsve_sync would; the trials' own
  * device error flags and CFL maxima are discarded, so a later dsve_sync reports only runs
  * made after tuning.  If a trial fails, the error is sticky and the context keeps the

@@ -797,7 +797,8 @@ static StepArgs step_args(dsve_ctx *ctx, const RunBufs &b, int j, bool from_copy
 // instead, the copy made while the CFL maxima are taken; the packed kernel's copies back at the end.
 static bool starts_from_copy(const dsve_ctx *ctx, int n_steps) { return !ctx->packed && (n_steps & 1); }
 
-// The CFL maxima of W^0 into sub-slot 0 of slot 0, all slots cleared first, and that copy.
+// All slots cleared, then the CFL maxima of W^0 into slot 0 (over segments spread over its sub-slots as in
+// a step, the packed kernel's into sub-slot 0) and, in the same pass, that copy: two launches.
 static dsve_status start_run(dsve_ctx *ctx, const RunBufs &b, int n_steps, double *h, double *q, double *z,
                              double *t)
 {
@@ -1356,12 +1357,12 @@ extern "C" dsve_status dsve_autotune(dsve_ctx *ctx, const double *h, const doubl
     HIP_TRY(ctx, hipEventCreate(&scr.ev[1]));
     double *sh = scr.p[0], *sq = scr.p[1], *sz = scr.p[2], *st_ = scr.p[3];
     hipEvent_t e0 = scr.ev[0], e1 = scr.ev[1];
-    // tile sizes: whole waves; 192 (191 cells per tile) gives the power-of-two channel lengths
-    // a tile count that divides more evenly over the persistent grid than 255 or 127
+    // workgroup sizes: over segments how many waves merge their CFL maxima in LDS before the slot, for the
+    // packed kernel also the tile
     const int tiles[] = {64, 128, 192, 256};
-    // workgroups per compute unit: 0 = as many as are resident at once; counts above that
-    // oversubscribe the persistent grid, so the hardware hands tiles out to workgroups as
-    // others finish
+    // workgroups per compute unit, 0 = automatic: over segments what the tiles are spread over (more and
+    // shorter segments balance better as the hardware hands them out, fewer cost fewer starts and merges),
+    // for the packed kernel its grid, from what is resident at once to several rounds of it
     const int bpcs[] = {0, 1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 64, 128};
     // Candidates run the way a run will: replays of a captured graph when the context uses
     // graphs (a warm-up run captures it, the timed run replays it; 12-step graphs keep the
