@@ -209,13 +209,15 @@ static void drop_table(dsve_ctx *c, void *p)
     c->table_held = false;
 }
 
-// To be called before launches that read the work table.
-static void note_capture(dsve_ctx *c)
+// Whether the caller captures the context's stream; called before launches that read the work table.
+static bool note_capture(dsve_ctx *c)
 {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    if (!c->stream || c->table_held) return;   // (the null stream cannot be captured)
+    if (!c->stream) return false;   // (the null stream cannot be captured)
     if (hipStreamIsCapturing(c->stream, &status) != hipSuccess) (void)hipGetLastError();
-    c->table_held = status == hipStreamCaptureStatusActive;
+    const bool captured = status == hipStreamCaptureStatusActive;
+    c->table_held = c->table_held || captured;
+    return captured;
 }
 
 static dsve_status build_tile_table(dsve_ctx *c, int tile)
@@ -983,9 +985,11 @@ static dsve_status run_steps(dsve_ctx *ctx, double *h, double *q, double *z, int
     // longer than running them (2^20 cells, 20 steps: 0.32 ms on top of 0.42).  From 300 steps on a first
     // run replays too: the capture is paid for by then, and launching holds the calling thread for most of
     // the run (9000 cells, launched and captured: 120 steps 0.66 and 0.75 ms, 300 steps 1.62 and 1.58,
-    // 600 steps 3.3 and 2.9, 2400 steps 11.5 and 11.1, of which 9.2 and 1.9 before the call returns).
+    // 600 steps 3.3 and 2.9, 2400 steps 11.5 and 11.1, of which 9.2 and 1.9 before the call returns), but
+    // where the caller captures it: a graph cannot be launched into another.
     const void *const key[4] = {h, q, z, t};
-    const bool known = ctx->launch_set || n_steps >= kDirectSteps || std::equal(key, key + 4, ctx->last_key) ||
+    const bool captured = note_capture(ctx);
+    const bool known = ctx->launch_set || (n_steps >= kDirectSteps && !captured) || std::equal(key, key + 4, ctx->last_key) ||
                        (ctx->g_keyed && std::equal(key, key + 4, ctx->g_key));
     std::copy(key, key + 4, ctx->last_key);
     const bool replay = ctx->graph_steps > 0 && known;
@@ -993,7 +997,6 @@ static dsve_status run_steps(dsve_ctx *ctx, double *h, double *q, double *z, int
         st = ensure_graphs(ctx, h, q, z, t, n_steps);
         if (st != DSVE_OK) return st;
     }
-    note_capture(ctx);
     const RunBufs b = ctx_bufs(ctx);
     const bool from_copy = starts_from_copy(ctx, n_steps);
     st = start_run(ctx, b, n_steps, h, q, z, t);
@@ -1100,7 +1103,7 @@ dsve_status adot_step_noalloc(dsve_ctx *ctx, double *h, double *q, double *z, in
     if (ctx->packed ? (!ctx->d_tile_chan || ctx->table_tile != ctx->tile)
                     : (!ctx->d_segments || ctx->seg_tiles != segment_length(ctx, ctx->tile, ctx->blocks_per_cu)))
         return fail(ctx, DSVE_E_HIP, "adot_step_noalloc: no work table for the current launch");
-    note_capture(ctx);
+    (void)note_capture(ctx);
     const bool from_copy = starts_from_copy(ctx, n_steps);
     dsve_status st = start_run(ctx, b, n_steps, h, q, z, t_dev);
     if (st != DSVE_OK) return st;

@@ -51,3 +51,30 @@ def test_replays_after_another_launch(dsve, shape):
         torch.cuda.synchronize()
         assert all(np.array_equal(s.cpu().numpy(), w) for s, w in zip(state, want)), launch
     ctx.close()
+
+
+def test_a_long_first_run_under_capture(dsve):
+    # 330 steps: a first run of that length replays graphs of its own, but for under capture
+    import torch
+    wl = inputs.make_c2(n_cells=9000, steps=330, length=1000.0 * 9000 / (1 << 20))
+    stream = torch.cuda.Stream()
+    ctx = dsve.Context.from_workload(wl, stream=stream)
+    first = dsve.upload(wl)
+    state = [x.clone() for x in first]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        ctx.adot_step(*state[:3], wl.steps, state[3])
+    assert ctx.last_run() == (0, 0, wl.steps)
+    for _ in range(3):
+        with torch.cuda.stream(stream):
+            own = [x.clone() for x in first]
+            ctx.adot_step(*own[:3], wl.steps, own[3])
+        ctx.sync()
+        for s, f in zip(state, first):
+            s.copy_(f)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(s, o) for s, o in zip(state, own))
+    ctx.close()

@@ -248,6 +248,14 @@ def test_a_long_first_run_replays_graphs(host):
         h.close()
 
 
+def test_a_captured_first_run_launches_its_steps(host):
+    # graphs are not launched into the caller's own
+    h = Host(host, 20_000, dict(capturing=1), stream=64)
+    assert h.run(600) == 0
+    assert (h.count("captures"), h.count("graphs"), h.count("steps")) == (0, 0, 600)
+    h.close()
+
+
 def test_where_one_workgroup_is_faster_than_parts(host):
     def parts(n, **kw):
         h = Host(host, n, **kw)

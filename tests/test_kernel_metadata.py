@@ -3,8 +3,9 @@ import os
 import re
 import struct
 
-import msgpack
 import pytest
+
+msgpack = pytest.importorskip("msgpack")
 
 LIB = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1912_04791_amd", "libdsve.so")
 
